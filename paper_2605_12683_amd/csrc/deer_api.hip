@@ -295,6 +295,8 @@ struct PlrnnWs {
     float *P, *v, *carry, *gws;
     float *gmap;   // M <= 16, 32 | chunks: group maps [B][chunks / 32][16 x 16 + 16]
     float *P2, *v2, *gmap2;   // the second set of aggregates of the fused passes (else null)
+    int *changed;             // M > 16 solve: chunks whose masks changed in this pass,
+    float *pgam;              // and the damping of each chunk's stored product
     NewtonCtl ctl;
     float *gpart;
     double *gpart2;
@@ -328,6 +330,10 @@ static PlrnnWs carve_plrnn(void *ws, int B, int T, int M, int op, size_t *bytes)
     if (op == DEER_OP_SOLVE) {
         w.ctl = carve_ctl(c, B, (size_t)T * M, nch);
         w.r = c.take<float>((size_t)B * T * M);
+        if (w.MP > 16) {
+            w.changed = c.take<int>(nch);
+            w.pgam = c.take<float>(nch);
+        }
     } else {
         w.gpart = c.take<float>(nch * w.MP * (w.MP + 2));
         w.gpart2 = c.take<double>(reduce_gpart_ws_bytes(w.MP) / sizeof(double));
@@ -853,11 +859,13 @@ static int solve_plrnn(const deer_model *m, const deer_forcing *f, const deer_so
         if (masks && (rc = launch_resjac_plrnn(a, z, nullptr, nullptr, nullptr, masks, nullptr, st))) return rc;
         return finish_solve(o, B, it, norm, nonfinite, act, iters, final_norm);
     }
-    // M <= 16: the fix-up also takes the pass-end control of the adaptive loop
+    // the fix-up also takes the pass-end control of the adaptive loop
     NewtonCtl ctl = w.ctl;
-    ctl.fused = w.MP == 16 && o->fixed_iters <= 0;
+    ctl.fused = plrnn_fixup_control(m->M) && o->fixed_iters <= 0;
     // one kernel per pass: the fix-up of the previous update and the forward pass of the next
     const bool pass16 = ctl.fused && w.P2;
+    // no chunk product is stored yet
+    if (w.pgam && (rc = launch_fill_f32(w.pgam, (size_t)B * w.ncs, NAN, st))) return rc;
     if (pass16) {
         ctl.nd.pv = ctl.pv;
         ctl.lead = 1;
@@ -880,9 +888,17 @@ static int solve_plrnn(const deer_model *m, const deer_forcing *f, const deer_so
         // group map and the fix-up walks the group maps itself (no carry kernel)
         const bool wm = w.MP == 16 && w.ncs % 4 == 0, gm = w.gmap != nullptr;
         const int mode = gm ? 2 : (wm ? 1 : 0);
-        if ((r = launch_newton_product_plrnn(a, zb, za, zsel, w.r, w.masks, w.P, w.v, dact, gam, w.C, w.ncs, mode,
-                                             w.gmap, mark, pass_no, st)))
-            return r;
+        if (w.MP == 16) {
+            if ((r = launch_newton_product_plrnn16(a, zb, za, zsel, w.P, w.v, dact, gam, w.C, w.ncs, mode, w.gmap, mark,
+                                                   pass_no, st)))
+                return r;
+        } else {
+            if ((r = launch_newton_local_plrnn(a, zb, za, zsel, w.r, w.masks, w.changed, w.v, dact, gam, w.C, w.ncs,
+                                               mark, pass_no, st)))
+                return r;
+            if ((r = launch_chunk_product_split(a, false, w.masks, w.changed, w.pgam, w.P, dact, gam, w.C, w.ncs, st)))
+                return r;
+        }
         if (gm) r = 0;
         else if (wm) r = launch_carry_walk16(false, w.P, w.v, w.carry, dact, B, w.ncs, st);
         else r = launch_carry(w.MP, false, w.P, w.v, w.carry, dact, nullptr, B, w.ncs, w.gws, st);

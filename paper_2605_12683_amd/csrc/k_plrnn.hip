@@ -5,7 +5,8 @@
 // Kernels (one Newton iteration = resjac -> chunk products -> carries -> fix-up):
 //   k_resjac_plrnn     residual r_t, masks m_t (and optionally F, dense J~) at every step
 //   k_chunk_product    per chunk of C steps: P_c = J~_e ... J~_s on the matrix cores (fp32
-//                      MFMA) and v_c = the chunk's local solution from a zero carry (VALU)
+//                      MFMA) and v_c = the chunk's local solution from a zero carry (VALU);
+//                      the forward pass at M > 16 is in k_split.hip
 //   k_carry            carries across chunks, one wave per sequence
 //   k_fixup_fwd        Delta_t = J~_t Delta_{t-1} - r_t from the carry, z += Delta, max|Delta|
 //   k_fixup_rev        lam_{t-1} = J~_t^T lam_t + g_{t-1} from the carry, fused parameter-
@@ -336,230 +337,6 @@ __global__ __launch_bounds__(64) void k_chunk_product_plrnn(
         const int id = chain0 + un;
         if (id < nchains) vout[(size_t)id * MP + ui] = u;
     }
-}
-
-// ---------------------------------------------------------------------------------------
-// Forward Newton pass with the residual fused in: per step of every chain the wave forms
-// z~_t, its ReLU ballot (which is at once the mask of the matrix-core bit select), F,
-// r_t = z_t - F, and advances both the chunk product and the chunk-local solution.
-// r and the masks are written for the fix-up pass.  Same MFMA layout as above.
-// ---------------------------------------------------------------------------------------
-template <int MP, bool WU>
-__global__ __launch_bounds__(64) void k_newton_product_plrnn(
-    const float *__restrict__ A, const float *__restrict__ W, const float *__restrict__ h, float alpha, int N,
-    const float *__restrict__ x, const float *__restrict__ z0, const float *zbuf, const float *zalt,
-    const int *__restrict__ zsel, float *__restrict__ r_out, uint32_t *__restrict__ masks, float *__restrict__ Pout,
-    float *__restrict__ vout, const int *__restrict__ active, const float *__restrict__ gamma, int B, int T, int M, int C,
-    int ncs, int tw) {
-    using G = Geo<MP>;
-    constexpr int NCH = G::NCH, NI = G::NI, NS = G::NS, MW = G::MW;
-    __shared__ __align__(16) float lds[64];
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int nchains = B * ncs;
-    const int chain0 = blockIdx.x * NCH;
-    int plen[NCH], cst[NCH];              // steps and first step of each chain
-    float gam[NCH];                       // damping of the linearisation (1 = exact Newton)
-    int maxlen = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n) {
-        const int id = chain0 + n;
-        bool ok = id < nchains;
-        const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
-        ok = ok && (!active || active[b]);
-        const int s0 = cc * C;
-        plen[n] = ok ? min(C, T - s0) : 0;
-        cst[n] = s0;
-        gam[n] = gamma ? gamma[b] : 1.f;
-        maxlen = max(maxlen, plen[n]);
-    }
-    float Aop[NI][NS];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * I + c, col = 16 * j + 4 * g + q;
-                Aop[I][4 * j + q] = (row < M && col < M) ? W[row * M + col] * p_of(col, N, alpha) : 0.f;
-            }
-    float dI[NI][4];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * I + 4 * g + r;
-            dI[I][r] = row < M ? A[row] * p_of(row, N, alpha) : 0.f;
-        }
-    if (NCH == 1) {   // one chain per wave: fold its damping into the operands once
-#pragma unroll
-        for (int I = 0; I < NI; ++I) {
-#pragma unroll
-            for (int s2 = 0; s2 < NS; ++s2) Aop[I][s2] *= gam[0];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) dI[I][r] *= gam[0];
-        }
-    }
-    // latent warm-up steps (P_1): the observed latents' rows of the diagonal term are dropped
-    float dIw[NI][4];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dIw[I][r] = (WU && 16 * I + 4 * g + r < N) ? 0.f : dI[I][r];
-    v4f acc[NI][4];
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int col = 16 * Jt + c - n * MP;
-#pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == col) ? 1.f : 0.f;
-    }
-    // lane-per-row part: lane = (chain un, latent ui)
-    const int un = lane / MP, ui = lane % MP;
-    const int uid = chain0 + un;
-    const bool uok0 = uid < nchains;
-    const int ub = uok0 ? uid / ncs : 0, us0 = uok0 ? (uid % ncs) * C : 0;
-    int ulen = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n)
-        if (n == un) ulen = plen[n];
-    const bool lat = ui < M;
-    float wrow[MP];
-#pragma unroll
-    for (int k = 0; k < MP; ++k) wrow[k] = (lat && k < M) ? W[ui * M + k] : 0.f;
-    const float Ai = lat ? A[ui] : 0.f, hi = (lat && h) ? h[ui] : 0.f;
-    const float pi = p_of(ui, N, alpha), di = Ai * pi;
-    const bool forced = ui < N;
-    float ugam = 1.f;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n)
-        if (n == un) ugam = gam[n];
-    const float *z = cur_iter(zbuf, zalt, zsel, ub);   // this lane's sequence's iterate
-    // z_{s-1} for the first step of the chunk
-    float zprev = 0.f;
-    if (ulen > 0 && lat) {
-        if (us0 == 0) zprev = z0 ? z0[(size_t)ub * M + ui] : (forced ? x[(size_t)ub * (T + 1) * N + ui] : 0.f);
-        else zprev = z[((size_t)ub * T + us0 - 1) * M + ui];
-    }
-    float u = 0.f;
-    // z_s and x_s are loaded PD steps ahead (a queue shifted by one every step)
-    constexpr int PD = 1;
-    float zq[PD], xq[PD];
-    auto fetch = [&](int t, float &zv, float &xv) {
-        zv = 0.f;
-        xv = 0.f;
-        if (t < ulen && lat) {
-            zv = z[((size_t)ub * T + us0 + t) * M + ui];
-            if (forced) xv = x[((size_t)ub * (T + 1) + us0 + t) * N + ui];
-        }
-    };
-#pragma unroll
-    for (int q = 0; q < PD; ++q) fetch(q, zq[q], xq[q]);
-    for (int t = 0; t < maxlen; ++t) {
-        const bool run = t < ulen && lat;
-        const int s = us0 + t;
-        const float zcur = zq[0], xb = xq[0];
-#pragma unroll
-        for (int q = 0; q + 1 < PD; ++q) {
-            zq[q] = zq[q + 1];
-            xq[q] = xq[q + 1];
-        }
-        fetch(t + PD, zq[PD - 1], xq[PD - 1]);
-        // forced state of this step (s == 0: z_0 itself)
-        float zt = 0.f;
-        if (run) {
-            if (s == 0 || !forced) zt = zprev;
-            else zt = forced_in<WU>(pi, alpha, zprev, xb, s, tw);
-        }
-        const bool pos = zt > 0.f;
-        const uint64_t bal = __ballot(pos);
-        lds[lane] = pos ? zt : 0.f;
-        lds_barrier();
-        const float F = fmaf(Ai, zt, lds_dot<MP>(lds, un, wrow)) + hi;
-        lds_barrier();
-        const float r = zcur - F;
-        if (run) {
-            const size_t e = ((size_t)ub * T + s) * M + ui;
-            r_out[e] = r;
-            if (ui == 0) {
-                const size_t step = (size_t)ub * T + s;
-                if (MP == 64) {
-                    masks[step * 2] = (uint32_t)bal;
-                    if (M > 32) masks[step * 2 + 1] = (uint32_t)(bal >> 32);
-                } else {
-                    const uint64_t seg = bal >> (un * MP);
-                    masks[step] = (uint32_t)(MP == 32 ? seg : (seg & 0xffffull));
-                }
-            }
-        }
-        // matrix-core step of every chain still running
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt) {
-            const int n = (16 * Jt) / MP;
-            if (t < plen[n]) {
-                const uint64_t seg = bal >> (n * MP);
-                const uint32_t w0 = (uint32_t)seg;
-                const uint32_t w1 = (uint32_t)(seg >> 32);
-                float Bop[NS];
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j) {
-                    const uint32_t wj = (j >> 1) ? w1 : w0;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) Bop[4 * j + q] = select_bit(wj, 16 * (j & 1) + 4 * g + q, acc[j][Jt][q]);
-                }
-                const bool warm = WU && cst[n] + t <= tw;   // P_1: the observed latents' rows dropped
-                if (warm) {
-#pragma unroll
-                    for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (16 * j + 4 * g + q < N) Bop[4 * j + q] = 0.f;
-                }
-                if (NCH > 1 && gam[n] != 1.f) {   // damped chain (uniform branch)
-                    const float gm = gam[n];
-#pragma unroll
-                    for (int s2 = 0; s2 < NS; ++s2) Bop[s2] *= gm;
-#pragma unroll
-                    for (int I = 0; I < NI; ++I)
-#pragma unroll
-                        for (int r2 = 0; r2 < 4; ++r2) acc[I][Jt][r2] *= gm;
-                }
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r2 = 0; r2 < 4; ++r2) acc[I][Jt][r2] *= warm ? dIw[I][r2] : dI[I][r2];
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int s2 = 0; s2 < NS; ++s2) acc[I][Jt] = mfma16x16x4(Aop[I][s2], Bop[s2], acc[I][Jt]);
-            }
-        }
-        // chunk-local solution: u <- gamma (d u + W (p m u)) - r
-        const float uo = (WU && forced && us0 + t <= tw) ? 0.f : u;   // P_s u
-        lds[lane] = pos ? pi * uo : 0.f;
-        lds_barrier();
-        const float y = fmaf(di, uo, lds_dot<MP>(lds, un, wrow));
-        lds_barrier();
-        if (run) {
-            u = fmaf(ugam, y, -r);
-            zprev = zcur;
-        }
-    }
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int id = chain0 + n;
-        if (id < nchains && plen[n] > 0) {
-            const int col = 16 * Jt + c - n * MP;
-            float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r2 = 0; r2 < 4; ++r2) P[(16 * I + 4 * g + r2) * MP + col] = acc[I][Jt][r2];
-        }
-    }
-    if (uok0) vout[(size_t)uid * MP + ui] = u;
 }
 
 // A-operand fragments of a 16 x 16 map (P_c, or its transpose) and the vector v_c for the
@@ -1820,208 +1597,6 @@ __global__ __launch_bounds__(512) void k_newton_pass16(
 }
 
 // ---------------------------------------------------------------------------------------
-// The same forward Newton pass for M = 64 when every latent has the same forcing factor p
-// (N = 0 or N = M).  Then the forced Jacobian factors as
-//   J~_t = gp (diag(A) + W diag(m_t)),   gp = gamma p,
-// so W itself (unscaled, in LDS) serves the matrix-core A operand, the residual F and the
-// chunk-local solution, and no M x M operand lives in registers: the kernel fits two waves per
-// SIMD, and one wave's VALU/LDS phase overlaps the other's matrix-core phase.  The scalar gp
-// is applied to the chunk product every 8 steps (acc *= gp^8) instead of every step.
-// One chain per wave (64 lanes = 64 latents for the lane-per-row part).
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ float lds_row_dot64(const float (*wl)[68], int row, const float *vec) {
-    const float4 *w4 = reinterpret_cast<const float4 *>(wl[row]);
-    const float4 *v4 = reinterpret_cast<const float4 *>(vec);
-    float a0 = 0.f, a1 = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; q += 2) {
-        const float4 w0 = w4[q], x0 = v4[q], w1 = w4[q + 1], x1 = v4[q + 1];
-        a0 = fmaf(w0.x, x0.x, a0); a0 = fmaf(w0.y, x0.y, a0); a0 = fmaf(w0.z, x0.z, a0); a0 = fmaf(w0.w, x0.w, a0);
-        a1 = fmaf(w1.x, x1.x, a1); a1 = fmaf(w1.y, x1.y, a1); a1 = fmaf(w1.z, x1.z, a1); a1 = fmaf(w1.w, x1.w, a1);
-    }
-    return a0 + a1;
-}
-
-// M = 64 with a uniform forcing factor (every latent forced, or none): one chain per wave, two
-// waves per SIMD.  J_F = diag(A) + W diag(m) is the matrix-core A operand: W + diag(A) is staged in
-// LDS once, and every step masks its columns with the step's ReLU bits (a column k of W is kept
-// where m_k = 1; the diagonal entry becomes A_k where m_k = 0), one row tile of 16 at a time,
-// shared by the four column tiles.  The chunk product alternates between two accumulator sets
-// (the previous step's set is the unmasked B operand), so no copy, mask or scaling of the
-// accumulators is needed per step; the factor gamma p is applied every 8 steps.  The residual
-// and the chunk-local solution are row dot products against the same LDS rows, corrected for
-// the diagonal: F_i = (W + diag A)_i relu(z~) + A_i min(z~_i, 0), and
-// y_i = (W + diag A)_i (m o u) + A_i u_i (1 - m_i).
-template <bool WU>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_newton_product_plrnn64u(
-    const float *__restrict__ A, const float *__restrict__ W, const float *__restrict__ h, float alpha, int N,
-    const float *__restrict__ x, const float *__restrict__ z0, const float *zbuf, const float *zalt,
-    const int *__restrict__ zsel, float *__restrict__ r_out, uint32_t *__restrict__ masks, float *__restrict__ Pout,
-    float *__restrict__ vout, const int *__restrict__ active, const float *__restrict__ gamma, int B, int T, int M, int C,
-    int ncs, int tw) {
-    constexpr int MP = 64, NI = 4;
-    __shared__ __align__(16) float wl[MP][68];   // W + diag(A), zero padded
-    __shared__ __align__(16) float lds[64];
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int id = blockIdx.x;
-    const bool ok0 = id < B * ncs;
-    const int b = ok0 ? id / ncs : 0, s0 = ok0 ? (id % ncs) * C : 0;
-    const bool ok = ok0 && (!active || active[b]);
-    const int len = ok ? min(C, T - s0) : 0;
-    for (int e = lane; e < MP * MP; e += 64) {
-        const int row = e / MP, col = e % MP;
-        wl[row][col] = (row < M && col < M) ? W[row * M + col] + (row == col ? A[row] : 0.f) : 0.f;
-    }
-    const float p = N > 0 ? __fsub_rn(1.0f, alpha) : 1.0f;
-    const float gp = (gamma ? gamma[b] : 1.f) * p;
-    const float gp2 = gp * gp, gp4 = gp2 * gp2, gp8 = gp4 * gp4;
-    // latent warm-up with every latent observed (N = M): the Jacobians of steps s <= tw are zero
-    // (P_1 = 0), so a chunk that holds one has P = 0 (the product runs unchanged and is zeroed at
-    // the end) and u restarts from -r there; N = 0 has no observed latent and no change
-    const bool warmchunk = WU && N > 0 && s0 <= tw;
-    // diagonal entries of this lane's A fragments: row 16 I + c is column 16 I + 4 g + q where
-    // c == 4 g + q; there the masked entry is A instead of 0
-    uint32_t dgA[NI][4];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            dgA[I][q] = (c == 4 * g + q && 16 * I + c < M) ? __float_as_uint(A[16 * I + c]) : 0u;
-    v4f acc[NI][4], acc2[NI][4];
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt)
-#pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 16 * Jt + c) ? 1.f : 0.f;
-    // lane-per-row part: lane = latent
-    const int ui = lane;
-    const bool lat = ui < M;
-    const float Ai = lat ? A[ui] : 0.f, hi = (lat && h) ? h[ui] : 0.f;
-    const bool forced = ui < N;
-    const float *z = cur_iter(zbuf, zalt, zsel, b);
-    float zprev = 0.f;
-    if (len > 0 && lat) {
-        if (s0 == 0) zprev = z0 ? z0[(size_t)b * M + ui] : (forced ? x[(size_t)b * (T + 1) * N + ui] : 0.f);
-        else zprev = z[((size_t)b * T + s0 - 1) * M + ui];
-    }
-    float u = 0.f;
-    float zn = 0.f, xn = 0.f;
-    if (len > 0 && lat) {
-        zn = z[((size_t)b * T + s0) * M + ui];
-        if (forced) xn = x[((size_t)b * (T + 1) + s0) * N + ui];
-    }
-    lds_barrier();   // W + diag(A) in LDS
-    const int maxlen = __builtin_amdgcn_readfirstlane(len);
-    // one step of the chain product, from accumulator set `in` to set `out`
-    auto product = [&](const v4f (&in)[NI][4], v4f (&out)[NI][4], uint32_t w0, uint32_t w1) {
-        uint32_t mk[4][4];   // all ones where the ReLU of column 16 j + 4 g + q is on
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                mk[j][q] = (uint32_t)__builtin_amdgcn_sbfe((int)((j >> 1) ? w1 : w0), 16 * (j & 1) + 4 * g + q, 1);
-#pragma unroll
-        for (int I = 0; I < NI; ++I) {
-            float a[4][4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float4 a4 = *reinterpret_cast<const float4 *>(&wl[16 * I + c][16 * j + 4 * g]);
-                const float av[4] = {a4.x, a4.y, a4.z, a4.w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t wb = __float_as_uint(av[q]);
-                    // (m & (W + A delta)) | (~m & A delta): the diagonal tile keeps A where m = 0
-                    a[j][q] = __uint_as_float(j == I ? ((mk[j][q] & wb) | (~mk[j][q] & dgA[I][q])) : (mk[j][q] & wb));
-                }
-            }
-#pragma unroll
-            for (int Jt = 0; Jt < 4; ++Jt) {
-                v4f s = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) s = mfma16x16x4(a[j][q], in[j][Jt][q], s);
-                out[I][Jt] = s;
-            }
-        }
-    };
-    auto step = [&](int t, const v4f (&in)[NI][4], v4f (&out)[NI][4]) {
-        const bool run = lat;
-        const int s = s0 + t;
-        const float zcur = zn, xb = xn;
-        if (t + 1 < len && lat) {
-            zn = z[((size_t)b * T + s + 1) * M + ui];
-            if (forced) xn = x[((size_t)b * (T + 1) + s + 1) * N + ui];
-        }
-        float zt = 0.f;
-        if (run) {
-            if (s == 0 || !forced) zt = zprev;
-            else zt = forced_in<WU>(p, alpha, zprev, xb, s, tw);
-        }
-        const bool pos = zt > 0.f;
-        const uint64_t bal = __ballot(pos);
-        lds[lane] = pos ? zt : 0.f;
-        lds_barrier();
-        const float F = fmaf(Ai, fminf(zt, 0.f), lds_row_dot64(wl, ui, lds)) + hi;
-        lds_barrier();
-        const float r = zcur - F;
-        if (run) {
-            r_out[((size_t)b * T + s) * M + ui] = r;
-            if (ui == 0) {
-                const size_t stp = (size_t)b * T + s;
-                masks[stp * 2] = (uint32_t)bal;
-                if (M > 32) masks[stp * 2 + 1] = (uint32_t)(bal >> 32);
-            }
-        }
-        // P <- (diag(A) + W diag(m)) P   (the factor gp is applied every 8 steps)
-        product(in, out, (uint32_t)bal, (uint32_t)(bal >> 32));
-        if ((t & 7) == 7) {
-#pragma unroll
-            for (int Jt = 0; Jt < 4; ++Jt)
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r2 = 0; r2 < 4; ++r2) out[I][Jt][r2] *= gp8;
-        }
-        // chunk-local solution: u <- gp (A o u + W (m o u)) - r
-        lds[lane] = pos ? u : 0.f;
-        lds_barrier();
-        const float y = fmaf(Ai, pos ? 0.f : u, lds_row_dot64(wl, ui, lds));
-        lds_barrier();
-        if (run) {
-            const float gps = (warmchunk && s <= tw) ? 0.f : gp;   // J~_s = 0 in a warm-up step
-            u = fmaf(gps, y, -r);
-            zprev = zcur;
-        }
-    };
-    int t = 0;
-    for (; t + 1 < maxlen; t += 2) {
-        step(t, acc, acc2);
-        step(t + 1, acc2, acc);
-    }
-    if (t < maxlen) {   // odd length: the last step lands in the second set
-        step(t, acc, acc2);
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I) acc[I][Jt] = acc2[I][Jt];
-    }
-    if (ok0 && len > 0) {
-        float rest = warmchunk ? 0.f : 1.f;
-        for (int k = 0; k < (len & 7); ++k) rest *= gp;
-        float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r2 = 0; r2 < 4; ++r2) P[(16 * I + 4 * g + r2) * MP + 16 * Jt + c] = acc[I][Jt][r2] * rest;
-    }
-    if (ok0) vout[(size_t)id * MP + ui] = u;
-}
-
-// ---------------------------------------------------------------------------------------
 // carries across chunks
 //   forward: carry_in[c] = y_end(c-1),  y_end(c) = P_c y_end(c-1) + v_c
 //   reverse: carry_in[c] = lam_{s1(c)}, lam_{s0(c)} = P_c^T lam_{s1(c)} + v_c
@@ -2953,7 +2528,7 @@ __global__ __launch_bounds__(MP * 4) void k_fixup_fwd_plrnn_mf(const float *__re
                                                                uint32_t *__restrict__ chain_bits,
                                                                const int *__restrict__ active,
                                                                const float *__restrict__ gamma, int B, int T, int M,
-                                                               int C, int ncs, int tw) {
+                                                               int C, int ncs, int tw, FusedCtl fc) {
     using G = Geo<MP>;
     constexpr int NW = MP / 16, NS = MP / 4, DQ = MP + 4;
     __shared__ __align__(16) float dls[2][16 * DQ];   // [buffer][chain c][latent]
@@ -3130,15 +2705,19 @@ __global__ __launch_bounds__(MP * 4) void k_fixup_fwd_plrnn_mf(const float *__re
         mx[wv][c][1] = zmax;
     }
     lds_barrier();
-    if (wv == 0 && g == 0 && ok) {   // reduced per sequence by the pass-end control
+    if (wv != 0) return;
+    if (g == 0 && ok) {
 #pragma unroll
         for (int w = 1; w < NW; ++w) {
             emax = emax > mx[w][c][0] ? emax : mx[w][c][0];
             zmax = zmax > mx[w][c][1] ? zmax : mx[w][c][1];
         }
-        chain_bits[id] = emax;
-        chain_bits[(size_t)nchains + id] = zmax;
+        if (!fc.seq) {   // reduced per sequence by k_seq_ctl / k_seq_max
+            chain_bits[id] = emax;
+            chain_bits[(size_t)nchains + id] = zmax;
+        }
     }
+    if (fc.seq) block16_arrive(fc, emax, zmax, ok, blockIdx.x * 16, ncs, lane);
 }
 
 // per-sequence max over its chains of the bits the forward fix-ups left:
@@ -3512,33 +3091,16 @@ int launch_chunk_product_plrnn(const PlrnnArgs &a, bool rev, const uint32_t *mas
     return DEER_OK;
 }
 
-int launch_newton_product_plrnn(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *r,
-                                uint32_t *masks, float *P, float *v, const int *active, const float *gamma, int C,
-                                int ncs, int wmaps, float *gmap, uint32_t *mark, uint32_t pass_no, hipStream_t st) {
-    const int MP = padded(a.M);
+int launch_newton_product_plrnn16(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *P,
+                                  float *v, const int *active, const float *gamma, int C, int ncs, int wmaps,
+                                  float *gmap, uint32_t *mark, uint32_t pass_no, hipStream_t st) {
+    if (a.M > 16) return invalid_arg("the register-tiled forward pass needs M <= 16");
     const int nch = a.B * ncs;
-    const int grid = (nch + (64 / MP) - 1) / (64 / MP);
+    const int grid = (nch + 3) / 4;
     KTimer kt("k_newton_product_plrnn", st);
-    if (wmaps == 2 && (MP != 16 || ncs % 32 || !gmap))
-        return invalid_arg("group maps need M <= 16, a chunk count divisible by 32 and their buffer");
-#define NP(MPV)                                                                                                    \
-    if (a.tw > 0)                                                                                                  \
-        hipLaunchKernelGGL((k_newton_product_plrnn<MPV, true>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.h, a.alpha, \
-                           a.N, a.x, a.z0, z, zalt, zsel, r, masks, P, v, active, gamma, a.B, a.T, a.M, C, ncs, a.tw); \
-    else                                                                                                           \
-        hipLaunchKernelGGL((k_newton_product_plrnn<MPV, false>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.h, a.alpha, \
-                           a.N, a.x, a.z0, z, zalt, zsel, r, masks, P, v, active, gamma, a.B, a.T, a.M, C, ncs, 0)
-    if (wmaps && (MP != 16 || ncs % 4))
-        return invalid_arg("composed wave maps need M <= 16 and a chunk count divisible by 4");
-    if (mark && MP != 16) return invalid_arg("pass marks are written by the M <= 16 forward pass only");
-    if (MP == 64 && (a.N == 0 || a.N == a.M)) {   // uniform forcing factor: W-in-LDS kernel
-        if (a.tw > 0)
-            hipLaunchKernelGGL(k_newton_product_plrnn64u<true>, dim3(nch), dim3(64), 0, st, a.A, a.W, a.h, a.alpha, a.N,
-                               a.x, a.z0, z, zalt, zsel, r, masks, P, v, active, gamma, a.B, a.T, a.M, C, ncs, a.tw);
-        else
-            hipLaunchKernelGGL(k_newton_product_plrnn64u<false>, dim3(nch), dim3(64), 0, st, a.A, a.W, a.h, a.alpha,
-                               a.N, a.x, a.z0, z, zalt, zsel, r, masks, P, v, active, gamma, a.B, a.T, a.M, C, ncs, 0);
-    } else if (MP == 16) {
+    if (wmaps == 2 && (ncs % 32 || !gmap))
+        return invalid_arg("group maps need a chunk count divisible by 32 and their buffer");
+    if (wmaps && ncs % 4) return invalid_arg("composed wave maps need a chunk count divisible by 4");
 #define NP16(TBV, WPBV)                                                                                                \
     hipLaunchKernelGGL((k_newton_product_plrnn16<TBV, WPBV, WUV>), dim3(grid / WPBV), dim3(64 * WPBV), 0, st, a.A, a.W, \
                        a.h, a.alpha, a.N, a.x, a.z0, z, zalt, zsel, P, v, active, gamma, a.B, a.T, a.M, C, ncs, wmaps, \
@@ -3551,19 +3113,13 @@ int launch_newton_product_plrnn(const PlrnnArgs &a, const float *z, const float 
         constexpr bool WUV = false; \
         NP16(TBV, WPBV);            \
     }
-        if (wmaps == 2) {
-            if (C % 32) { NP16W(16, 8) } else { NP16W(32, 8) }
-        } else {
-            if (C % 32) { NP16W(16, 1) } else { NP16W(32, 1) }
-        }
+    if (wmaps == 2) {
+        if (C % 32) { NP16W(16, 8) } else { NP16W(32, 8) }
+    } else {
+        if (C % 32) { NP16W(16, 1) } else { NP16W(32, 1) }
+    }
 #undef NP16W
 #undef NP16
-    } else if (MP == 32) {
-        NP(32);
-    } else {
-        NP(64);
-    }
-#undef NP
     DEER_LAUNCH_CHECK("k_newton_product_plrnn");
     return DEER_OK;
 }
@@ -3687,6 +3243,8 @@ static bool fixup_mfma() {
     return !e || atoi(e) != 0;
 }
 
+bool plrnn_fixup_control(int M) { return M <= 16 || fixup_mfma(); }
+
 int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const float *r, const float *carry_in,
                            float *z, float *zalt, const int *zsel, uint32_t *chain_bits, const int *active,
                            const float *gamma, int C, int ncs, const float *Pm, const float *vm,
@@ -3709,7 +3267,7 @@ int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const floa
     if (gmap && (!Pm || ncs % 32)) return invalid_arg("group maps need the wave maps and 32 | chunk count");
     if (Pm && (MP != 16 || ncs % 4))
         return invalid_arg("composed wave maps need M <= 16 and a chunk count divisible by 4");
-    if (fc && MP != 16) return invalid_arg("the fused pass-end control needs M <= 16");
+    if (fc && !plrnn_fixup_control(a.M)) return invalid_arg("this fix-up does not take the pass-end control");
     FusedCtl fcv{};
     if (fc) fcv = *fc;
     if (MP == 16) {
@@ -3726,11 +3284,11 @@ int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const floa
     if (a.tw > 0)                                                                                                     \
         hipLaunchKernelGGL((k_fixup_fwd_plrnn_mf<MPV, VV, true>), dim3(gridm), dim3(MPV * 4), 0, st, a.A, a.W, a.alpha, \
                            a.N, masks, r, carry_in, z, zalt, zsel, chain_bits, active, gamma, a.B, a.T, a.M, C, ncs,  \
-                           a.tw);                                                                                     \
+                           a.tw, fcv);                                                                                \
     else                                                                                                              \
         hipLaunchKernelGGL((k_fixup_fwd_plrnn_mf<MPV, VV, false>), dim3(gridm), dim3(MPV * 4), 0, st, a.A, a.W,       \
                            a.alpha, a.N, masks, r, carry_in, z, zalt, zsel, chain_bits, active, gamma, a.B, a.T, a.M, \
-                           C, ncs, 0)
+                           C, ncs, 0, fcv)
         const bool v4 = (a.M & 3) == 0;
         if (MP == 32) {
             if (v4) { FXM(32, true); } else { FXM(32, false); }

@@ -615,31 +615,8 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
         }
     }
     if (!fc.seq) return;
-    // fused pass-end control: lane 0 gathers the 16 chains' maxima and arrives once per
-    // sequence they belong to (chains of a sequence that is not running do not arrive)
-    uint32_t em[16], zm[16];
-    bool okc[16];
-#pragma unroll
-    for (int n = 0; n < 16; ++n) {
-        em[n] = (uint32_t)__shfl((int)emax, n, 64);
-        zm[n] = (uint32_t)__shfl((int)zmax, n, 64);
-        okc[n] = __shfl((int)ok, n, 64) != 0;
-    }
-    if (lane != 0) return;
-    const int chain0 = blockIdx.x * 16;
-    for (int n = 0; n < 16; ++n) {
-        if (!okc[n]) continue;
-        const int bn = (chain0 + n) / ncs;
-        if (n > 0 && okc[n - 1] && (chain0 + n - 1) / ncs == bn) continue;   // counted with its first chain
-        uint32_t E = 0u, Z = 0u;
-        int cnt = 0;
-        for (int m2 = n; m2 < 16 && okc[m2] && (chain0 + m2) / ncs == bn; ++m2) {
-            E = E > em[m2] ? E : em[m2];
-            Z = Z > zm[m2] ? Z : zm[m2];
-            ++cnt;
-        }
-        seq_arrive(fc, bn, cnt, ncs, E, Z);
-    }
+    // fused pass-end control (chains of a sequence that is not running do not arrive)
+    block16_arrive(fc, emax, zmax, ok, blockIdx.x * 16, ncs, lane);
 }
 
 // ---------------------------------------------------------------------------------------

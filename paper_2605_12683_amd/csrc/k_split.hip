@@ -1,0 +1,510 @@
+// Vanilla PLRNN, 16 < M <= 64: the Newton pass's first two kernels (eqs. GTF_residual,
+// GTF_DEER_update).
+//
+//   k_newton_local_plrnn   residual r_t = z_t - F(z~_{t-1}), ReLU masks m_t and the chunk-local
+//                          solution v_c (from a zero carry), 16 chunks as matrix-core columns;
+//                          says which chunks' masks changed since the pass before
+//   k_chunk_product_split  P_c = J~_e ... J~_s of a chunk from the masks, J~_t = gamma (diag(A) +
+//                          W diag(m_t)) diag(p), on the fp16 matrix cores with split operands
+//
+// P_c depends on the masks and the damping only.  Near the solution few ReLU decisions change
+// from one Newton update to the next, so a chunk whose masks and damping are those its stored
+// product was formed with keeps it: the same bits, without the 2 M^3 flops per step.
+#include "common.h"
+#include "launch.h"
+#include "newton_ctl.h"
+#include "split16.h"
+
+namespace deer {
+
+__device__ __forceinline__ float sp_p(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
+
+// ---------------------------------------------------------------------------------------
+// residual, masks, local solution.  Block = 16 chunks (column c) x MP / 16 waves; wave w owns the
+// row tile w: lane (g, c) the latents i0 = 16 w + 4 g .. i0 + 3 of chunk c.  Per step every lane
+// puts relu(z~) and m p u of its latents in LDS (double-buffered, one barrier a step), and two
+// products with the rows of W (A fragments in registers, fp32 matrix cores) follow:
+//   F = A z~ + W relu(z~) + h,  r = z - F;     u <- gamma (A p u + W (m p u)) - r
+// The rows of z and x of PD steps are in flight in a register double buffer.  HBM-bound: z and x
+// read, r and the masks written (M = 64, 32 x 131072 steps: 0.92 ms, 3.5 TB/s).  VEC: M and N multiples of 4 and x, z 16-byte aligned.
+// The masks of four steps are put together from LDS and stored by one wave, which reads the
+// words they replace ahead and reports any difference in changed[chunk].
+// ---------------------------------------------------------------------------------------
+template <int MP, bool VEC, bool WU>
+__global__ __launch_bounds__(MP * 4) void k_newton_local_plrnn(
+    const float *__restrict__ A, const float *__restrict__ W, const float *__restrict__ h, float alpha, int N,
+    const float *__restrict__ x, const float *__restrict__ z0, const float *zbuf, const float *zalt,
+    const int *__restrict__ zsel, float *__restrict__ r_out, uint32_t *__restrict__ masks, int *__restrict__ changed,
+    float *__restrict__ vout, const int *__restrict__ active, const float *__restrict__ gamma, int B, int T, int M, int C,
+    int ncs, int tw, uint32_t *mark, uint32_t pass_no) {
+    constexpr int NW = MP / 16, NS = MP / 4, DQ = MP + 4, MW = MP / 32, PD = VEC ? 8 : 4, MR = 2 * PD;
+    __shared__ __align__(16) float rls[2][16 * DQ], uls[2][16 * DQ];   // [buffer][chunk][latent]
+    __shared__ __align__(16) uint8_t mls[MR][16][MP / 4];              // mask nibbles of the last 2 PD steps
+    __shared__ int chs[2][16];
+    if (mark && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(mark, pass_no, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
+    const int nchains = B * ncs;
+    const int id = blockIdx.x * 16 + c;
+    const bool exists = id < nchains;
+    const int b = exists ? id / ncs : 0, cc = exists ? id % ncs : 0;
+    const bool ok = exists && (!active || active[b]);
+    const int s0 = cc * C;
+    const int len = ok ? max(min(C, T - s0), 0) : 0;
+    int maxlen = len;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
+    maxlen = __builtin_amdgcn_readfirstlane(maxlen);
+    if (maxlen == 0) return;   // uniform over the block: no chunk of it runs
+    float aw[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int k = 16 * (s / 4) + 4 * g + (s % 4), row = 16 * wv + c;
+        aw[s] = (row < M && k < M) ? W[row * M + k] : 0.f;
+    }
+    const int i0 = 16 * wv + 4 * g;
+    float Av[4], hv[4], pv[4];
+    bool fo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool lat = i0 + q < M;
+        Av[q] = lat ? A[i0 + q] : 0.f;
+        hv[q] = lat && h ? h[i0 + q] : 0.f;
+        pv[q] = sp_p(i0 + q, N, alpha);
+        fo[q] = i0 + q < N;
+    }
+    const float gm = gamma ? gamma[b] : 1.f;
+    const float *z = cur_iter(zbuf, zalt, zsel, b);
+    const size_t rowb = (size_t)b * T + s0;             // first row of the chunk in z
+    const size_t rowx = (size_t)b * (T + 1) + s0;       // x row of step s0
+    float zp[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = i0 + q;
+        zp[q] = 0.f;
+        if (len > 0 && i < M) {
+            if (s0 == 0) zp[q] = z0 ? z0[(size_t)b * M + i] : (fo[q] ? x[rowx * N + i] : 0.f);
+            else zp[q] = z[(rowb - 1) * M + i];
+        }
+    }
+    float u[4] = {0.f, 0.f, 0.f, 0.f};
+    // branch-free: a step past the chunk reads its first row, a latent past M (an unforced one)
+    // latent 0; what does not apply is zeroed
+    float4 zq[PD], xq[PD];
+    auto fetch = [&](int t, float4 &zn, float4 &xn) {
+        const bool run = t < len;
+        const size_t o = run ? t : 0;
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (VEC) {
+            const float4 zv = *reinterpret_cast<const float4 *>(z + (rowb + o) * M + (i0 < M ? i0 : 0));
+            zn = run && i0 < M ? zv : zero;
+            if (N > 0) {
+                const float4 xv = *reinterpret_cast<const float4 *>(x + (rowx + o) * N + (i0 < N ? i0 : 0));
+                xn = run && i0 < N ? xv : zero;
+            } else {
+                xn = zero;
+            }
+        } else {
+            float zv[4], xv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float a = z[(rowb + o) * M + (i0 + q < M ? i0 + q : 0)];
+                const float d = N > 0 ? x[(rowx + o) * N + (fo[q] ? i0 + q : 0)] : 0.f;
+                zv[q] = run && i0 + q < M ? a : 0.f;
+                xv[q] = run && fo[q] ? d : 0.f;
+            }
+            zn = make_float4(zv[0], zv[1], zv[2], zv[3]);
+            xn = make_float4(xv[0], xv[1], xv[2], xv[3]);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < PD; ++k) fetch(k, zq[k], xq[k]);
+    // masks in store: of each tile of PD steps wave w < PD / 4 takes steps 4 w .. 4 w + 3, lane (g, c)
+    // step 4 w + g of chunk c
+    uint32_t diff = 0u;
+    for (int t0 = 0; t0 < maxlen; t0 += PD) {
+        const int td = t0 + 4 * wv + g;
+        const bool duty = wv < PD / 4 && td < len;
+        uint32_t old0 = 0u, old1 = 0u;
+        if (duty) {
+            old0 = masks[(rowb + td) * MW];
+            if (MW > 1) old1 = masks[(rowb + td) * MW + 1];
+        }
+        float4 zn2[PD], xn2[PD];
+#pragma unroll
+        for (int k = 0; k < PD; ++k) fetch(t0 + PD + k, zn2[k], xn2[k]);
+#pragma unroll
+        for (int k = 0; k < PD; ++k) {
+            const int t = t0 + k;
+            if (t >= maxlen) break;
+            const int cur = k & 1;   // PD is even: buffer parity follows t
+            const int s = s0 + t;
+            const float zc[4] = {zq[k].x, zq[k].y, zq[k].z, zq[k].w}, xc[4] = {xq[k].x, xq[k].y, xq[k].z, xq[k].w};
+            const bool warm = WU && s <= tw;
+            float zt[4], rz[4], mu[4], uo[4];
+            uint32_t nib = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float f = __fadd_rn(__fmul_rn(pv[q], zp[q]), __fmul_rn(alpha, xc[q]));
+                if (WU && warm) f = xc[q];
+                zt[q] = (s == 0 || !fo[q]) ? zp[q] : f;
+                const bool pos = zt[q] > 0.f;
+                nib |= pos ? 1u << q : 0u;
+                rz[q] = pos ? zt[q] : 0.f;
+                uo[q] = (WU && warm && fo[q]) ? 0.f : pv[q] * u[q];   // P_s u
+                mu[q] = pos ? uo[q] : 0.f;
+            }
+            *reinterpret_cast<float4 *>(&rls[cur][c * DQ + i0]) = make_float4(rz[0], rz[1], rz[2], rz[3]);
+            *reinterpret_cast<float4 *>(&uls[cur][c * DQ + i0]) = make_float4(mu[0], mu[1], mu[2], mu[3]);
+            mls[t & (MR - 1)][c][4 * wv + g] = (uint8_t)nib;
+            lds_barrier();
+            v4f f0 = {0.f, 0.f, 0.f, 0.f}, f1 = f0, y0 = f0, y1 = f0;
+#pragma unroll
+            for (int j = 0; j < NS / 4; ++j) {
+                const float4 dr = *reinterpret_cast<const float4 *>(&rls[cur][c * DQ + 16 * j + 4 * g]);
+                const float4 du = *reinterpret_cast<const float4 *>(&uls[cur][c * DQ + 16 * j + 4 * g]);
+                y0 = mfma16x16x4(aw[4 * j + 0], du.x, y0);
+                f0 = mfma16x16x4(aw[4 * j + 0], dr.x, f0);
+                y1 = mfma16x16x4(aw[4 * j + 1], du.y, y1);
+                f1 = mfma16x16x4(aw[4 * j + 1], dr.y, f1);
+                y0 = mfma16x16x4(aw[4 * j + 2], du.z, y0);
+                f0 = mfma16x16x4(aw[4 * j + 2], dr.z, f0);
+                y1 = mfma16x16x4(aw[4 * j + 3], du.w, y1);
+                f1 = mfma16x16x4(aw[4 * j + 3], dr.w, f1);
+            }
+            float rr[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float F = fmaf(Av[q], zt[q], f0[q] + f1[q]) + hv[q];
+                rr[q] = zc[q] - F;
+                const float un = fmaf(gm, fmaf(Av[q], uo[q], y0[q] + y1[q]), -rr[q]);
+                u[q] = t < len ? un : u[q];
+                zp[q] = zc[q];
+            }
+            if (t < len) {
+                float *ro = r_out + (rowb + t) * M + i0;
+                if constexpr (VEC) {
+                    if (i0 < M) *reinterpret_cast<float4 *>(ro) = make_float4(rr[0], rr[1], rr[2], rr[3]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (i0 + q < M) ro[q] = rr[q];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PD; ++k) {
+            zq[k] = zn2[k];
+            xq[k] = xn2[k];
+        }
+        // the ring holds two tiles, so the next tile's nibbles go to the other half of it
+        if (duty) {
+            uint32_t w[MW];
+#pragma unroll
+            for (int k = 0; k < MW; ++k) {
+                const uint2 n8 = *reinterpret_cast<const uint2 *>(&mls[td & (MR - 1)][c][8 * k]);
+                uint32_t lo = n8.x, hi = n8.y;   // four nibbles each, one per byte
+                lo = (lo | (lo >> 4)) & 0x00ff00ffu;
+                lo = (lo | (lo >> 8)) & 0xffffu;
+                hi = (hi | (hi >> 4)) & 0x00ff00ffu;
+                hi = (hi | (hi >> 8)) & 0xffffu;
+                w[k] = lo | (hi << 16);
+                masks[(rowb + td) * MW + k] = w[k];
+            }
+            diff |= (w[0] ^ old0) | (MW > 1 ? w[MW - 1] ^ old1 : 0u);
+        }
+    }
+    if (ok) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) vout[(size_t)id * MP + i0 + q] = u[q];
+    }
+    int dv = diff != 0u;
+    dv |= __shfl_xor(dv, 16, 64);
+    dv |= __shfl_xor(dv, 32, 64);
+    if (wv < 2 && g == 0) chs[wv][c] = dv;   // wave 1 found none where PD is 4
+    lds_barrier();
+    if (wv == 0 && g == 0 && ok) changed[id] = chs[0][c] | chs[1][c];
+}
+
+// ---------------------------------------------------------------------------------------
+// chunk products.  One chunk per wave.  The accumulators of a step hold P in the 16 x 16 tiles
+// (I, Jt); lane (g, c) element r is P[16 I + 4 g + r][16 Jt + c].  With the k slots of a 16x16x32
+// instruction numbered k = 32 kk + 16 (e >> 2) + 4 g + (e & 3) (e the slot within the lane) these
+// accumulators, split, are the next step's B operand: no data moves between lanes.
+//
+// A operand: gamma (W + diag A) diag(p), scaled by 2^s (largest entry in [2^9, 2^10)) and split
+// once, kept in LDS (MP = 64; 16 KB) or registers; per step the columns whose ReLU is off are
+// cleared, the diagonal keeping A (v_bfi between the two).
+// B operand: column j of P carries its own power of two 2^E[j].  Every step multiplies by 2^-(s+q),
+// 2^q at least the largest absolute row sum of gamma (W + diag A) diag(p), so no entry can grow
+// out of fp16's range whatever the masks are; every KR steps (fewer where 2^q is large) the
+// column is renormalised to [2^13, 2^14) instead.
+//
+// Per step at M = 64: 96 matrix instructions (0.76 us on a SIMD) and about 280 vector ones
+// (conversion of 4096 entries, masks; issued one after the other, the matrix cores and the vector
+// units of a SIMD do not overlap), where fp32 matrix instructions took 256 (3.55 us).  M = 64,
+// 32 x 131072 steps: 5.6 ms for every chunk against 15.6 ms in fp32 with the residual in the same
+// kernel; with the products that are kept, 33 ms against 140 ms for the passes of a solve of
+// nine updates.
+// REV: the adjoint's range, J~_{hi-1} ... J~_{s0+1}, hi = min(s1 + 1, T).
+// ---------------------------------------------------------------------------------------
+template <int MP, bool REV, bool WU>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_product_split(
+    const float *__restrict__ A, const float *__restrict__ W, float alpha, int N, const uint32_t *__restrict__ masks,
+    const int *__restrict__ changed, float *__restrict__ pgam, float *__restrict__ Pout, const int *__restrict__ active,
+    const float *__restrict__ gamma, int B, int T, int M, int C, int ncs, int tw) {
+    constexpr int NI = MP / 16, KK = MP / 32, MW = MP / 32;
+    __shared__ __align__(16) v4u wls[NI][KK][2][64];   // [row tile][k block][hi, lo][lane]
+    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
+    const int id = blockIdx.x;
+    const int b = id / ncs, s0 = (id % ncs) * C;
+    if (active && !active[b]) return;
+    const float gm = gamma ? gamma[b] : 1.f;
+    // the stored product is that of these masks and this damping
+    if (!REV && changed && !changed[id] && pgam[id] == gm) return;
+    const int s1 = min(s0 + C, T);
+    const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
+    const int len = __builtin_amdgcn_readfirstlane(hi - lo);
+    const float m1 = opaque_m1();
+
+    // scale of the A operand and the row-sum bound
+    float wf[NI][NI][4], ad[NI];
+    float wmax = 0.f, rsum = 0.f;
+#pragma unroll
+    for (int I = 0; I < NI; ++I) {
+        const int row = 16 * I + c;
+        ad[I] = row < M ? A[row] * (gm * sp_p(row, N, alpha)) : 0.f;
+        float rs = 0.f;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = 16 * j + 4 * g + q;
+                const float w = (row < M && k < M) ? W[row * M + k] * (gm * sp_p(k, N, alpha)) : 0.f;
+                wf[I][j][q] = (k == row) ? w + ad[I] : w;
+                wmax = fmaxf(wmax, fabsf(wf[I][j][q]));
+                rs += fabsf(w);
+            }
+        rs += __shfl_xor(rs, 16, 64);
+        rs += __shfl_xor(rs, 32, 64);
+        rsum = fmaxf(rsum, rs + fabsf(ad[I]));
+        wmax = fmaxf(wmax, fabsf(ad[I]));
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        wmax = fmaxf(wmax, __shfl_xor(wmax, off, 64));
+        rsum = fmaxf(rsum, __shfl_xor(rsum, off, 64));
+    }
+    const int sc = __builtin_amdgcn_readfirstlane(min(9 - exp_of(wmax), 100));
+    const int qe = __builtin_amdgcn_readfirstlane(max(exp_of(rsum) + 1, -20));
+    const int kr = qe <= 3 ? 4 : qe <= 6 ? 2 : 1;
+    const float fplain = pow2i(max(-(sc + qe), -126));
+#pragma unroll
+    for (int I = 0; I < NI; ++I)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            v4u hv, lv;
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2) {
+                uint32_t ph, pl;
+                const float *w4 = wf[I][2 * kk + (e2 >> 1)];
+                split_pair(ldexpf(w4[2 * (e2 & 1)], sc), ldexpf(w4[2 * (e2 & 1) + 1], sc), m1, ph, pl);
+                hv[e2] = ph;
+                lv[e2] = pl;
+            }
+            wls[I][kk][0][lane] = hv;
+            wls[I][kk][1][lane] = lv;
+        }
+    // A alone, for the diagonal of a row whose ReLU is off: pair h holds slots q = 2 h, 2 h + 1
+    uint32_t dgh[NI][2], dgl[NI][2];
+#pragma unroll
+    for (int I = 0; I < NI; ++I)
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+            const float d = ldexpf(ad[I], sc);
+            split_pair(c == 4 * g + 2 * h2 ? d : 0.f, c == 4 * g + 2 * h2 + 1 ? d : 0.f, m1, dgh[I][h2], dgl[I][h2]);
+        }
+    // columns kept in a latent warm-up step (P_1 drops the observed ones)
+    uint32_t om[NI][2];
+    if constexpr (WU) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+                const int k = 16 * j + 4 * g + 2 * h2;
+                om[j][h2] = (k < N ? 0u : 0xffffu) | (k + 1 < N ? 0u : 0xffff0000u);
+            }
+    }
+    wave_lds_sync();
+
+    v4f acc[NI][NI];
+    int E[NI];
+#pragma unroll
+    for (int Jt = 0; Jt < NI; ++Jt) {
+        E[Jt] = 0;
+#pragma unroll
+        for (int I = 0; I < NI; ++I)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 16 * Jt + c) ? 1.f : 0.f;
+    }
+    // mask words of 64 steps at a time, one step per lane, the next 64 in flight
+    const size_t rowm = (size_t)b * T + lo;
+    uint32_t mc[MW], mn[MW];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int k = 0; k < MW; ++k) mn[k] = t0 + lane < len ? masks[(rowm + t0 + lane) * MW + k] : 0u;
+    };
+    fetch(0);
+    for (int t = 0; t < len; ++t) {
+        if ((t & 63) == 0) {
+#pragma unroll
+            for (int k = 0; k < MW; ++k) mc[k] = mn[k];
+            fetch(t + 64);
+        }
+        // P to the B operand
+        v4u bh[KK][NI], bl[KK][NI];
+        const bool renorm = (t & (kr - 1)) == 0;
+#pragma unroll
+        for (int Jt = 0; Jt < NI; ++Jt) {
+            float f = fplain;
+            if (renorm) {
+                float m = 0.f;
+#pragma unroll
+                for (int I = 0; I < NI; ++I)
+                    m = absmax3(acc[I][Jt][2], acc[I][Jt][3], absmax3(acc[I][Jt][0], acc[I][Jt][1], m));
+                m = group_max(m);
+                const int ph = min(13 - exp_of(m), 126);
+                f = pow2i(ph);
+                E[Jt] -= ph + sc;
+            } else {
+                E[Jt] += qe;
+            }
+#pragma unroll
+            for (int I = 0; I < NI; ++I)
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    uint32_t ph, pl;
+                    split_pair(acc[I][Jt][2 * h2] * f, acc[I][Jt][2 * h2 + 1] * f, m1, ph, pl);
+                    bh[I >> 1][Jt][2 * (I & 1) + h2] = ph;
+                    bl[I >> 1][Jt][2 * (I & 1) + h2] = pl;
+                }
+        }
+        // all ones in the half of each slot whose ReLU is on
+        uint32_t pm[NI][2];
+#pragma unroll
+        for (int k = 0; k < MW; ++k) {
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)mc[k], t & 63) >> (4 * g);
+#pragma unroll
+            for (int j2 = 0; j2 < 2; ++j2)
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    const uint32_t l = (uint32_t)__builtin_amdgcn_sbfe((int)w, 16 * j2 + 2 * h2, 1);
+                    const uint32_t u = (uint32_t)__builtin_amdgcn_sbfe((int)w, 16 * j2 + 2 * h2 + 1, 1);
+                    pm[2 * k + j2][h2] = (l & 0xffffu) | (u & 0xffff0000u);
+                }
+        }
+        uint32_t keep[NI][2];
+        if constexpr (WU) {
+            const bool warm = lo + t <= tw;
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    keep[j][h2] = warm ? om[j][h2] : 0xffffffffu;
+                    pm[j][h2] &= keep[j][h2];
+                }
+        }
+#pragma unroll
+        for (int I = 0; I < NI; ++I) {
+            v4u ah[KK], al[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const v4u wh = wls[I][kk][0][lane], wl = wls[I][kk][1][lane];
+#pragma unroll
+                for (int e2 = 0; e2 < 4; ++e2) {
+                    const int j = 2 * kk + (e2 >> 1), h2 = e2 & 1;
+                    uint32_t dh = 0u, dl = 0u;
+                    if (j == I) {
+                        dh = WU ? dgh[I][h2] & keep[j][h2] : dgh[I][h2];
+                        dl = WU ? dgl[I][h2] & keep[j][h2] : dgl[I][h2];
+                    }
+                    ah[kk][e2] = (pm[j][h2] & wh[e2]) | (~pm[j][h2] & dh);
+                    al[kk][e2] = (pm[j][h2] & wl[e2]) | (~pm[j][h2] & dl);
+                }
+            }
+            v4f s[NI];
+#pragma unroll
+            for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+#pragma unroll
+                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(al[kk], bh[kk][Jt], s[Jt]);
+#pragma unroll
+                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(ah[kk], bl[kk][Jt], s[Jt]);
+            }
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(ah[kk], bh[kk][Jt], s[Jt]);
+#pragma unroll
+            for (int Jt = 0; Jt < NI; ++Jt) acc[I][Jt] = s[Jt];
+        }
+    }
+    float *P = Pout + (size_t)id * MP * MP;
+#pragma unroll
+    for (int Jt = 0; Jt < NI; ++Jt)
+#pragma unroll
+        for (int I = 0; I < NI; ++I)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * Jt + c] = ldexpf(acc[I][Jt][r], E[Jt]);
+    if (!REV && pgam && lane == 0) pgam[id] = gm;
+}
+
+// ---- launchers ---------------------------------------------------------------------------
+// 16-byte rows of z and x: every row a multiple of four floats on a 16-byte boundary
+static bool rows16(const PlrnnArgs &a, const float *z, const float *zalt) {
+    return a.M % 4 == 0 && a.N % 4 == 0 && (((uintptr_t)a.x | (uintptr_t)z | (uintptr_t)zalt) & 15u) == 0;
+}
+
+int launch_newton_local_plrnn(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *r,
+                              uint32_t *masks, int *changed, float *v, const int *active, const float *gamma, int C,
+                              int ncs, uint32_t *mark, uint32_t pass_no, hipStream_t st) {
+    const int grid = (a.B * ncs + 15) / 16;
+    const bool vec = rows16(a, z, zalt);
+    KTimer kt("k_newton_local_plrnn", st);
+#define NL(MPV, VV, WUV)                                                                                              \
+    hipLaunchKernelGGL((k_newton_local_plrnn<MPV, VV, WUV>), dim3(grid), dim3(MPV * 4), 0, st, a.A, a.W, a.h, a.alpha, \
+                       a.N, a.x, a.z0, z, zalt, zsel, r, masks, changed, v, active, gamma, a.B, a.T, a.M, C, ncs, a.tw, \
+                       mark, pass_no)
+#define NLW(MPV, VV) if (a.tw > 0) NL(MPV, VV, true); else NL(MPV, VV, false)
+    if (padded_dim(a.M) == 32) {
+        if (vec) NLW(32, true); else NLW(32, false);
+    } else {
+        if (vec) NLW(64, true); else NLW(64, false);
+    }
+#undef NLW
+#undef NL
+    DEER_LAUNCH_CHECK("k_newton_local_plrnn");
+    return DEER_OK;
+}
+
+int launch_chunk_product_split(const PlrnnArgs &a, bool rev, const uint32_t *masks, const int *changed, float *pgam,
+                               float *P, const int *active, const float *gamma, int C, int ncs, hipStream_t st) {
+    const int grid = a.B * ncs;
+    KTimer kt(rev ? "k_chunk_product_split_rev" : "k_chunk_product_split", st);
+#define CPS(MPV, RV, WUV)                                                                                              \
+    hipLaunchKernelGGL((k_chunk_product_split<MPV, RV, WUV>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.alpha, a.N, masks, \
+                       changed, pgam, P, active, gamma, a.B, a.T, a.M, C, ncs, a.tw)
+#define CPSW(MPV, RV) if (a.tw > 0) CPS(MPV, RV, true); else CPS(MPV, RV, false)
+    if (padded_dim(a.M) == 32) {
+        if (rev) CPSW(32, true); else CPSW(32, false);
+    } else {
+        if (rev) CPSW(64, true); else CPSW(64, false);
+    }
+#undef CPSW
+#undef CPS
+    DEER_LAUNCH_CHECK("k_chunk_product_split");
+    return DEER_OK;
+}
+
+}  // namespace deer

@@ -46,11 +46,21 @@ int launch_resjac_plrnn(const PlrnnArgs &a, const float *z, float *F, float *r, 
 int launch_chunk_product_plrnn(const PlrnnArgs &a, bool rev, const uint32_t *masks, const float *rhs, const float *z,
                                float seed_scale, float *P, float *v, const int *active, int C, int ncs,
                                hipStream_t st);
-// M <= 16 only: block 0 of the pass writes pass_no to the host-visible word *mark as it
+// forward pass, M <= 16: block 0 writes pass_no to the host-visible word *mark as it
 // starts (every kernel queued before it has completed); mark may be null
-int launch_newton_product_plrnn(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *r,
-                                uint32_t *masks, float *P, float *v, const int *active, const float *gamma, int C,
-                                int ncs, int wmaps, float *gmap, uint32_t *mark, uint32_t pass_no, hipStream_t st);
+int launch_newton_product_plrnn16(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *P,
+                                  float *v, const int *active, const float *gamma, int C, int ncs, int wmaps,
+                                  float *gmap, uint32_t *mark, uint32_t pass_no, hipStream_t st);
+// forward pass, 16 < M <= 64 (k_split.hip): residual, masks and local solutions v, with
+// changed[chunk] set where a mask differs from the one it replaces (mark as above), then the chunk
+// products of the chunks whose masks changed or whose stored product had another damping
+// (pgam[chunk]: the damping of the stored product, NaN for none; rev: the adjoint's products of
+// every chunk, changed / pgam / active / gamma unused)
+int launch_newton_local_plrnn(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *r,
+                              uint32_t *masks, int *changed, float *v, const int *active, const float *gamma, int C,
+                              int ncs, uint32_t *mark, uint32_t pass_no, hipStream_t st);
+int launch_chunk_product_split(const PlrnnArgs &a, bool rev, const uint32_t *masks, const int *changed, float *pgam,
+                               float *P, const int *active, const float *gamma, int C, int ncs, hipStream_t st);
 // M <= 16 with wave maps (P, v from launch_newton_product_plrnn with wmaps): carries of the
 // wave maps, written to the carry slot of each wave's first chunk
 int launch_carry_walk16(bool rev, const float *P, const float *v, float *carry, const int *active, int B, int ncs,
@@ -62,6 +72,8 @@ int launch_adjoint_plrnn16(const PlrnnArgs &a, const float *g, float seed_scale,
 int launch_carry(int MP, bool rev, const float *P, const float *v, float *carry_in, const int *active,
                  uint32_t *norm_bits, int B, int ncs, float *gws, hipStream_t st);
 size_t carry_ws_floats(int MP, int B, int ncs);
+// whether launch_fixup_fwd_plrnn takes the pass-end control (fc) at this width
+bool plrnn_fixup_control(int M);
 int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const float *r, const float *carry_in,
                            float *z, float *zalt, const int *zsel, uint32_t *chain_bits, const int *active,
                            const float *gamma, int C, int ncs, const float *Pm, const float *vm,

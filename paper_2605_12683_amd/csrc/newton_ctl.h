@@ -70,4 +70,32 @@ __device__ __forceinline__ void seq_arrive(const FusedCtl &fc, int b, int cnt, i
     __hip_atomic_store(blk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Arrival of the 16 chains chain0 .. chain0 + 15 from lanes 0..15 of one wave (emax, zmax: lane
+// c's chain; ok: it runs): lane 0 gathers the maxima and arrives once per sequence.
+__device__ __forceinline__ void block16_arrive(const FusedCtl &fc, uint32_t emax, uint32_t zmax, bool ok, int chain0,
+                                               int ncs, int lane) {
+    uint32_t em[16], zm[16];
+    bool okc[16];
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+        em[n] = (uint32_t)__shfl((int)emax, n, 64);
+        zm[n] = (uint32_t)__shfl((int)zmax, n, 64);
+        okc[n] = __shfl((int)ok, n, 64) != 0;
+    }
+    if (lane != 0) return;
+    for (int n = 0; n < 16; ++n) {
+        if (!okc[n]) continue;
+        const int bn = (chain0 + n) / ncs;
+        if (n > 0 && okc[n - 1] && (chain0 + n - 1) / ncs == bn) continue;   // counted with its first chain
+        uint32_t E = 0u, Z = 0u;
+        int cnt = 0;
+        for (int m2 = n; m2 < 16 && okc[m2] && (chain0 + m2) / ncs == bn; ++m2) {
+            E = E > em[m2] ? E : em[m2];
+            Z = Z > zm[m2] ? Z : zm[m2];
+            ++cnt;
+        }
+        seq_arrive(fc, bn, cnt, ncs, E, Z);
+    }
+}
+
 }  // namespace deer

@@ -1,0 +1,69 @@
+// fp32 matrix products on the fp16 matrix cores by splitting (internal to libdeer, not part of
+// the ABI).
+//
+// A float x in fp16's range is held as hi + lo, hi = fp16(x), lo = fp16(x - hi), both rounded to
+// nearest (the difference is exact): 22 significant bits and a sign for lo, |x - hi - lo| <=
+// 2^-23 of x's binade while lo is a normal number.  A product of two split operands takes three
+// matrix instructions, lo hi + hi lo + hi hi in that order, each with fp32 products and sums; the
+// dropped lo lo is below 2^-22.  Against 64 bits such a product of 64 terms is as near as the
+// fp32 matrix instruction (whose 16 partial sums round more often) and takes 3/8 of its matrix
+// time: 16 instructions of 16 x 16 x 32 in fp16 or bf16 take 127 ns on a SIMD, 16 of 16 x 16 x 4
+// in fp32 222 ns.
+//
+// fp16 has 5 exponent bits, so operands are scaled by powers of two (exact) before they are
+// split: the largest entry near the top of the range, where an entry needs to be 2^-17 of it
+// before lo becomes subnormal (its error is then 2^-25 absolute, 2^-38 of the largest entry).
+#pragma once
+
+#include "common.h"
+
+namespace deer {
+
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// D = A B + acc for one 16 x 16 x 32 tile; lane (g, c) supplies eight k slots of row c of A and
+// of column c of B and holds acc[4 g + r][c].  Any assignment of k to slots is allowed if A and
+// B agree on it.
+__device__ __forceinline__ v4f mfma_h(v4u a, v4u b, v4f acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), acc, 0, 0, 0);
+}
+
+// -1 the compiler cannot see: x - float(h) then stays one mixed-precision multiply-add instead
+// of a conversion and a subtraction
+__device__ __forceinline__ float opaque_m1() {
+    float m1 = -1.f;
+    asm volatile("" : "+s"(m1));
+    return m1;
+}
+
+// hi and lo of two consecutive k slots, packed
+__device__ __forceinline__ void split_pair(float x0, float x1, float m1, uint32_t &hi, uint32_t &lo) {
+    hi = __builtin_bit_cast(uint32_t, v2h{(_Float16)x0, (_Float16)x1});
+    asm("" : "+v"(hi));   // one packed conversion (else the halves are converted again for lo)
+    const v2h h = __builtin_bit_cast(v2h, hi);
+    const v2h l = {(_Float16)__builtin_fmaf((float)h[0], m1, x0), (_Float16)__builtin_fmaf((float)h[1], m1, x1)};
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
+// max over the four lane groups (lanes c, c + 16, c + 32, c + 48) of a non-negative value
+__device__ __forceinline__ float group_max(float v) {
+    auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// max(|a|, |b|, m) in one instruction
+__device__ __forceinline__ float absmax3(float a, float b, float m) {
+    float r;
+    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(m));
+    return r;
+}
+
+// exponent of a non-negative float (0 for zero and subnormals read as -127)
+__device__ __forceinline__ int exp_of(float v) { return (int)(__float_as_uint(v) >> 23) - 127; }
+__device__ __forceinline__ float pow2i(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }   // -126 <= e <= 127
+
+}  // namespace deer

@@ -1,0 +1,103 @@
+"""Chunk products on the fp16 matrix cores with split operands (vanilla PLRNN, 16 < M <= 64): the
+Newton iterates against the float64 oracle's at the edges of the tiles, where the power-of-two
+scaling can go wrong, and where a chunk keeps its stored product."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2605_12683_amd as D  # noqa: E402
+from gpu_util import oracle_model, rel_inf, say  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-4   # the project's normwise tolerance
+
+
+@pytest.fixture(autouse=True)
+def _chunk():
+    os.environ.pop("DEER_CHUNK", None)
+    yield
+    os.environ.pop("DEER_CHUNK", None)
+
+
+def _case(M, N, B, T, seed, a_range=(0.3, 0.75), w_norm=0.2):
+    return W.random_plrnn_case(M, N, B, T, 0.2, seed, w_norm=w_norm, a_range=a_range)
+
+
+# M: first and last width of each padded size, a width that is no multiple of 4 and one that is;
+# chunks: shorter than the 8-step tile of the local kernel, one tile, one over the 64-step mask tile
+@pytest.mark.parametrize("M,N,B,T,chunk,T_w", [
+    (17, 3, 2, 40, 5, 0), (20, 20, 1, 130, 65, 0), (32, 8, 17, 64, 16, 9), (33, 33, 2, 200, 66, 0),
+    (48, 12, 3, 65, 8, 64), (63, 5, 1, 257, 128, 3), (64, 64, 2, 1, 16, 0), (64, 0, 2, 90, 31, 0), (64, 64, 2, 300, 100, 120)])
+def test_iterates(M, N, B, T, chunk, T_w):
+    os.environ["DEER_CHUNK"] = str(chunk)
+    c = _case(M, N or 3, B, T, 6000 + M + T)
+    init = "teacher" if N else "zero"   # nothing observed: x is not read
+    say("split iterates", M, N, B, T, chunk, T_w)
+    rng = np.random.default_rng(M)
+    z0 = rng.standard_normal((B, M)).astype(np.float32)
+    for k in (1, 3):
+        res = D.deer_solve(oracle_model(c), c.x, 0.2, N, fixed_iters=k, z0=z0, T_w=T_w, init=init)
+        ref = O.newton(oracle_model(c), c.x, 0.2, N, fixed_iters=k, z0=z0, T_w=T_w, init=init)
+        assert rel_inf(res["z"].cpu().numpy(), ref["z"]) < TOL
+
+
+# the operands' scales: weights far from one (the row-sum bound and the renormalisation period follow
+# them), a diagonal far below W, rows of very different size
+@pytest.mark.parametrize("M", [24, 64])
+@pytest.mark.parametrize("kind", ["large", "huge", "tiny", "rows", "zero"])
+def test_scales(M, kind):
+    os.environ["DEER_CHUNK"] = "2" if kind == "huge" else "24"
+    T = {"large": 60, "huge": 5}.get(kind, 96)
+    c = _case(M, M, 2, T, 6100 + M)
+    p = {k: v.copy() for k, v in c.params.items()}
+    if kind == "large":        # products grow to ~1e30 within the sequence
+        p["W"] *= 16.0
+    elif kind == "huge":       # one step grows by ~2^20
+        p["W"] *= np.float32(2.0 ** 21)
+    elif kind == "tiny":       # products fall by ~2^-10 a step
+        p["W"] *= 1e-3
+        p["A"] *= 1e-3
+    elif kind == "rows":
+        p["W"] *= (2.0 ** -np.linspace(0, 18, M)).astype(np.float32)[:, None]
+    else:
+        p["W"] *= 0.0
+        p["A"] *= 0.0
+    m = {"kind": "plrnn", **p}
+    x = c.x[:, :T + 1]
+    say("split scales", M, kind)
+    res = D.deer_solve(m, x, 0.2, M, fixed_iters=1, init="zero")
+    ref = O.newton(m, x, 0.2, M, fixed_iters=1, init="zero")
+    assert rel_inf(res["z"].cpu().numpy(), ref["z"]) < TOL
+
+
+@pytest.mark.parametrize("M,bound", [(20, 0.0), (64, 0.0), (64, 0.05), (33, 0.05)])
+def test_kept_products(M, bound):
+    """Updates past convergence keep every chunk's product (no mask changes), and with a small step
+    bound rejected updates re-form them with another damping at unchanged masks: the fixed point
+    and a second, tighter solve from it agree with the rollout."""
+    os.environ["DEER_CHUNK"] = "32"
+    c = _case(M, M, 3, 500, 6200 + M, w_norm=0.35)
+    m = oracle_model(c)
+    ref = O.rollout(m, c.x, 0.2, M)
+    say("split kept products", M, bound)
+    res = D.deer_solve(m, c.x, 0.2, M, tol=1e-5, max_iter=5000, step_bound=bound)
+    assert res["status"] == 0 and rel_inf(res["z"].cpu().numpy(), ref) < TOL
+    more = D.deer_solve(m, c.x, 0.2, M, fixed_iters=8)
+    assert rel_inf(more["z"].cpu().numpy(), ref) < 1e-5
+
+
+def test_nonfinite_weights():
+    c = _case(40, 40, 2, 64, 6300)
+    m = oracle_model(c)
+    m["W"] = m["W"].copy()
+    m["W"][3, 5] = np.nan
+    say("split NaN weights")
+    assert D.deer_solve(m, c.x, 0.2, 40, tol=1e-5, max_iter=50)["status"] == 3
