@@ -335,7 +335,8 @@ static PlrnnWs carve_plrnn(void *ws, int B, int T, int M, int op, size_t *bytes)
             w.pgam = c.take<float>(nch);
         }
     } else {
-        w.gpart = c.take<float>(nch * w.MP * (w.MP + 2));
+        const size_t parts = w.MP > 16 ? (size_t)adjoint_walk_blocks(B, w.ncs) : nch;
+        w.gpart = c.take<float>(parts * w.MP * (w.MP + 2));
         w.gpart2 = c.take<double>(reduce_gpart_ws_bytes(w.MP) / sizeof(double));
     }
     *bytes = c.off;
@@ -1478,13 +1479,17 @@ int deer_adjoint_ex(const deer_model *m, const deer_forcing *f, int B, int T, co
             }
             return DEER_OK;
         }
-        if ((rc = launch_resjac_plrnn(a, z, nullptr, nullptr, nullptr, w.masks, nullptr, st))) return rc;
-        if ((rc = launch_chunk_product_plrnn(a, true, w.masks, g, z, scale, w.P, w.v, nullptr, w.C, w.ncs, st)))
+        if ((rc = launch_adjoint_walk_plrnn(a, false, g, scale, z, nullptr, w.v, w.masks, nullptr, w.C, w.ncs, st)))
+            return rc;
+        if ((rc = launch_chunk_product_split(a, true, w.masks, nullptr, nullptr, w.P, nullptr, nullptr, w.C, w.ncs, st)))
             return rc;
         if ((rc = launch_carry(w.MP, true, w.P, w.v, w.carry, nullptr, nullptr, B, w.ncs, w.gws, st))) return rc;
-        if ((rc = launch_fixup_rev_plrnn(a, w.masks, g, scale, z, w.carry, lam, w.gpart, w.C, w.ncs, st))) return rc;
+        if ((rc = launch_adjoint_walk_plrnn(a, true, g, scale, z, w.carry, lam, nullptr, w.gpart, w.C, w.ncs, st)))
+            return rc;
         if (grads && (grads->A || grads->W || grads->h)) {
-            if ((rc = launch_reduce_gpart(w.gpart, B * w.ncs, w.MP, m->M, grads->A, grads->W, grads->h, w.gpart2, st))) return rc;
+            if ((rc = launch_reduce_gpart(w.gpart, adjoint_walk_blocks(B, w.ncs), w.MP, m->M, grads->A, grads->W,
+                                          grads->h, w.gpart2, st)))
+                return rc;
         }
         return DEER_OK;
     }

@@ -2,15 +2,16 @@
 //   z_t = diag(A) z~_{t-1} + W relu(z~_{t-1}) + h          (eq. shplrnn_nonlinear, V = I, b = 0)
 //   J~_t = (diag(A) + W diag(m_t)) P_alpha                  (Jacobian of F, eq. error_forcing_decomp)
 //
-// Kernels (one Newton iteration = resjac -> chunk products -> carries -> fix-up):
+// Kernels (one Newton iteration = residual and chunk products -> carries -> fix-up):
 //   k_resjac_plrnn     residual r_t, masks m_t (and optionally F, dense J~) at every step
-//   k_chunk_product    per chunk of C steps: P_c = J~_e ... J~_s on the matrix cores (fp32
+//   k_newton_product_plrnn16, k_newton_pass16, k_chunk_product_plrnn16_rev (M <= 16)
+//                      per chunk of C steps: P_c = J~_e ... J~_s on the matrix cores (fp32
 //                      MFMA) and v_c = the chunk's local solution from a zero carry (VALU);
-//                      the forward pass at M > 16 is in k_split.hip
+//                      M > 16: k_split.hip
 //   k_carry            carries across chunks, one wave per sequence
 //   k_fixup_fwd        Delta_t = J~_t Delta_{t-1} - r_t from the carry, z += Delta, max|Delta|
 //   k_fixup_rev        lam_{t-1} = J~_t^T lam_t + g_{t-1} from the carry, fused parameter-
-//                      gradient partial sums (gradients appendix)
+//                      gradient partial sums (gradients appendix); M > 16: k_split.hip
 //
 // Padded dimension MP in {16, 32, 64} (the next one >= M); a wave holds NCH = 64/MP chains.
 #include <type_traits>
@@ -147,195 +148,6 @@ __global__ __launch_bounds__(64) void k_resjac_plrnn(const float *__restrict__ A
                 }
             }
         }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// chunk aggregates.  Product over the step range [lo, hi) of the chain:
-//   forward: P_c = J~_{s1-1} ... J~_{s0}           v_c = Delta_{s1-1} from a zero carry
-//   reverse: P_c = J~_{s1} ... J~_{s0+1}  (then read transposed)
-//            v_c = lam_{s0} of the chunk from lam_{s1} = 0
-// MFMA formulation of P <- J~ P = diag(A p) P + (W diag(p)) (diag(m) P):
-//   A operand = W diag(p) (constant, registers), B operand = the masked accumulator itself
-//   (with the k-permutation kappa(4j+q, g) = 16j + 4g + q the 16x16x4 output layout is
-//   exactly the B layout of the next step, so no data moves between steps).
-// ---------------------------------------------------------------------------------------
-template <int MP, bool REV, bool WU>
-__global__ __launch_bounds__(64) void k_chunk_product_plrnn(
-    const float *__restrict__ A, const float *__restrict__ W, float alpha, int N, const uint32_t *__restrict__ masks,
-    const float *__restrict__ rhs, const float *__restrict__ z, const float *__restrict__ x, float seed_scale,
-    float *__restrict__ Pout, float *__restrict__ vout, const int *__restrict__ active, int B, int T, int M, int C,
-    int ncs, int tw) {
-    using G = Geo<MP>;
-    constexpr int NCH = G::NCH, NI = G::NI, NS = G::NS, MW = G::MW;
-    __shared__ __align__(16) float lds[64];
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int nchains = B * ncs;
-    const int chain0 = blockIdx.x * NCH;
-
-    int pb[NCH], plo[NCH], plen[NCH], us0[NCH], us1[NCH];
-    int maxlen = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n) {
-        const int id = chain0 + n;
-        bool ok = id < nchains;
-        const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
-        ok = ok && (!active || active[b]);
-        const int s0 = cc * C, s1 = min(s0 + C, T);
-        const int lo = REV ? s0 + 1 : s0;
-        const int hi = REV ? min(s1 + 1, T) : s1;
-        pb[n] = b;
-        plo[n] = lo;
-        plen[n] = ok ? max(hi - lo, 0) : 0;
-        us0[n] = s0;
-        us1[n] = ok ? s1 : s0;
-        maxlen = max(maxlen, max(plen[n], us1[n] - us0[n]));
-    }
-
-    // A operand: (W diag(p))[16I + c][16j + 4g + q]
-    float Aop[NI][NS];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * I + c, col = 16 * j + 4 * g + q;
-                Aop[I][4 * j + q] = (row < M && col < M) ? W[row * M + col] * p_of(col, N, alpha) : 0.f;
-            }
-    float dI[NI][4];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * I + 4 * g + r;
-            dI[I][r] = row < M ? A[row] * p_of(row, N, alpha) : 0.f;
-        }
-    // latent warm-up steps (P_1): the observed latents' rows of the diagonal term are dropped
-    float dIw[NI][4];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dIw[I][r] = (WU && 16 * I + 4 * g + r < N) ? 0.f : dI[I][r];
-    // accumulators start at the identity of each chain
-    v4f acc[NI][4];
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int col = 16 * Jt + c - n * MP;
-#pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == col) ? 1.f : 0.f;
-    }
-
-    // VALU chain for v_c: lane = (chain un, row ui)
-    const int un = lane / MP, ui = lane % MP;
-    float wv[MP];
-    float du = 0.f, pu = 0.f, Au = 0.f;
-    if (!REV) {
-#pragma unroll
-        for (int k = 0; k < MP; ++k) wv[k] = (ui < M && k < M) ? W[ui * M + k] * p_of(k, N, alpha) : 0.f;
-        du = ui < M ? A[ui] * p_of(ui, N, alpha) : 0.f;
-    } else {
-#pragma unroll
-        for (int k = 0; k < MP; ++k) wv[k] = (ui < M && k < M) ? W[k * M + ui] : 0.f;
-        pu = p_of(ui, N, alpha);
-        Au = ui < M ? A[ui] : 0.f;
-    }
-    int ub = 0, ulo = 0, uhi = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n)
-        if (n == un) { ub = pb[n]; ulo = us0[n]; uhi = us1[n]; }
-    float u = 0.f;
-
-    for (int t = 0; t < maxlen; ++t) {
-        // ---- matrix-core part: one step of every chain whose product is still running
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt) {
-            const int n = (16 * Jt) / MP;
-            if (t < plen[n]) {
-                const size_t step = (size_t)pb[n] * T + plo[n] + t;
-                const uint32_t w0 = masks[step * MW];
-                const uint32_t w1 = MW > 1 ? masks[step * MW + 1] : 0u;
-                float Bop[NS];
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j) {
-                    const uint32_t wj = (j >> 1) ? w1 : w0;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) Bop[4 * j + q] = select_bit(wj, 16 * (j & 1) + 4 * g + q, acc[j][Jt][q]);
-                }
-                const bool warm = WU && plo[n] + t <= tw;   // J~ of step plo + t with P_1
-                if (warm) {
-#pragma unroll
-                    for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (16 * j + 4 * g + q < N) Bop[4 * j + q] = 0.f;
-                }
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[I][Jt][r] *= warm ? dIw[I][r] : dI[I][r];
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) acc[I][Jt] = mfma16x16x4(Aop[I][s], Bop[s], acc[I][Jt]);
-            }
-        }
-        // ---- VALU part: local solution of the chunk
-        const bool run = ulo + t < uhi;
-        if (!REV) {
-            const int s = ulo + t;
-            const size_t step = (size_t)ub * T + s;
-            const float uo = (WU && ui < N && s <= tw) ? 0.f : u;   // P_s u
-            float w = 0.f;
-            if (run && ui < M) w = mask_bit(masks, step, MW, ui) ? uo : 0.f;
-            lds[lane] = w;
-            lds_barrier();
-            const float y = fmaf(du, uo, lds_dot<MP>(lds, un, wv));
-            lds_barrier();
-            if (run && ui < M) u = y - rhs[step * M + ui];
-        } else {
-            const int k = uhi - 1 - t;    // lam_k = J~_{k+1}^T lam_{k+1} + g_k
-            lds[lane] = u;
-            lds_barrier();
-            const float wt = lds_dot<MP>(lds, un, wv);
-            lds_barrier();
-            if (run && ui < M) {
-                const size_t step = (size_t)ub * T + k;
-                float y = 0.f;
-                if (t > 0 && !(WU && ui < N && k + 1 <= tw)) {   // P_{k+1} = P_1 drops observed rows
-                    const float m = (float)mask_bit(masks, step + 1, MW, ui);
-                    y = pu * fmaf(Au, u, m * wt);
-                }
-                float gk;
-                if (rhs) gk = rhs[step * M + ui];
-                else gk = (ui < N && (!WU || k >= tw))
-                              ? seed_scale * (z[step * M + ui] - x[((size_t)ub * (T + 1) + k + 1) * N + ui])
-                              : 0.f;
-                u = y + gk;
-            }
-        }
-    }
-
-    // ---- write the aggregates
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int id = chain0 + n;
-        if (id < nchains && (plen[n] > 0 || us1[n] > us0[n])) {
-            const int col = 16 * Jt + c - n * MP;
-            float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + col] = acc[I][Jt][r];
-        }
-    }
-    {
-        const int id = chain0 + un;
-        if (id < nchains) vout[(size_t)id * MP + ui] = u;
     }
 }
 
@@ -2821,106 +2633,6 @@ int launch_ctl_init(const NewtonDev &nd, uint32_t *seq, int B, hipStream_t st) {
     return DEER_OK;
 }
 
-// ---------------------------------------------------------------------------------------
-// reverse fix-up: lam from the carry, written out, with the parameter-gradient partial
-// sums of this chunk: dW[i][j] += lam_i relu(z~_j), dA_i += lam_i z~_i, dh_i += lam_i
-// (layout gpart[chain][MP][MP + 2]).
-// ---------------------------------------------------------------------------------------
-template <int MP, bool WU>
-__global__ __launch_bounds__(64) void k_fixup_rev_plrnn(const float *__restrict__ A, const float *__restrict__ W,
-                                                        float alpha, int N, const uint32_t *__restrict__ masks,
-                                                        const float *__restrict__ gin, float seed_scale,
-                                                        const float *__restrict__ x, const float *__restrict__ z0,
-                                                        const float *__restrict__ z, const float *__restrict__ carry_in,
-                                                        float *__restrict__ lam_out, float *__restrict__ gpart, int B,
-                                                        int T, int M, int C, int ncs, int tw) {
-    using G = Geo<MP>;
-    __shared__ __align__(16) float lds[64];
-    const int lane = threadIdx.x, n = lane / MP, i = lane % MP;
-    const int id = blockIdx.x * G::NCH + n;
-    const bool ok = id < B * ncs;
-    const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
-    const int s0 = cc * C, s1 = ok ? min(s0 + C, T) : s0;
-    float wcol[MP], dW[MP];
-#pragma unroll
-    for (int k = 0; k < MP; ++k) {
-        wcol[k] = (i < M && k < M) ? W[k * M + i] : 0.f;
-        dW[k] = 0.f;
-    }
-    const float pi = p_of(i, N, alpha), Ai = i < M ? A[i] : 0.f;
-    float lam = (ok && i < M) ? carry_in[(size_t)id * MP + i] : 0.f;
-    float dA = 0.f, dh = 0.f;
-    const int maxlen = __builtin_amdgcn_readfirstlane(C);
-    // per-step inputs (mask of step k + 1, cotangent g_k, forced state z~_{k-1}), PD steps ahead
-    auto fetch = [&](int t, float &mv, float &gv, float &zv) {
-        const int k = s1 - 1 - t;
-        const bool run = k >= s0 && i < M;
-        mv = 0.f;
-        gv = 0.f;
-        zv = 0.f;
-        if (run) {
-            const size_t step = (size_t)b * T + k;
-            if (k + 1 < T) mv = (float)mask_bit(masks, step + 1, G::MW, i);
-            if (gin) gv = gin[step * M + i];
-            else if (i < N && (!WU || k >= tw))   // no MSE seed for the warm-up states
-                gv = seed_scale * (z[step * M + i] - x[((size_t)b * (T + 1) + k + 1) * N + i]);
-            zv = forced_state(x, z0, z, b, k, i, T, M, N, alpha, WU ? tw : 0);
-        }
-    };
-    constexpr int PD = 1;
-    float mq[PD], gq[PD], zq[PD];
-#pragma unroll
-    for (int q = 0; q < PD; ++q) fetch(q, mq[q], gq[q], zq[q]);
-    for (int t = 0; t < maxlen; ++t) {
-        const int k = s1 - 1 - t;
-        const bool run = k >= s0 && i < M;
-        const float mc = mq[0], gk = gq[0], zc = zq[0];
-#pragma unroll
-        for (int q = 0; q + 1 < PD; ++q) {
-            mq[q] = mq[q + 1];
-            gq[q] = gq[q + 1];
-            zq[q] = zq[q + 1];
-        }
-        fetch(t + PD, mq[PD - 1], gq[PD - 1], zq[PD - 1]);
-        lds[lane] = lam;
-        lds_barrier();
-        const float wt = lds_dot<MP>(lds, n, wcol);
-        lds_barrier();
-        float zt = 0.f;
-        if (run) {
-            const size_t step = (size_t)b * T + k;
-            // J~_{k+1}^T lam, P_{k+1} = P_1 dropping the observed rows in a latent warm-up step
-            const bool jon = k + 1 < T && !(WU && i < N && k + 1 <= tw);
-            const float y = jon ? pi * fmaf(Ai, lam, mc * wt) : 0.f;
-            lam = y + gk;
-            if (lam_out) lam_out[step * M + i] = lam;
-            zt = zc;
-            dA = fmaf(lam, zt, dA);
-            dh += lam;
-        }
-        const float lr = run ? lam : 0.f;
-        lds[lane] = (run && zt > 0.f) ? zt : 0.f;
-        lds_barrier();
-        const float4 *l4 = reinterpret_cast<const float4 *>(lds + n * MP);
-#pragma unroll
-        for (int q = 0; q < MP / 4; ++q) {
-            const float4 v = l4[q];
-            dW[4 * q + 0] = fmaf(lr, v.x, dW[4 * q + 0]);
-            dW[4 * q + 1] = fmaf(lr, v.y, dW[4 * q + 1]);
-            dW[4 * q + 2] = fmaf(lr, v.z, dW[4 * q + 2]);
-            dW[4 * q + 3] = fmaf(lr, v.w, dW[4 * q + 3]);
-        }
-        lds_barrier();
-    }
-    if (ok) {
-        float *gp = gpart + ((size_t)id * MP + i) * (MP + 2);
-#pragma unroll
-        for (int k = 0; k < MP; ++k) gp[k] = dW[k];
-        gp[MP] = dA;
-        gp[MP + 1] = dh;
-    }
-}
-
 // sum the per-chunk partials in float64 in two stages: blocks over (slice of the chains, 64
 // consecutive entries of [MP][MP + 2]), the four waves of a block taking every fourth chain of
 // the slice with 8 loads in flight and their sums added through LDS in a fixed order; then the
@@ -3065,29 +2777,6 @@ int launch_resjac_plrnn(const PlrnnArgs &a, const float *z, float *F, float *r, 
     }
 #undef RJ
     DEER_LAUNCH_CHECK("k_resjac_plrnn");
-    return DEER_OK;
-}
-
-int launch_chunk_product_plrnn(const PlrnnArgs &a, bool rev, const uint32_t *masks, const float *rhs, const float *z,
-                               float seed_scale, float *P, float *v, const int *active, int C, int ncs,
-                               hipStream_t st) {
-    const int MP = padded(a.M);
-    const int nch = a.B * ncs;
-    const int grid = (nch + (64 / MP) - 1) / (64 / MP);
-    KTimer kt("k_chunk_product_plrnn", st);
-#define CP(MPV, R, WUV)                                                                                              \
-    hipLaunchKernelGGL((k_chunk_product_plrnn<MPV, R, WUV>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.alpha, a.N,    \
-                       masks, rhs, z, a.x, seed_scale, P, v, active, a.B, a.T, a.M, C, ncs, a.tw)
-#define CPW(MPV, R) \
-    if (a.tw > 0) CP(MPV, R, true); else CP(MPV, R, false);
-    if (!rev) {
-        if (MP == 16) { CPW(16, false) } else if (MP == 32) { CPW(32, false) } else { CPW(64, false) }
-    } else {
-        if (MP == 16) { CPW(16, true) } else if (MP == 32) { CPW(32, true) } else { CPW(64, true) }
-    }
-#undef CPW
-#undef CP
-    DEER_LAUNCH_CHECK("k_chunk_product_plrnn");
     return DEER_OK;
 }
 
@@ -3304,31 +2993,6 @@ int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const floa
 #undef FX16
 #undef FX
     DEER_LAUNCH_CHECK("k_fixup_fwd_plrnn");
-    return DEER_OK;
-}
-
-int launch_fixup_rev_plrnn(const PlrnnArgs &a, const uint32_t *masks, const float *g, float seed_scale, const float *z,
-                           const float *carry_in, float *lam, float *gpart, int C, int ncs, hipStream_t st) {
-    const int MP = padded(a.M);
-    const int nch = a.B * ncs;
-    const int grid = (nch + (64 / MP) - 1) / (64 / MP);
-    KTimer kt("k_fixup_rev_plrnn", st);
-#define FR(MPV)                                                                                                      \
-    if (a.tw > 0)                                                                                                    \
-        hipLaunchKernelGGL((k_fixup_rev_plrnn<MPV, true>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.alpha, a.N, masks, \
-                           g, seed_scale, a.x, a.z0, z, carry_in, lam, gpart, a.B, a.T, a.M, C, ncs, a.tw);         \
-    else                                                                                                             \
-        hipLaunchKernelGGL((k_fixup_rev_plrnn<MPV, false>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.alpha, a.N,     \
-                           masks, g, seed_scale, a.x, a.z0, z, carry_in, lam, gpart, a.B, a.T, a.M, C, ncs, 0)
-    if (MP == 16) {
-        FR(16);
-    } else if (MP == 32) {
-        FR(32);
-    } else {
-        FR(64);
-    }
-#undef FR
-    DEER_LAUNCH_CHECK("k_fixup_rev_plrnn");
     return DEER_OK;
 }
 

@@ -1,11 +1,13 @@
 // Vanilla PLRNN, 16 < M <= 64: the Newton pass's first two kernels (eqs. GTF_residual,
-// GTF_DEER_update).
+// GTF_DEER_update) and the adjoint's (eq. backward_recursion).
 //
 //   k_newton_local_plrnn   residual r_t = z_t - F(z~_{t-1}), ReLU masks m_t and the chunk-local
 //                          solution v_c (from a zero carry), 16 chunks as matrix-core columns;
 //                          says which chunks' masks changed since the pass before
 //   k_chunk_product_split  P_c = J~_e ... J~_s of a chunk from the masks, J~_t = gamma (diag(A) +
 //                          W diag(m_t)) diag(p), on the fp16 matrix cores with split operands
+//   k_adjoint_walk_plrnn   the adjoint down a chunk: its local solution and the masks, or from the
+//                          carry the adjoint and the parameter gradients
 //
 // P_c depends on the masks and the damping only.  Near the solution few ReLU decisions change
 // from one Newton update to the next, so a chunk whose masks and damping are those its stored
@@ -18,6 +20,17 @@
 namespace deer {
 
 __device__ __forceinline__ float sp_p(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
+
+// mask word of 32 latents from its eight nibbles, one per byte
+__device__ __forceinline__ uint32_t pack_nibbles(const uint8_t *n8) {
+    const uint2 n = *reinterpret_cast<const uint2 *>(n8);
+    uint32_t lo = n.x, hi = n.y;
+    lo = (lo | (lo >> 4)) & 0x00ff00ffu;
+    lo = (lo | (lo >> 8)) & 0xffffu;
+    hi = (hi | (hi >> 4)) & 0x00ff00ffu;
+    hi = (hi | (hi >> 8)) & 0xffffu;
+    return lo | (hi << 16);
+}
 
 // ---------------------------------------------------------------------------------------
 // residual, masks, local solution.  Block = 16 chunks (column c) x MP / 16 waves; wave w owns the
@@ -202,13 +215,7 @@ __global__ __launch_bounds__(MP * 4) void k_newton_local_plrnn(
             uint32_t w[MW];
 #pragma unroll
             for (int k = 0; k < MW; ++k) {
-                const uint2 n8 = *reinterpret_cast<const uint2 *>(&mls[td & (MR - 1)][c][8 * k]);
-                uint32_t lo = n8.x, hi = n8.y;   // four nibbles each, one per byte
-                lo = (lo | (lo >> 4)) & 0x00ff00ffu;
-                lo = (lo | (lo >> 8)) & 0xffffu;
-                hi = (hi | (hi >> 4)) & 0x00ff00ffu;
-                hi = (hi | (hi >> 8)) & 0xffffu;
-                w[k] = lo | (hi << 16);
+                w[k] = pack_nibbles(&mls[td & (MR - 1)][c][8 * k]);
                 masks[(rowb + td) * MW + k] = w[k];
             }
             diff |= (w[0] ^ old0) | (MW > 1 ? w[MW - 1] ^ old1 : 0u);
@@ -460,7 +467,270 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     if (!REV && pgam && lane == 0) pgam[id] = gm;
 }
 
+// ---------------------------------------------------------------------------------------
+// the adjoint's walk of a chunk, lam_k = J~_{k+1}^T lam_{k+1} + g_k for k = s1 - 1 .. s0 (eq.
+// backward_recursion), in the layout of k_newton_local_plrnn: 16 chunks as columns, wave w the row
+// tile w of W^T, lam through double-buffered LDS, one barrier a step.
+//   FINAL false: from a zero lam; the result is the chunk's local solution v_c.  The masks (formed
+//     here from z and x, every row read once) are written for the chunk products.
+//   FINAL true: from the carry; lam is written and the parameter gradients
+//     dW += lam_k relu(z~_k)^T,  dA += lam_k o z~_k,  dh += lam_k
+//     are summed over the block's 16 chunks (dW on the matrix cores, the chunks as the k
+//     dimension), two steps at a time in fp32 and those sums in float64, one partial
+//     gpart[block][MP][MP + 2] per block.
+// z~_k = forced(z_{k-1}, x_k) serves the gradient of step k and is the mask of step k - 1's Jacobian
+// term; the same rows give the MSE seed of step k - 1.  HBM-bound: z, x (and g) read, lam written
+// (M = 64, 32 x 131072 steps: 0.82 ms, and 1.15 ms with the gradients; the lane-per-latent kernel with
+// the gradient products on the vector units took 3.8 ms).
+// ---------------------------------------------------------------------------------------
+template <int MP, bool VEC, bool WU, bool GIN, bool FINAL>
+__global__ __launch_bounds__(MP * 4) __attribute__((amdgpu_waves_per_eu(2))) void k_adjoint_walk_plrnn(
+    const float *__restrict__ A, const float *__restrict__ W, float alpha, int N, const float *__restrict__ x,
+    const float *__restrict__ z0, const float *__restrict__ z, const float *__restrict__ gin, float seed_scale,
+    const float *__restrict__ carry_in, float *__restrict__ out, uint32_t *__restrict__ masks,
+    float *__restrict__ gpart, int B, int T, int M, int C, int ncs, int tw) {
+    constexpr int NW = MP / 16, NS = MP / 4, DQ = MP + 4, MW = MP / 32, PD = VEC && !GIN && !FINAL ? 8 : 4, MR = 2 * PD;
+    __shared__ __align__(16) float lls[2][16 * DQ], rls[FINAL ? 2 : 1][16 * DQ];   // lam, relu(z~): [buffer][chunk][latent]
+    __shared__ __align__(16) uint8_t mls[FINAL ? 1 : MR][16][MP / 4];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
+    const int nchains = B * ncs;
+    const int id = blockIdx.x * 16 + c;
+    const bool ok = id < nchains;
+    const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
+    const int s0 = cc * C, s1 = min(s0 + C, T);
+    const int len = ok ? max(s1 - s0, 0) : 0;
+    int maxlen = len;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
+    maxlen = __builtin_amdgcn_readfirstlane(maxlen);
+    float aw[NS];   // rows of W^T
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int k = 16 * (s / 4) + 4 * g + (s % 4), row = 16 * wv + c;
+        aw[s] = (row < M && k < M) ? W[k * M + row] : 0.f;
+    }
+    const int i0 = 16 * wv + 4 * g;
+    float Av[4], pv[4];
+    bool fo[4], la[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        la[q] = i0 + q < M;
+        Av[q] = la[q] ? A[i0 + q] : 0.f;
+        pv[q] = sp_p(i0 + q, N, alpha);
+        fo[q] = i0 + q < N;
+    }
+    const size_t rowb = (size_t)b * T, rowx = (size_t)b * (T + 1);
+    // z~_s of this lane's latents from the rows z_{s-1} (zr) and x_s (xr)
+    auto forced = [&](int s, const float (&zr)[4], const float (&xr)[4], float (&zt)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float f = __fadd_rn(__fmul_rn(pv[q], zr[q]), __fmul_rn(alpha, xr[q]));
+            if (WU && s <= tw) f = xr[q];
+            zt[q] = (s == 0 || !fo[q]) ? zr[q] : f;
+        }
+    };
+    // rows of step t (k = s1 - 1 - t): z_{k-1} (z_0 itself, given or [x_0; 0], for k = 0), x_k and
+    // the cotangent g_k; branch-free as in the forward kernel
+    auto fetch = [&](int t, float4 &zn, float4 &xn, float4 &gn) {
+        const bool run = t < len;
+        const int k = run ? s1 - 1 - t : s0;
+        float zv[4], xv[4], gv[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (VEC) {
+            const int iz = i0 < M ? i0 : 0, ix = i0 < N ? i0 : 0;
+            const float4 x4 = N > 0 ? *reinterpret_cast<const float4 *>(x + (rowx + k) * N + ix) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 z4 = *reinterpret_cast<const float4 *>(z + (rowb + (k > 0 ? k - 1 : 0)) * M + iz);
+            xv[0] = x4.x, xv[1] = x4.y, xv[2] = x4.z, xv[3] = x4.w;
+            zv[0] = z4.x, zv[1] = z4.y, zv[2] = z4.z, zv[3] = z4.w;
+            if constexpr (GIN) {
+                const float4 g4 = *reinterpret_cast<const float4 *>(gin + (rowb + k) * M + iz);
+                gv[0] = g4.x, gv[1] = g4.y, gv[2] = g4.z, gv[3] = g4.w;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                xv[q] = N > 0 ? x[(rowx + k) * N + (fo[q] ? i0 + q : 0)] : 0.f;
+                zv[q] = z[(rowb + (k > 0 ? k - 1 : 0)) * M + (la[q] ? i0 + q : 0)];
+                if constexpr (GIN) gv[q] = gin[(rowb + k) * M + (la[q] ? i0 + q : 0)];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            xv[q] = run && fo[q] ? xv[q] : 0.f;
+            if (k == 0) zv[q] = z0 ? z0[(size_t)b * M + (la[q] ? i0 + q : 0)] : xv[q];
+            zv[q] = run && la[q] ? zv[q] : 0.f;
+            gv[q] = run && la[q] ? gv[q] : 0.f;
+        }
+        zn = make_float4(zv[0], zv[1], zv[2], zv[3]);
+        xn = make_float4(xv[0], xv[1], xv[2], xv[3]);
+        gn = make_float4(gv[0], gv[1], gv[2], gv[3]);
+    };
+    // entering step k = s1 - 1: z_k, x_{k+1} (MSE seed) and the mask z~_{k+1} > 0
+    float zk[4], xk[4], zn1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        zk[q] = len > 0 && la[q] ? z[(rowb + s1 - 1) * M + i0 + q] : 0.f;
+        xk[q] = len > 0 && fo[q] ? x[(rowx + s1) * N + i0 + q] : 0.f;
+    }
+    forced(s1, zk, xk, zn1);
+    float lam[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lam[q] = FINAL && ok && la[q] ? carry_in[(size_t)id * MP + i0 + q] : 0.f;
+    *reinterpret_cast<float4 *>(&lls[0][c * DQ + i0]) = make_float4(lam[0], lam[1], lam[2], lam[3]);
+    v4f dw[NW];
+    float dA[4], dh[4];
+    double dws[NW][4], dAs[4], dhs[4];
+    if constexpr (FINAL) {
+#pragma unroll
+        for (int J = 0; J < NW; ++J) {
+            dw[J] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) dws[J][q] = 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            dA[q] = dh[q] = 0.f;
+            dAs[q] = dhs[q] = 0.0;
+        }
+    }
+    // dW += lam relu(z~)^T of the step whose rows are in buffer `buf`
+    auto grad = [&](int buf) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float lv = lls[buf][(4 * s + g) * DQ + 16 * wv + c];
+#pragma unroll
+            for (int J = 0; J < NW; ++J)
+                dw[J] = mfma16x16x4(lv, rls[buf][(4 * s + g) * DQ + 16 * J + c], dw[J]);
+        }
+    };
+    auto flush = [&]() {
+#pragma unroll
+        for (int J = 0; J < NW; ++J) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) dws[J][q] += (double)dw[J][q];
+            dw[J] = (v4f){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            dAs[q] += (double)dA[q];
+            dhs[q] += (double)dh[q];
+            dA[q] = dh[q] = 0.f;
+        }
+    };
+    float4 zq[PD], xq[PD], gq[PD];
+#pragma unroll
+    for (int k = 0; k < PD; ++k) fetch(k, zq[k], xq[k], gq[k]);
+    lds_barrier();
+    for (int t0 = 0; t0 < maxlen; t0 += PD) {
+        float4 zn2[PD], xn2[PD], gn2[PD];
+#pragma unroll
+        for (int k = 0; k < PD; ++k) fetch(t0 + PD + k, zn2[k], xn2[k], gn2[k]);
+#pragma unroll
+        for (int k8 = 0; k8 < PD; ++k8) {
+            const int t = t0 + k8;
+            if (t >= maxlen) break;
+            const int cur = k8 & 1;   // PD is even: buffer parity follows t
+            const bool run = t < len;
+            const int k = s1 - 1 - t;
+            const float zr[4] = {zq[k8].x, zq[k8].y, zq[k8].z, zq[k8].w}, xr[4] = {xq[k8].x, xq[k8].y, xq[k8].z, xq[k8].w};
+            const float gr[4] = {gq[k8].x, gq[k8].y, gq[k8].z, gq[k8].w};
+            v4f y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+#pragma unroll
+            for (int j = 0; j < NS / 4; ++j) {
+                const float4 d = *reinterpret_cast<const float4 *>(&lls[cur][c * DQ + 16 * j + 4 * g]);
+                y0 = mfma16x16x4(aw[4 * j + 0], d.x, y0);
+                y1 = mfma16x16x4(aw[4 * j + 1], d.y, y1);
+                y0 = mfma16x16x4(aw[4 * j + 2], d.z, y0);
+                y1 = mfma16x16x4(aw[4 * j + 3], d.w, y1);
+            }
+            if (FINAL && t > 0) grad(cur);   // step t - 1
+            if (FINAL && (t & 1)) flush();   // short fp32 sums: their rounding is what is left
+            float zt[4], rz[4];
+            forced(k, zr, xr, zt);
+            uint32_t nib = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool pos = zt[q] > 0.f;
+                nib |= pos ? 1u << q : 0u;
+                rz[q] = pos ? zt[q] : 0.f;
+                const bool jon = k + 1 < T && !(WU && fo[q] && k + 1 <= tw);   // P_{k+1} = P_1 drops observed rows
+                const float y = jon ? pv[q] * fmaf(Av[q], lam[q], zn1[q] > 0.f ? y0[q] + y1[q] : 0.f) : 0.f;
+                float gk;
+                if constexpr (GIN) gk = gr[q];
+                else gk = fo[q] && (!WU || k >= tw) ? seed_scale * (zk[q] - xk[q]) : 0.f;   // warm-up states: no seed
+                lam[q] = run && la[q] ? y + gk : (FINAL ? 0.f : lam[q]);
+                if constexpr (FINAL) {
+                    dA[q] = fmaf(lam[q], run ? zt[q] : 0.f, dA[q]);
+                    dh[q] += lam[q];
+                }
+                zk[q] = zr[q];
+                xk[q] = xr[q];
+                zn1[q] = zt[q];
+            }
+            *reinterpret_cast<float4 *>(&lls[cur ^ 1][c * DQ + i0]) = make_float4(lam[0], lam[1], lam[2], lam[3]);
+            if constexpr (FINAL) {
+                *reinterpret_cast<float4 *>(&rls[cur ^ 1][c * DQ + i0]) =
+                    run ? make_float4(rz[0], rz[1], rz[2], rz[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+                if (out && run) {
+                    float *lo = out + (rowb + k) * M + i0;
+                    if constexpr (VEC) {
+                        if (i0 < M) *reinterpret_cast<float4 *>(lo) = make_float4(lam[0], lam[1], lam[2], lam[3]);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (la[q]) lo[q] = lam[q];
+                    }
+                }
+            } else {
+                mls[t & (MR - 1)][c][4 * wv + g] = (uint8_t)nib;
+            }
+            lds_barrier();
+        }
+#pragma unroll
+        for (int k = 0; k < PD; ++k) {
+            zq[k] = zn2[k];
+            xq[k] = xn2[k];
+            gq[k] = gn2[k];
+        }
+        if constexpr (!FINAL) {
+            const int td = t0 + 4 * wv + g;
+            if (wv < PD / 4 && td < len) {
+#pragma unroll
+                for (int k = 0; k < MW; ++k)
+                    masks[(rowb + s1 - 1 - td) * MW + k] = pack_nibbles(&mls[td & (MR - 1)][c][8 * k]);
+            }
+        }
+    }
+    if constexpr (!FINAL) {
+        if (ok) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[(size_t)id * MP + i0 + q] = lam[q];
+        }
+    } else {
+        if (maxlen > 0) grad(maxlen & 1);   // the last step
+        flush();
+        float *gp = gpart + (size_t)blockIdx.x * MP * (MP + 2);
+#pragma unroll
+        for (int J = 0; J < NW; ++J)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) gp[(i0 + r) * (MP + 2) + 16 * J + c] = (float)dws[J][r];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // the 16 chunks' sums
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                dAs[q] += __shfl_xor(dAs[q], off, 64);
+                dhs[q] += __shfl_xor(dhs[q], off, 64);
+            }
+            if (c == 0) {
+                gp[(i0 + q) * (MP + 2) + MP] = (float)dAs[q];
+                gp[(i0 + q) * (MP + 2) + MP + 1] = (float)dhs[q];
+            }
+        }
+    }
+}
+
 // ---- launchers ---------------------------------------------------------------------------
+int adjoint_walk_blocks(int B, int ncs) { return (B * ncs + 15) / 16; }
+
 // 16-byte rows of z and x: every row a multiple of four floats on a 16-byte boundary
 static bool rows16(const PlrnnArgs &a, const float *z, const float *zalt) {
     return a.M % 4 == 0 && a.N % 4 == 0 && (((uintptr_t)a.x | (uintptr_t)z | (uintptr_t)zalt) & 15u) == 0;
@@ -485,6 +755,31 @@ int launch_newton_local_plrnn(const PlrnnArgs &a, const float *z, const float *z
 #undef NLW
 #undef NL
     DEER_LAUNCH_CHECK("k_newton_local_plrnn");
+    return DEER_OK;
+}
+
+int launch_adjoint_walk_plrnn(const PlrnnArgs &a, bool fin, const float *g, float seed_scale, const float *z,
+                              const float *carry, float *out, uint32_t *masks, float *gpart, int C, int ncs,
+                              hipStream_t st) {
+    const int grid = adjoint_walk_blocks(a.B, ncs);
+    const bool vec = rows16(a, z, z) && (((uintptr_t)g | (fin ? (uintptr_t)out : 0)) & 15u) == 0;
+    KTimer kt(fin ? "k_fixup_rev_plrnn" : "k_adjoint_local_plrnn", st);
+#define AW(MPV, VV, WUV, GV, FV)                                                                                       \
+    hipLaunchKernelGGL((k_adjoint_walk_plrnn<MPV, VV, WUV, GV, FV>), dim3(grid), dim3(MPV * 4), 0, st, a.A, a.W, a.alpha, \
+                       a.N, a.x, a.z0, z, g, seed_scale, carry, out, masks, gpart, a.B, a.T, a.M, C, ncs, a.tw)
+#define AWF(MPV, VV, WUV, GV) if (fin) AW(MPV, VV, WUV, GV, true); else AW(MPV, VV, WUV, GV, false)
+#define AWG(MPV, VV, WUV) if (g) { AWF(MPV, VV, WUV, true); } else { AWF(MPV, VV, WUV, false); }
+#define AWW(MPV, VV) if (a.tw > 0) { AWG(MPV, VV, true) } else { AWG(MPV, VV, false) }
+    if (padded_dim(a.M) == 32) {
+        if (vec) { AWW(32, true) } else { AWW(32, false) }
+    } else {
+        if (vec) { AWW(64, true) } else { AWW(64, false) }
+    }
+#undef AWW
+#undef AWG
+#undef AWF
+#undef AW
+    DEER_LAUNCH_CHECK("k_adjoint_walk_plrnn");
     return DEER_OK;
 }
 

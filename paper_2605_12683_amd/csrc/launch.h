@@ -43,9 +43,6 @@ int padded_dim(int M);
 // vanilla PLRNN
 int launch_resjac_plrnn(const PlrnnArgs &a, const float *z, float *F, float *r, float *J, uint32_t *masks,
                         const int *active, hipStream_t st);
-int launch_chunk_product_plrnn(const PlrnnArgs &a, bool rev, const uint32_t *masks, const float *rhs, const float *z,
-                               float seed_scale, float *P, float *v, const int *active, int C, int ncs,
-                               hipStream_t st);
 // forward pass, M <= 16: block 0 writes pass_no to the host-visible word *mark as it
 // starts (every kernel queued before it has completed); mark may be null
 int launch_newton_product_plrnn16(const PlrnnArgs &a, const float *z, const float *zalt, const int *zsel, float *P,
@@ -61,6 +58,13 @@ int launch_newton_local_plrnn(const PlrnnArgs &a, const float *z, const float *z
                               int ncs, uint32_t *mark, uint32_t pass_no, hipStream_t st);
 int launch_chunk_product_split(const PlrnnArgs &a, bool rev, const uint32_t *masks, const int *changed, float *pgam,
                                float *P, const int *active, const float *gamma, int C, int ncs, hipStream_t st);
+// adjoint, 16 < M <= 64: fin false: local solutions of the chunks into out [chunks][MP] and the masks
+// for the products; fin true: lam into out [B,T,M] (or null) from the carries, and the gradient
+// partials gpart[adjoint_walk_blocks][MP][MP + 2]
+int adjoint_walk_blocks(int B, int ncs);
+int launch_adjoint_walk_plrnn(const PlrnnArgs &a, bool fin, const float *g, float seed_scale, const float *z,
+                              const float *carry, float *out, uint32_t *masks, float *gpart, int C, int ncs,
+                              hipStream_t st);
 // M <= 16 with wave maps (P, v from launch_newton_product_plrnn with wmaps): carries of the
 // wave maps, written to the carry slot of each wave's first chunk
 int launch_carry_walk16(bool rev, const float *P, const float *v, float *carry, const int *active, int B, int ncs,
@@ -124,8 +128,6 @@ int launch_newton_pass16(const PlrnnArgs &a, float *z, float *zalt, const float 
 int launch_ctl_init(const NewtonDev &nd, uint32_t *seq, int B, hipStream_t st);
 int launch_seq_max(const uint32_t *chain_bits, const int *active, uint32_t *norm_bits, int B, int ncs,
                    hipStream_t st);
-int launch_fixup_rev_plrnn(const PlrnnArgs &a, const uint32_t *masks, const float *g, float seed_scale, const float *z,
-                           const float *carry_in, float *lam, float *gpart, int C, int ncs, hipStream_t st);
 int launch_reduce_gpart(const float *gpart, int nchains, int MP, int M, float *dA, float *dW, float *dh,
                         double *part2, hipStream_t st);
 size_t reduce_gpart_ws_bytes(int MP);

@@ -101,3 +101,49 @@ def test_nonfinite_weights():
     m["W"][3, 5] = np.nan
     say("split NaN weights")
     assert D.deer_solve(m, c.x, 0.2, 40, tol=1e-5, max_iter=50)["status"] == 3
+
+
+@pytest.mark.parametrize("M,N,B,T,chunk,T_w,own", [
+    (17, 3, 2, 40, 5, 0, False), (20, 20, 1, 130, 65, 0, True), (32, 8, 17, 64, 16, 9, False), (33, 33, 2, 201, 66, 0, True),
+    (48, 12, 3, 65, 8, 64, False), (64, 64, 2, 1, 16, 0, False), (64, 64, 3, 2, 1, 0, True), (64, 4, 2, 90, 31, 30, True),
+    (64, 64, 1, 300, 100, 0, False)])
+def test_adjoint(M, N, B, T, chunk, T_w, own):
+    """lam and the gradients with the MSE seed and with a given cotangent and initial state, against
+    the oracle at the same float32 trajectory."""
+    os.environ["DEER_CHUNK"] = str(chunk)
+    c = _case(M, N, B, T, 6400 + M + T)
+    m = oracle_model(c)
+    rng = np.random.default_rng(M)
+    z0 = rng.standard_normal((B, M)).astype(np.float32) if own else None
+    z32 = O.rollout(m, c.x, 0.2, N, z0=z0, T_w=T_w).astype(np.float32)
+    g = rng.standard_normal(z32.shape).astype(np.float32) if own else None
+    say("split adjoint", M, N, B, T, chunk, T_w, own)
+    out = D.deer_adjoint(m, c.x, z32, 0.2, N, z0=z0, g=g, T_w=T_w)
+    lam = O.adjoint(m, c.x, z32, 0.2, N, z0=z0, g=g, mask_precision="float32", T_w=T_w)
+    ref = O.param_grads(m, c.x, z32, 0.2, N, lam, z0=z0, mask_precision="float32", T_w=T_w)
+    assert rel_inf(out["lam"].cpu().numpy(), lam) < TOL
+    for k in ("A", "W", "h"):
+        assert rel_inf(out["grads"][k].cpu().numpy(), ref[k]) < TOL, k
+
+
+@pytest.mark.parametrize("M", [32, 64])
+def test_unaligned_rows(M):
+    """x, z and g four bytes off a 16-byte boundary: the scalar loads give the values of the wide ones."""
+    c = _case(M, M, 2, 150, 6500 + M)
+    m = oracle_model(c)
+
+    def off(t):
+        b = torch.empty(t.numel() + 1, device="cuda")
+        b[1:] = t.reshape(-1)
+        return b[1:].view(t.shape)
+
+    x = torch.from_numpy(c.x).cuda()
+    g = torch.randn(2, 150, M, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    say("split unaligned", M)
+    res = [D.deer_solve(m, xx, 0.2, M, tol=1e-5, z=zz) for xx, zz in ((x, torch.empty(2, 150, M, device="cuda")),
+                                                                     (off(x), off(torch.empty(2, 150, M, device="cuda"))))]
+    assert torch.equal(res[0]["z"], res[1]["z"])
+    for gg in (None, g):
+        a = D.deer_adjoint(m, x, res[0]["z"], 0.2, M, g=gg)
+        b = D.deer_adjoint(m, off(x), off(res[0]["z"]), 0.2, M, g=None if gg is None else off(gg))
+        assert torch.equal(a["lam"], b["lam"]) and all(torch.equal(a["grads"][k], b["grads"][k]) for k in a["grads"])
