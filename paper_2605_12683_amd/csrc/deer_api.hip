@@ -9,6 +9,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <chrono>
 #include <vector>
 
@@ -366,6 +367,8 @@ static DenseWs carve_dense(void *ws, int B, int T, int M, size_t *bytes, bool sh
 struct ShWs {
     float *r, *J, *g, *lam, *part;
     uint32_t *masks;
+    uint32_t *masks2;   // solve without a stored Jacobian: the masks of every other pass,
+    float *pgam;        // and the damping of each chunk's stored product
     DenseWs d;
     NewtonCtl ctl;
 };
@@ -396,8 +399,13 @@ static ShWs carve_sh(void *ws, int B, int T, int M, int L, int op, bool need_g, 
     w.J = stored_J ? c.take<float>((size_t)B * T * M * M) : nullptr;
     if (op == DEER_OP_SOLVE) {
         const int C = choose_chunk(B, T, padded_dim(M), !stored_J);
-        w.ctl = carve_ctl(c, B, (size_t)T * M, (size_t)B * ((T + C - 1) / C));
+        const size_t nch = (size_t)B * ((T + C - 1) / C);
+        w.ctl = carve_ctl(c, B, (size_t)T * M, nch);
         w.r = c.take<float>((size_t)B * T * M);
+        if (!stored_J) {
+            w.masks2 = c.take<uint32_t>((size_t)B * T * LW);
+            w.pgam = c.take<float>(nch);
+        }
     } else {
         if (need_g) w.g = c.take<float>((size_t)B * T * M);
         if (need_lam) w.lam = c.take<float>((size_t)B * T * M);
@@ -942,19 +950,25 @@ static int solve_shplrnn(const deer_model *m, const deer_forcing *f, const deer_
         if ((rc = host_block(B, ctl.nd, &mark_unused))) return rc;
     }
     const FusedCtl fc{ctl.nd, ctl.seq, o->tol, o->step_bound == 0.f ? kDefaultStepBound : o->step_bound, kDamp};
+    // no chunk product is stored yet
+    if (fused && (rc = launch_fill_f32(w.pgam, (size_t)B * d.ncs, NAN, st))) return rc;
+    // the masks of this pass and of the one before (a sequence that runs has run in every pass)
+    uint32_t *mk = w.masks, *mk_prev = w.masks2;
     auto update = [&](const int *dact, const float *gam, const int *zsel, float *zb, float *za, uint32_t *mark,
                       uint32_t pass_no) -> int {
         int r;
+        if (fused) std::swap(mk, mk_prev);
         if (fused && sh_res_mfma()) {
-            if ((r = launch_resjac_shmfma(a, zb, za, zsel, w.r, w.masks, dact, st, mark, pass_no))) return r;
-        } else if ((r = launch_resjac_shplrnn(a, zb, za, zsel, nullptr, w.r, w.masks, dact, st))) {
+            if ((r = launch_resjac_shmfma(a, zb, za, zsel, w.r, mk, dact, st, mark, pass_no))) return r;
+        } else if ((r = launch_resjac_shplrnn(a, zb, za, zsel, nullptr, w.r, mk, dact, st))) {
             return r;
         }
         if (fused) {
-            if ((r = launch_chunk_product_shfused(false, a, w.masks, w.r, -1.f, gam, d.P, d.v, dact, d.C, d.ncs, st)))
+            if ((r = launch_chunk_aggregates_sh(false, a, mk, mk_prev, w.r, -1.f, gam, w.pgam, d.P, d.v, dact, d.C, d.ncs,
+                                                st)))
                 return r;
             if ((r = launch_carry(d.MP, false, d.P, d.v, d.carry, dact, nullptr, B, d.ncs, d.gws, st))) return r;
-            return launch_fixup_shjvp(false, a, w.masks, w.r, -1.f, gam, d.carry, zb, za, zsel, w.ctl.chain_bits, dact,
+            return launch_fixup_shjvp(false, a, mk, w.r, -1.f, gam, d.carry, zb, za, zsel, w.ctl.chain_bits, dact,
                                       d.C, d.ncs, st, (ctl.fused && dact) ? &fc : nullptr);
         }
         if ((r = jacform_sh(a, w.masks, w.J, dact, gam, st))) return r;
@@ -1512,8 +1526,8 @@ int deer_adjoint_ex(const deer_model *m, const deer_forcing *f, int B, int T, co
         float *lo = lam ? lam : w.lam;
         if ((rc = launch_resjac_shplrnn(a, z, nullptr, nullptr, nullptr, nullptr, w.masks, nullptr, st))) return rc;
         if (fused) {
-            if ((rc = launch_chunk_product_shfused(true, a, w.masks, gg, 1.f, nullptr, d.P, d.v, nullptr, d.C, d.ncs,
-                                                   st)))
+            if ((rc = launch_chunk_aggregates_sh(true, a, w.masks, nullptr, gg, 1.f, nullptr, nullptr, d.P, d.v, nullptr,
+                                                 d.C, d.ncs, st)))
                 return rc;
             if ((rc = launch_carry(d.MP, true, d.P, d.v, d.carry, nullptr, nullptr, B, d.ncs, d.gws, st))) return rc;
             if ((rc = launch_fixup_shjvp(true, a, w.masks, gg, 1.f, nullptr, d.carry, nullptr, lo, nullptr, nullptr,

@@ -2529,7 +2529,7 @@ __global__ __launch_bounds__(MP * 4) void k_fixup_fwd_plrnn_mf(const float *__re
             chain_bits[(size_t)nchains + id] = zmax;
         }
     }
-    if (fc.seq) block16_arrive(fc, emax, zmax, ok, blockIdx.x * 16, ncs, lane);
+    if (fc.seq) block16_arrive(fc, emax, zmax, ok, b, ncs, lane);
 }
 
 // per-sequence max over its chains of the bits the forward fix-ups left:

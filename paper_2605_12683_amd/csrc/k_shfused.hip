@@ -4,20 +4,21 @@
 // is never written to HBM: the residual kernel leaves the hidden masks m_t (L bits per step),
 // and the two kernels here rebuild what they need of J~_t from them and from W1, W2.
 //
-//   k_chunk_product_shfused  per chunk, J~_t^T formed on the matrix cores (K = L, the masks
+//   k_chunk_aggregates_sh    per chunk, J~_t^T formed on the matrix cores (K = L, the masks
 //        applied to the W1 operand) lands in exactly the register layout of an A operand of
-//        J~_t, so the composition P <- J~_t P and the local solution u <- J~_t u + s r_t follow
-//        at once, as in the stored-Jacobian chunk product.  A wave owns one chunk and forms
+//        J~_t, so the composition P <- J~_t P follows at once.  A wave owns one chunk and forms
 //        the Jacobians of NT consecutive steps per pass over the W1 / W2 tiles in LDS.
 //   k_fixup_shjvp            the chunk re-run from its carry with J~_t applied as a
 //        Jacobian-vector product, Delta_t = gamma (A p Delta + W1 (m_t (W2 (p Delta)))) + s r_t.
 //        A block runs 16 chains as the 16 columns of two matrix-core products per step; its 4
 //        waves split the hidden units, hold their slices of W2 diag(p) and W1 as A fragments in
-//        registers for the whole chunk, and sum their partial W1 products through LDS.
+//        registers for the whole chunk, and sum their partial W1 products through LDS.  The same
+//        walk from a zero carry gives the chunk-local solutions (in k_chunk_aggregates_sh).
 // Per step this replaces 4 M^2 bytes written and read twice by 4 L / 8 bytes of masks.
 #include "common.h"
 #include "launch.h"
 #include "newton_ctl.h"
+#include "split16.h"
 
 namespace deer {
 
@@ -25,8 +26,12 @@ __device__ __forceinline__ float pf_at(int i, int N, float alpha) { return i < N
 
 static int shf_LP(int L) { return (L + 15) / 16 * 16; }
 
+// chunk products: W1 and W2 as hi and lo halves in blocks of 32 units, the mask table, five maxima of
+// each wave; local walk: double-buffered partial sums of the four waves and the maxima
 size_t shfused_product_lds(int M, int L) {
-    return (size_t)2 * padded_dim(M) * (shf_LP(L) + 4) * sizeof(float);
+    const size_t MP = padded_dim(M), prod = 8 * MP * ((L + 31) / 32 * 32) + 256 * sizeof(v4u) + 4 * 5 * sizeof(float);
+    const size_t walk = 2 * 4 * (MP / 16) * 64 * sizeof(v4f) + 4 * 16 * 2 * sizeof(uint32_t);
+    return prod > walk ? prod : walk;
 }
 
 // l tiles per wave of the fix-up (4 waves share the (L + 15) / 16 tiles)
@@ -49,347 +54,299 @@ bool shfused_supported(int M, int L) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Jacobian formation shared by the two chunk products.  LDS: w2t [MP][LQ] = (W2 diag(p))^T
-// (row i, column l) and w1s [MP][LQ] = W1 (row j, column l), LQ = LP + 4 (the rows read by a
-// 16-lane group fall on different banks).
-// jt tile (I, Jt) of step nt: lane (g, c) element r = J^T[16I + 4g + r][16Jt + c]
-//   = J[16Jt + c][16I + 4g + r]   (J = W1 diag(m) W2 diag(p), without the diagonal),
-// which is the A fragment of row tile Jt, k-step 4I + r of a product J X (lane (g, c) of an A
-// fragment holds J[16I' + c][16j + 4g + q]).
+// chunk products on the fp16 matrix cores with split operands (split16.h).  Per step
+//   J^T tile (I, Jt) = sum_l (W2 diag p)[l, 16 I + .] m_l W1[16 Jt + ., l]
+// from the two weights, split once per block into LDS (hi and lo of eight l per lane and tile) with
+// W1's half cleared where the unit is off; a block of 32 units takes the lane's eight mask bits
+// through a 256-entry table of half-word masks.  A lane of the accumulator holds J[16 Jt + c][16 I +
+// 4 g + r], which is slot (I & 1, r) of k block I >> 1 of an A operand with the k slots numbered as in
+// k_chunk_product_split, so with the diagonal added, scaled and split again it composes at once,
+// P <- J~ P.  A wave owns one chunk and forms the Jacobians of NT consecutive steps together (one
+// read of the weights from LDS for all of them).
+//
+// Scales: the weights' largest entries to [2^9, 2^10); J~ by 2^sj from the bound
+// R = gamma (|W1|_inf |W2 diag p|_inf + max |A p|) >= its absolute row sums, R 2^sj in [2^13, 2^14);
+// P's columns as in k_chunk_product_split.
+//
+// A chunk whose masks are those of the pass before (masks_prev) and whose damping is that of its
+// stored product keeps it; masks_prev null: every product is formed.
+// forward: P_c = J~_{s1-1} ... J~_{s0};  REV (the adjoint): J~_{hi-1} ... J~_{s0+1}, hi = min(s1 + 1, T).
+//
+// M = 32, L = 256: a step is 108 matrix instructions (0.86 us on a SIMD) and about 200 vector ones,
+// where fp32 matrix instructions took 320 (4.4 us); 8 x 65536 steps: 0.71 ms for every chunk of the
+// adjoint against 2.6 ms.
 // ---------------------------------------------------------------------------------------
-template <int MP>
-__device__ __forceinline__ void shf_stage_weights(const ShArgs &a, float *w2t, float *w1s, int LQ) {
-    const int M = a.M, L = a.L, N = a.N;
-    for (int e = threadIdx.x; e < MP * LQ; e += 256) {
-        const int i = e / LQ, l = e % LQ;
-        const bool ok = i < M && l < L;
-        w2t[e] = ok ? a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha) : 0.f;
-        w1s[e] = ok ? a.W1[(size_t)i * L + l] : 0.f;
+template <int MP, int NT, bool REV, bool WU>
+__device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t *__restrict__ masks,
+                                                 const uint32_t *__restrict__ masks_prev,
+                                                 const float *__restrict__ gamma, float *__restrict__ pgam,
+                                                 float *__restrict__ Pout, const int *__restrict__ active, int C,
+                                                 int ncs, int LB, int block, v4u *smem4) {
+    constexpr int NI = MP / 16, KK = (MP + 31) / 32, NV = (NT * 16 + 63) / 64;
+    v4u *wa = smem4;                       // [LB][NI][hi, lo][64]  (W2 diag p)^T
+    v4u *wb = smem4 + LB * NI * 128;       // [LB][NI][hi, lo][64]  W1
+    v4u *lut = smem4 + 2 * LB * NI * 128;  // [256] half-word masks of eight bits
+    float (*red)[5] = reinterpret_cast<float (*)[5]>(lut + 256);   // [4][5]
+    const int M = a.M, L = a.L, T = a.T, N = a.N, LW = (L + 31) / 32;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
+    const int id = block * 4 + wv;
+    const bool exists = id < a.B * ncs;
+    const int b = exists ? id / ncs : 0, s0 = exists ? (id % ncs) * C : 0;
+    const int s1 = min(s0 + C, T);
+    const float gm = gamma ? gamma[b] : 1.f;
+    bool todo = exists && (!active || active[b]);
+    if (!REV && masks_prev && todo && pgam[id] == gm) {
+        const size_t w0 = ((size_t)b * T + s0) * LW;
+        const int nw = (s1 - s0) * LW;
+        uint32_t d = 0u;
+        for (int e = lane; e < nw; e += 64) d |= masks[w0 + e] ^ masks_prev[w0 + e];
+        todo = __builtin_amdgcn_ballot_w64(d != 0u) != 0ull;
     }
-}
+    if (!__syncthreads_or(todo)) return;
+    const float m1 = opaque_m1();
 
-// jt of the steps whose mask rows are row_first + nt, nt < nvalid (wave-uniform, <= NT)
-template <int MP, int NT>
-__device__ __forceinline__ void shf_form(const float *w2t, const float *w1s, int LQ, int njl,
-                                         const uint32_t *__restrict__ masks, int LW, size_t row_first, int nvalid,
-                                         int g, int c, v4f (&jt)[NT][MP / 16][MP / 16]) {
-    constexpr int NI = MP / 16;
+    // largest entries and the row-sum bounds of W1 and W2 diag p, max |A p|
+    {
+        constexpr int TR = 256 / MP;   // threads per row of W1
+        float x1 = 0.f, x2 = 0.f, n1 = 0.f, n2 = 0.f, da = 0.f;
+        const int i = tid / TR;
+        for (int l = tid % TR; l < L; l += TR) {
+            const float w = i < M ? fabsf(a.W1[(size_t)i * L + l]) : 0.f;
+            x1 = fmaxf(x1, w);
+            n1 += w;
+        }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+        for (int off = 1; off < TR; off <<= 1) n1 += __shfl_xor(n1, off, 64);
+        for (int l = tid; l < L; l += 256) {
+            float n = 0.f;
+            for (int j = 0; j < M; ++j) {
+                const float w = fabsf(a.W2[(size_t)l * M + j] * pf_at(j, N, a.alpha));
+                x2 = fmaxf(x2, w);
+                n += w;
+            }
+            n2 = fmaxf(n2, n);
+        }
+        if (tid < M) da = fabsf(a.A[tid] * pf_at(tid, N, a.alpha));
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            x1 = fmaxf(x1, __shfl_xor(x1, off, 64));
+            x2 = fmaxf(x2, __shfl_xor(x2, off, 64));
+            n1 = fmaxf(n1, __shfl_xor(n1, off, 64));
+            n2 = fmaxf(n2, __shfl_xor(n2, off, 64));
+            da = fmaxf(da, __shfl_xor(da, off, 64));
+        }
+        if (lane == 0) {
+            red[wv][0] = x1;
+            red[wv][1] = x2;
+            red[wv][2] = n1;
+            red[wv][3] = n2;
+            red[wv][4] = da;
+        }
+    }
+    // table: half-word k of entry e is all ones where bit k of e is set
+    {
+        v4u t;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            t[k] = ((tid >> (2 * k)) & 1 ? 0xffffu : 0u) | ((tid >> (2 * k + 1)) & 1 ? 0xffff0000u : 0u);
+        lut[tid] = t;
+    }
+    __syncthreads();
+    float mx[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) mx[k] = fmaxf(fmaxf(red[0][k], red[1][k]), fmaxf(red[2][k], red[3][k]));
+    const int sc1 = min(9 - exp_of(mx[0]), 100), sc2 = min(9 - exp_of(mx[1]), 100);
+    for (int e = tid; e < LB * NI * 64; e += 256) {
+        const int ln = e & 63, I = (e >> 6) % NI, kb = (e >> 6) / NI;
+        const int i = 16 * I + (ln & 15), l0 = 32 * kb + 8 * (ln >> 4);
+        v4u ah, al, bh, bl;
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+            float w2[2], w1[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int l = l0 + 2 * e2 + k;
+                const bool ok = i < M && l < L;
+                w2[k] = ok ? ldexpf(a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha), sc2) : 0.f;
+                w1[k] = ok ? ldexpf(a.W1[(size_t)i * L + l], sc1) : 0.f;
+            }
+            uint32_t h, lo;
+            split_pair(w2[0], w2[1], m1, h, lo);
+            ah[e2] = h;
+            al[e2] = lo;
+            split_pair(w1[0], w1[1], m1, h, lo);
+            bh[e2] = h;
+            bl[e2] = lo;
+        }
+        const int o = (kb * NI + I) * 128 + ln;
+        wa[o] = ah;
+        wa[o + 64] = al;
+        wb[o] = bh;
+        wb[o + 64] = bl;
+    }
+    __syncthreads();
+    if (!todo) return;
+
+    const float R = fabsf(gm) * fmaf(mx[2], mx[3], mx[4]);
+    const int sj = __builtin_amdgcn_readfirstlane(min(13 - exp_of(R), 100));
+    const int qe = __builtin_amdgcn_readfirstlane(max(exp_of(R) + 1, -20));
+    const int kr = qe <= 3 ? 4 : qe <= 6 ? 2 : 1;
+    const float fplain = pow2i(max(-(sj + qe), -126));
+    const float fj = ldexpf(gm, sj - sc1 - sc2);
+    float dgr[NI][4];   // the diagonal of row 16 Jt + c, in the lane and slot that hold it
+#pragma unroll
+    for (int Jt = 0; Jt < NI; ++Jt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * Jt + c;
+            dgr[Jt][r] = (c == 4 * g + r && row < M) ? ldexpf(gm * (a.A[row] * pf_at(row, N, a.alpha)), sj) : 0.f;
+        }
+    v4f acc[NI][NI];
+    int E[NI];
+#pragma unroll
+    for (int tt = 0; tt < NI; ++tt) {
+        E[tt] = 0;
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
-            for (int Jt = 0; Jt < NI; ++Jt) jt[nt][I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
-    // mask words: one per pair of 16-unit k tiles, loaded a pair ahead
-    uint32_t mw[NT];
+            for (int r = 0; r < 4; ++r) acc[I][tt][r] = (16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
+    }
+    const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
+    const int len = __builtin_amdgcn_readfirstlane(hi - lo);
+    // mask words of NT steps, one per lane, the next NT steps' in flight
+    const uint32_t *mrow = masks + ((size_t)b * T + lo) * LW;
+    uint32_t mc[NV], mn[NV];
+    auto fetch = [&](int t0) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) mw[nt] = nt < nvalid ? masks[(row_first + nt) * LW] : 0u;
-    // LDS operands of k tile j, read one tile ahead of their matrix-core instructions
-    float4 av[NI], bv[NI];
-    auto lds_ops = [&](int j, float4 (&ao)[NI], float4 (&bo)[NI]) {
-#pragma unroll
-        for (int I = 0; I < NI; ++I) ao[I] = *reinterpret_cast<const float4 *>(w2t + (16 * I + c) * LQ + 16 * j + 4 * g);
-#pragma unroll
-        for (int Jt = 0; Jt < NI; ++Jt)
-            bo[Jt] = *reinterpret_cast<const float4 *>(w1s + (16 * Jt + c) * LQ + 16 * j + 4 * g);
-    };
-    lds_ops(0, av, bv);
-    for (int jp = 0; jp < njl; jp += 2) {
-        uint32_t mc[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            mc[nt] = mw[nt];
-            const int wn = (jp >> 1) + 1;
-            mw[nt] = (nt < nvalid && wn < LW) ? masks[(row_first + nt) * LW + wn] : 0u;
+        for (int k = 0; k < NV; ++k) {
+            const int e = 64 * k + lane;
+            mn[k] = (e < NT * LW && t0 * LW + e < len * LW) ? mrow[t0 * LW + e] : 0u;
         }
+    };
+    if (len > 0) fetch(0);
+    for (int t0 = 0; t0 < len; t0 += NT) {
+        const int nv = min(NT, len - t0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int j = jp + h;
-            if (j >= njl) break;
-            float4 an[NI], bn[NI];
-            lds_ops(j + 1 < njl ? j + 1 : j, an, bn);
-            const int sh = 16 * h + 4 * g;
+        for (int k = 0; k < NV; ++k) mc[k] = mn[k];
+        fetch(t0 + NT);
+        v4f jt[NT][NI][NI];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int I = 0; I < NI; ++I)
+#pragma unroll
+                for (int Jt = 0; Jt < NI; ++Jt) jt[nt][I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int kb = 0; kb < LB; ++kb) {
+            v4u oa[NI][2], ob[NI][2];
+#pragma unroll
+            for (int I = 0; I < NI; ++I)
+#pragma unroll
+                for (int hl = 0; hl < 2; ++hl) {
+                    oa[I][hl] = wa[((kb * NI + I) * 2 + hl) * 64 + lane];
+                    ob[I][hl] = wb[((kb * NI + I) * 2 + hl) * 64 + lane];
+                }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                if (nt >= nvalid) continue;
-                const uint32_t w = mc[nt];
+                const int e = nt * LW + kb;   // steps past the chunk have zero masks (and are not composed)
+                uint32_t w;
+                if (NV == 1 || e < 64) w = (uint32_t)__builtin_amdgcn_readlane((int)mc[0], e & 63);
+                else w = (uint32_t)__builtin_amdgcn_readlane((int)mc[NV - 1], e & 63);
+                const v4u pm = lut[(w >> (8 * g)) & 255u];
 #pragma unroll
                 for (int Jt = 0; Jt < NI; ++Jt) {
-                    const float b0 = select_bit(w, sh + 0, bv[Jt].x), b1 = select_bit(w, sh + 1, bv[Jt].y);
-                    const float b2 = select_bit(w, sh + 2, bv[Jt].z), b3 = select_bit(w, sh + 3, bv[Jt].w);
+                    const v4u bh = ob[Jt][0] & pm, bl = ob[Jt][1] & pm;
 #pragma unroll
-                    for (int I = 0; I < NI; ++I) {
-                        v4f t = jt[nt][I][Jt];
-                        t = mfma16x16x4(av[I].x, b0, t);
-                        t = mfma16x16x4(av[I].y, b1, t);
-                        t = mfma16x16x4(av[I].z, b2, t);
-                        t = mfma16x16x4(av[I].w, b3, t);
-                        jt[nt][I][Jt] = t;
+                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][1], bh, jt[nt][I][Jt]);
+#pragma unroll
+                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][0], bl, jt[nt][I][Jt]);
+#pragma unroll
+                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][0], bh, jt[nt][I][Jt]);
+                }
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (nt >= nv) break;
+            const int t = t0 + nt;
+            // P to the B operand
+            v4u bh[KK][NI], bl[KK][NI];
+            const bool renorm = (t & (kr - 1)) == 0;
+#pragma unroll
+            for (int tt = 0; tt < NI; ++tt) {
+                float f = fplain;
+                if (renorm) {
+                    float m2 = 0.f;
+#pragma unroll
+                    for (int I = 0; I < NI; ++I)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) m2 = fmaf(acc[I][tt][r], acc[I][tt][r], m2);
+                    const int ph = norm_shift(group_sum(m2));
+                    f = pow2i(ph);
+                    E[tt] -= ph + sj;
+                } else {
+                    E[tt] += qe;
+                }
+#pragma unroll
+                for (int I = 0; I < 2 * KK; ++I)
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2) {
+                        uint32_t ph = 0u, pl = 0u;
+                        if (I < NI) split_pair(acc[I < NI ? I : 0][tt][2 * h2] * f, acc[I < NI ? I : 0][tt][2 * h2 + 1] * f, m1, ph, pl);
+                        bh[I >> 1][tt][2 * (I & 1) + h2] = ph;
+                        bl[I >> 1][tt][2 * (I & 1) + h2] = pl;
                     }
-                }
             }
+            // a latent warm-up step's P_1 drops the observed latents' columns
+            const bool warm = WU && lo + t <= a.tw;
 #pragma unroll
-            for (int I = 0; I < NI; ++I) {
-                av[I] = an[I];
-                bv[I] = bn[I];
+            for (int Jt = 0; Jt < NI; ++Jt) {
+                v4u ah[KK], al[KK];
+#pragma unroll
+                for (int I = 0; I < 2 * KK; ++I)
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2) {
+                        uint32_t ph = 0u, pl = 0u;
+                        if (I < NI) {
+                            const int Ic = I < NI ? I : 0, k = 16 * I + 4 * g + 2 * h2;
+                            float v0 = jt[nt][Ic][Jt][2 * h2], v1 = jt[nt][Ic][Jt][2 * h2 + 1];
+                            v0 = I == Jt ? fmaf(v0, fj, dgr[Jt][2 * h2]) : v0 * fj;
+                            v1 = I == Jt ? fmaf(v1, fj, dgr[Jt][2 * h2 + 1]) : v1 * fj;
+                            if (WU && warm) {
+                                v0 = k < N ? 0.f : v0;
+                                v1 = k + 1 < N ? 0.f : v1;
+                            }
+                            split_pair(v0, v1, m1, ph, pl);
+                        }
+                        ah[I >> 1][2 * (I & 1) + h2] = ph;
+                        al[I >> 1][2 * (I & 1) + h2] = pl;
+                    }
+                v4f s[NI];
+#pragma unroll
+                for (int tt = 0; tt < NI; ++tt) s[tt] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+#pragma unroll
+                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(al[kk], bh[kk][tt], s[tt]);
+#pragma unroll
+                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(ah[kk], bl[kk][tt], s[tt]);
+                }
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(ah[kk], bh[kk][tt], s[tt]);
+#pragma unroll
+                for (int tt = 0; tt < NI; ++tt) acc[Jt][tt] = s[tt];
             }
         }
     }
-}
-
-// A fragments of J~ = gm (J + diag(A p)) from one step's jt: row tile I, k-step s = 4j + q
-// holds J~[16I + c][16j + 4g + q]; dg[I] = A_i p_i of row i = 16I + c
-template <int MP>
-__device__ __forceinline__ void shf_afrag(const v4f (&jt)[MP / 16][MP / 16], const float (&dg)[MP / 16], float gm,
-                                          int g, int c, float (&ac)[MP / 16][MP / 4]) {
-    constexpr int NI = MP / 16;
+    float *P = Pout + (size_t)id * MP * MP;
 #pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v = jt[j][I][q];
-                if (I == j && c == 4 * g + q) v = v + dg[I];
-                ac[I][4 * j + q] = gm * v;
-            }
-}
-
-// a latent warm-up step's P_1 (section "Latent state warm-up"): the observed latents' columns of
-// J~ (k-steps 16 j + 4 g + q < N) dropped from its A fragments
-template <int MP>
-__device__ __forceinline__ void shf_drop_observed(float (&ac)[MP / 16][MP / 4], int N, int g) {
-    constexpr int NI = MP / 16;
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (16 * j + 4 * g + q < N) ac[I][4 * j + q] = 0.f;
-}
-
-// ---------------------------------------------------------------------------------------
-// forward chunk product: per chain the B operand is [P | u] (P's MP/16 column tiles plus one
-// whose column 0 is u), P <- J~_t P and u <- J~_t u + rhs_sign r_t, with P = I and u = 0 at
-// the chunk start (the stored-Jacobian kernel's contract: P and the local solution v per chain).
-// ---------------------------------------------------------------------------------------
-template <int MP, int NT>
-__global__ __launch_bounds__(256) void k_chunk_product_shfused(const ShArgs a, const uint32_t *__restrict__ masks,
-                                                               const float *__restrict__ rhs, float rhs_sign,
-                                                               const float *__restrict__ gamma,
-                                                               float *__restrict__ Pout, float *__restrict__ vout,
-                                                               const int *__restrict__ active, int C, int ncs,
-                                                               int LP) {
-    constexpr int NI = MP / 16, NS = MP / 4, PT = MP / 16;
-    extern __shared__ __align__(16) float smem[];
-    const int M = a.M, L = a.L, T = a.T, N = a.N, LQ = LP + 4;
-    float *w2t = smem;
-    float *w1s = smem + MP * LQ;
-    shf_stage_weights<MP>(a, w2t, w1s, LQ);
-    __syncthreads();
-    const int tid = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const int LW = (L + 31) / 32;
-    const int nchains = a.B * ncs;
-    const int id = blockIdx.x * 4 + wv;
-    const bool exists = id < nchains;
-    const int b = exists ? id / ncs : 0, cc = exists ? id % ncs : 0;
-    const bool ok = exists && (!active || active[b]);
-    const int s0 = cc * C;
-    const int len = __builtin_amdgcn_readfirstlane(ok ? max(min(s0 + C, T) - s0, 0) : 0);
-    const float gm = gamma ? gamma[b] : 1.f;
-    float dg[NI];
-#pragma unroll
-    for (int I = 0; I < NI; ++I) {
-        const int row = 16 * I + c;
-        dg[I] = row < M ? a.A[row] * pf_at(row, N, a.alpha) : 0.f;
-    }
-    v4f acc[PT + 1][NI];
-#pragma unroll
-    for (int tt = 0; tt <= PT; ++tt)
+    for (int tt = 0; tt < NI; ++tt)
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                acc[tt][I][r] = (tt < PT && 16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
-    const size_t row0 = (size_t)b * T + s0;
-    const int njl = LP / 16;
-    for (int t0 = 0; t0 < len; t0 += NT) {
-        const int nv = min(NT, len - t0);
-        // right-hand sides of the NT steps (lanes of column 0), loaded before the formation
-        float rc[NT][NI][4];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + 4 * g + r;
-                    rc[nt][I][r] = (nt < nv && c == 0 && row < M) ? rhs[(row0 + t0 + nt) * M + row] : 0.f;
-                }
-        v4f jt[NT][NI][NI];
-        shf_form<MP, NT>(w2t, w1s, LQ, njl, masks, LW, row0 + t0, nv, g, c, jt);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if (nt >= nv) break;
-            float ac[NI][NS];
-            shf_afrag<MP>(jt[nt], dg, gm, g, c, ac);
-            if (a.tw > 0 && s0 + t0 + nt <= a.tw) shf_drop_observed<MP>(ac, N, g);
-#pragma unroll
-            for (int tt = 0; tt <= PT; ++tt) {
-                float Bop[NS];
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) Bop[4 * j + q] = acc[tt][j][q];
-#pragma unroll
-                for (int I = 0; I < NI; ++I) {
-                    v4f s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int k = 0; k < NS; ++k) s = mfma16x16x4(ac[I][k], Bop[k], s);
-                    acc[tt][I] = s;
-                }
-            }
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[PT][I][r] = fmaf(rhs_sign, rc[nt][I][r], acc[PT][I][r]);
-        }
-    }
-    if (!exists) return;
-    if (len > 0) {
-        float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-        for (int tt = 0; tt < PT; ++tt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = acc[tt][I][r];
-    }
-    if (c == 0) {
-#pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) vout[(size_t)id * MP + 16 * I + 4 * g + r] = acc[PT][I][r];
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// reverse chunk product (adjoint, eq. backward_recursion: y_k = J~_{k+1}^T y_{k+1} + s b_k).
-// Chunk [s0, s1) stores the stored-Jacobian kernel's pair: Q = J~_{hi-1} ... J~_{s0+1}
-// (hi = min(s1 + 1, T); the carry pass applies Q^T) and the local solution from a zero carry,
-//   v = y_{s0} = sum_{k = s0}^{s1 - 1} Q_k^T (s b_k),   Q_k = J~_k ... J~_{s0+1},  Q_{s0} = I,
-// which the forward sweep that builds Q accumulates on the way: at step k first v += Q^T s b_k
-// (each lane adds the products of its rows of a column; the 4 lane groups' sums are added at
-// the end), then Q <- J~_{k+1} Q.  Undamped (the adjoint is taken at the solution).
-// ---------------------------------------------------------------------------------------
-template <int MP, int NT>
-__global__ __launch_bounds__(256) void k_chunk_product_shfused_rev(const ShArgs a, const uint32_t *__restrict__ masks,
-                                                                   const float *__restrict__ rhs, float rhs_sign,
-                                                                   float *__restrict__ Pout, float *__restrict__ vout,
-                                                                   int C, int ncs, int LP) {
-    constexpr int NI = MP / 16, NS = MP / 4, PT = MP / 16;
-    extern __shared__ __align__(16) float smem[];
-    const int M = a.M, L = a.L, T = a.T, N = a.N, LQ = LP + 4;
-    float *w2t = smem;
-    float *w1s = smem + MP * LQ;
-    shf_stage_weights<MP>(a, w2t, w1s, LQ);
-    __syncthreads();
-    const int tid = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const int LW = (L + 31) / 32;
-    const int nchains = a.B * ncs;
-    const int id = blockIdx.x * 4 + wv;
-    const bool exists = id < nchains;
-    const int b = exists ? id / ncs : 0, cc = exists ? id % ncs : 0;
-    const int s0 = cc * C;
-    const int len = __builtin_amdgcn_readfirstlane(exists ? max(min(s0 + C, T) - s0, 0) : 0);
-    float dg[NI];
-#pragma unroll
-    for (int I = 0; I < NI; ++I) {
-        const int row = 16 * I + c;
-        dg[I] = row < M ? a.A[row] * pf_at(row, N, a.alpha) : 0.f;
-    }
-    v4f acc[PT][NI];
-#pragma unroll
-    for (int tt = 0; tt < PT; ++tt)
-#pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[tt][I][r] = (16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
-    float vc[PT];   // this lane group's part of element 16 tt + c of the local solution
-#pragma unroll
-    for (int tt = 0; tt < PT; ++tt) vc[tt] = 0.f;
-    const size_t row0 = (size_t)b * T + s0;
-    const int njl = LP / 16;
-    for (int t0 = 0; t0 < len; t0 += NT) {
-        const int nv = min(NT, len - t0);
-        // J~_{k+1} exists for k + 1 < T
-        const int nj = max(0, min(nv, T - 1 - (s0 + t0)));
-        float bk[NT][NI][4];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + 4 * g + r;
-                    bk[nt][I][r] = (nt < nv && row < M) ? rhs_sign * rhs[(row0 + t0 + nt) * M + row] : 0.f;
-                }
-        v4f jt[NT][NI][NI];
-        shf_form<MP, NT>(w2t, w1s, LQ, njl, masks, LW, row0 + t0 + 1, nj, g, c, jt);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if (nt >= nv) break;
-#pragma unroll
-            for (int tt = 0; tt < PT; ++tt) {
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) vc[tt] = fmaf(acc[tt][I][r], bk[nt][I][r], vc[tt]);
-            }
-            if (nt >= nj) continue;
-            float ac[NI][NS];
-            shf_afrag<MP>(jt[nt], dg, 1.f, g, c, ac);
-            if (a.tw > 0 && s0 + t0 + nt + 1 <= a.tw) shf_drop_observed<MP>(ac, N, g);   // J~_{k+1}
-#pragma unroll
-            for (int tt = 0; tt < PT; ++tt) {
-                float Bop[NS];
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) Bop[4 * j + q] = acc[tt][j][q];
-#pragma unroll
-                for (int I = 0; I < NI; ++I) {
-                    v4f s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int k = 0; k < NS; ++k) s = mfma16x16x4(ac[I][k], Bop[k], s);
-                    acc[tt][I] = s;
-                }
-            }
-        }
-    }
-    if (!exists) return;
-    if (len > 0) {
-        float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-        for (int tt = 0; tt < PT; ++tt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = acc[tt][I][r];
-    }
-    // the lane groups' partial sums of each column
-#pragma unroll
-    for (int tt = 0; tt < PT; ++tt) {
-        vc[tt] += __shfl_xor(vc[tt], 16, 64);
-        vc[tt] += __shfl_xor(vc[tt], 32, 64);
-    }
-    if (g == 0) {
-#pragma unroll
-        for (int tt = 0; tt < PT; ++tt) vout[(size_t)id * MP + 16 * tt + c] = vc[tt];
-    }
+            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = ldexpf(acc[I][tt][r], E[tt]);
+    if (!REV && pgam && lane == 0) pgam[id] = gm;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -403,18 +360,27 @@ __global__ __launch_bounds__(256) void k_chunk_product_shfused_rev(const ShArgs 
 //     u[k] = W1^T[tile lt, :] y,  u *= m,  p2[I] = (W2 diag(p))^T[tile I, wave's tiles] u
 //     next = (p2 + A p y) + s g_k  (no J term when k + 1 = T); y_k written
 // A = the first factor's rows as A fragments, B = y or u in the k-permuted accumulator layout.
+// LOCAL: from y = 0 instead of the carry, the chunk's last y (the local solution) written to
+// outbuf[chain][MP] and nothing else.
 // The waves' contributions (wave 0 adds the diagonal and the right-hand side) are summed in
 // LDS in a fixed order, so every wave holds the same next y.
 // ---------------------------------------------------------------------------------------
-template <int MP, int NLW, bool REV>
-__global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint32_t *__restrict__ masks,
-                                                     const float *__restrict__ rhs, float rhs_sign,
-                                                     const float *__restrict__ gamma,
-                                                     const float *__restrict__ carry_in, float *zbuf, float *outbuf,
-                                                     const int *__restrict__ zsel, uint32_t *__restrict__ chain_bits,
-                                                     const int *__restrict__ active, int C, int ncs, FusedCtl fc) {
+template <int MP>
+struct ShWalkLds {
+    v4f red[2][4][MP / 16][64];
+    uint32_t mx[4][16][2];
+};
+
+template <int MP, int NLW, bool REV, bool LOCAL>
+__device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__restrict__ masks,
+                                           const float *__restrict__ rhs, float rhs_sign,
+                                           const float *__restrict__ gamma, const float *__restrict__ carry_in,
+                                           float *zbuf, float *outbuf, const int *__restrict__ zsel,
+                                           uint32_t *__restrict__ chain_bits, const int *__restrict__ active, int C,
+                                           int ncs, const FusedCtl &fc, int block, ShWalkLds<MP> &sm) {
     constexpr int NI = MP / 16, NS = MP / 4;
-    __shared__ v4f red[2][4][NI][64];
+    auto &red = sm.red;
+    auto &mx = sm.mx;
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4,
               c = lane & 15;
     const int M = a.M, L = a.L, T = a.T, N = a.N;
@@ -443,7 +409,7 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
                     !e ? 0.f : REV ? a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha) : a.W1[(size_t)i * L + l];
             }
     const int nchains = a.B * ncs;
-    const int id = blockIdx.x * 16 + c;
+    const int id = block * 16 + c;
     const bool exists = id < nchains;
     const int b = exists ? id / ncs : 0, cc = exists ? id % ncs : 0;
     const bool ok = exists && (!active || active[b]);
@@ -455,8 +421,8 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
     for (int off = 1; off < 16; off <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
     maxlen = __builtin_amdgcn_readfirstlane(maxlen);
     const float gm = gamma ? gamma[b] : 1.f;
-    const float *zin = REV ? nullptr : cur_iter(zbuf, outbuf, zsel, b);
-    float *zout = REV ? outbuf : next_iter(zbuf, outbuf, zsel, b);
+    const float *zin = REV || LOCAL ? nullptr : cur_iter(zbuf, outbuf, zsel, b);
+    float *zout = REV || LOCAL ? outbuf : next_iter(zbuf, outbuf, zsel, b);
     float dg[NI][4];
     v4f dl[NI];
 #pragma unroll
@@ -465,7 +431,7 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
         for (int r = 0; r < 4; ++r) {
             const int i = 16 * I + 4 * g + r;
             dg[I][r] = i < M ? a.A[i] * pf_at(i, N, a.alpha) : 0.f;
-            dl[I][r] = (ok && i < M) ? carry_in[(size_t)id * MP + i] : 0.f;
+            dl[I][r] = (!LOCAL && ok && i < M) ? carry_in[(size_t)id * MP + i] : 0.f;
         }
     const size_t rowb = (size_t)b * T;
     // row of step t of this chain, and whether its Jacobian exists (reverse: J~_{k+1}, k + 1 < T)
@@ -490,7 +456,7 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
             const int i = 16 * I + 4 * g + wv;
             const bool e = run && i < M;
             rn[I] = e ? rhs[(rowb + k) * M + i] : 0.f;
-            zn[I] = (!REV && e) ? zin[(rowb + k) * M + i] : 0.f;
+            zn[I] = (!REV && !LOCAL && e) ? zin[(rowb + k) * M + i] : 0.f;
         }
     };
     fetch(0);
@@ -564,9 +530,9 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s[r] = s[r] + o[r];
             }
-            dl[I] = s;
+            if (!LOCAL || t < len) dl[I] = s;   // local: past the chunk its last y stays
         }
-        if (t < len) {
+        if (!LOCAL && t < len) {
 #pragma unroll
             for (int I = 0; I < NI; ++I) {
                 const int i = 16 * I + 4 * g + wv;
@@ -586,7 +552,14 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
             }
         }
     }
-    if (REV) return;
+    if (LOCAL && ok) {
+#pragma unroll
+        for (int I = 0; I < NI; ++I) {
+            const v4f d = dl[I];
+            outbuf[(size_t)id * MP + 16 * I + 4 * g + wv] = wv == 0 ? d[0] : wv == 1 ? d[1] : wv == 2 ? d[2] : d[3];
+        }
+    }
+    if (REV || LOCAL) return;
     // per-chain maxima: the lane groups, then the 4 waves (through the LDS of the last step,
     // whose reads are done once every wave has passed this barrier)
 #pragma unroll
@@ -596,7 +569,6 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
         emax = emax > o ? emax : o;
         zmax = zmax > oz ? zmax : oz;
     }
-    __shared__ uint32_t mx[4][16][2];
     if (g == 0) {
         mx[wv][c][0] = emax;
         mx[wv][c][1] = zmax;
@@ -616,7 +588,41 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
     }
     if (!fc.seq) return;
     // fused pass-end control (chains of a sequence that is not running do not arrive)
-    block16_arrive(fc, emax, zmax, ok, blockIdx.x * 16, ncs, lane);
+    block16_arrive(fc, emax, zmax, ok, b, ncs, lane);
+}
+
+template <int MP, int NLW, bool REV>
+__global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint32_t *__restrict__ masks,
+                                                     const float *__restrict__ rhs, float rhs_sign,
+                                                     const float *__restrict__ gamma,
+                                                     const float *__restrict__ carry_in, float *zbuf, float *outbuf,
+                                                     const int *__restrict__ zsel, uint32_t *__restrict__ chain_bits,
+                                                     const int *__restrict__ active, int C, int ncs, FusedCtl fc) {
+    __shared__ ShWalkLds<MP> sm;
+    shjvp_walk<MP, NLW, REV, false>(a, masks, rhs, rhs_sign, gamma, carry_in, zbuf, outbuf, zsel, chain_bits, active, C,
+                                    ncs, fc, blockIdx.x, sm);
+}
+
+// ---------------------------------------------------------------------------------------
+// A chunk's aggregates: the first blocks walk the local solutions (16 chunks each), the others form
+// the chunk products (4 chunks each).  The two need nothing of each other, and on a short sequence
+// neither fills the chip: M = 4, L = 50, 32768 steps take 20 us together and 20 + 15 us one after the
+// other.  M = 32, L = 256, 8 x 65536 steps: 0.66 ms a pass on average (with the products that are
+// kept) against 1.96 ms in fp32.
+// ---------------------------------------------------------------------------------------
+template <int MP, int NT, int NLW, bool REV, bool WU>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_aggregates_sh(
+    const ShArgs a, const uint32_t *__restrict__ masks, const uint32_t *__restrict__ masks_prev,
+    const float *__restrict__ rhs, float rhs_sign, const float *__restrict__ gamma, float *__restrict__ pgam,
+    float *__restrict__ Pout, float *__restrict__ vout, const int *__restrict__ active, int C, int ncs, int LB,
+    int nwalk) {
+    extern __shared__ __align__(16) v4u smem4[];
+    if ((int)blockIdx.x < nwalk)
+        shjvp_walk<MP, NLW, REV, true>(a, masks, rhs, rhs_sign, gamma, nullptr, nullptr, vout, nullptr, nullptr, active, C,
+                                       ncs, FusedCtl{}, blockIdx.x, *reinterpret_cast<ShWalkLds<MP> *>(smem4));
+    else
+        sh_chunk_product<MP, NT, REV, WU>(a, masks, masks_prev, gamma, pgam, Pout, active, C, ncs, LB,
+                                          blockIdx.x - nwalk, smem4);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -828,30 +834,32 @@ int launch_resjac_shmfma(const ShArgs &a, const float *z, const float *zalt, con
     return DEER_OK;
 }
 
-int launch_chunk_product_shfused(bool rev, const ShArgs &a, const uint32_t *masks, const float *rhs,
-                                 float rhs_sign, const float *gamma, float *P, float *v, const int *active, int C,
-                                 int ncs, hipStream_t st) {
+int launch_chunk_aggregates_sh(bool rev, const ShArgs &a, const uint32_t *masks, const uint32_t *masks_prev,
+                               const float *rhs, float rhs_sign, const float *gamma, float *pgam, float *P, float *v,
+                               const int *active, int C, int ncs, hipStream_t st) {
     const int MP = padded_dim(a.M);
     if (!shfused_supported(a.M, a.L) || (rev && (gamma || active))) return DEER_ERR_INVALID_ARG;
-    const int nch = a.B * ncs;
-    const int grid = (nch + 3) / 4;
-    const int LP = shf_LP(a.L);
+    const int nwalk = (a.B * ncs + 15) / 16, grid = nwalk + (a.B * ncs + 3) / 4;
+    const int LB = (a.L + 31) / 32, nlw = shf_nlw(a.L);
     const size_t lds = shfused_product_lds(a.M, a.L);
-    KTimer kt(rev ? "k_chunk_product_shfused_rev" : "k_chunk_product_shfused", st);
-#define CPS(MPV, NTV)                                                                                             \
-    hipLaunchKernelGGL((k_chunk_product_shfused<MPV, NTV>), dim3(grid), dim3(256), lds, st, a, masks, rhs, rhs_sign, \
-                       gamma, P, v, active, C, ncs, LP)
-#define CPR(MPV, NTV)                                                                                            \
-    hipLaunchKernelGGL((k_chunk_product_shfused_rev<MPV, NTV>), dim3(grid), dim3(256), lds, st, a, masks, rhs, \
-                       rhs_sign, P, v, C, ncs, LP)
-    if (rev) {
-        if (MP == 16) CPR(16, 4); else if (MP == 32) CPR(32, 4); else CPR(64, 1);
+    KTimer kt(rev ? "k_chunk_aggregates_sh_rev" : "k_chunk_aggregates_sh", st);
+#define CPS(MPV, NTV, NL, RV, WUV)                                                                                   \
+    hipLaunchKernelGGL((k_chunk_aggregates_sh<MPV, NTV, NL, RV, WUV>), dim3(grid), dim3(256), lds, st, a, masks,        \
+                       masks_prev, rhs, rhs_sign, gamma, pgam, P, v, active, C, ncs, LB, nwalk)
+#define CPW(MPV, NTV, NL, RV) { if (a.tw > 0) CPS(MPV, NTV, NL, RV, true); else CPS(MPV, NTV, NL, RV, false); }
+#define CPR(MPV, NTV, NL) { if (rev) CPW(MPV, NTV, NL, true) else CPW(MPV, NTV, NL, false) }
+    // shfused_supported bounds NLW * MP / 2 (the walk's A fragments per lane) by 64
+    if (MP == 16) {
+        if (nlw == 1) CPR(16, 8, 1) else if (nlw == 2) CPR(16, 8, 2) else if (nlw == 4) CPR(16, 8, 4) else CPR(16, 8, 8)
+    } else if (MP == 32) {
+        if (nlw == 1) CPR(32, 4, 1) else if (nlw == 2) CPR(32, 4, 2) else CPR(32, 4, 4)
     } else {
-        if (MP == 16) CPS(16, 4); else if (MP == 32) CPS(32, 4); else CPS(64, 1);
+        if (nlw == 1) CPR(64, 1, 1) else CPR(64, 1, 2)
     }
 #undef CPR
+#undef CPW
 #undef CPS
-    DEER_LAUNCH_CHECK("k_chunk_product_shfused");
+    DEER_LAUNCH_CHECK("k_chunk_aggregates_sh");
     return DEER_OK;
 }
 
@@ -865,22 +873,19 @@ int launch_fixup_shjvp(bool rev, const ShArgs &a, const uint32_t *masks, const f
     const int grid = (nch + 15) / 16;
     const int nlw = shf_nlw(a.L);
     KTimer kt(rev ? "k_fixup_shjvp_rev" : "k_fixup_shjvp", st);
-#define FXJ(MPV, NL, RV)                                                                                         \
-    hipLaunchKernelGGL((k_fixup_shjvp<MPV, NL, RV>), dim3(grid), dim3(256), 0, st, a, masks, rhs, rhs_sign, gamma, \
+#define FXL(MPV, NL, RV)                                                                                             \
+    hipLaunchKernelGGL((k_fixup_shjvp<MPV, NL, RV>), dim3(grid), dim3(256), 0, st, a, masks, rhs, rhs_sign, gamma,     \
                        carry_in, z, out, zsel, chain_bits, active, C, ncs, fcv)
-    // shfused_supported bounds NLW * MP / 2 (the A fragments per lane) by 64
-#define FXJ_ALL(RV)                                                                                                  \
-    if (MP == 16) {                                                                                                  \
-        if (nlw == 1) FXJ(16, 1, RV); else if (nlw == 2) FXJ(16, 2, RV); else if (nlw == 4) FXJ(16, 4, RV);          \
-        else FXJ(16, 8, RV);                                                                                         \
-    } else if (MP == 32) {                                                                                           \
-        if (nlw == 1) FXJ(32, 1, RV); else if (nlw == 2) FXJ(32, 2, RV); else FXJ(32, 4, RV);                        \
-    } else {                                                                                                         \
-        if (nlw == 1) FXJ(64, 1, RV); else FXJ(64, 2, RV);                                                           \
+#define FXJ(MPV, NL) { if (rev) FXL(MPV, NL, true); else FXL(MPV, NL, false); }
+    if (MP == 16) {
+        if (nlw == 1) FXJ(16, 1) else if (nlw == 2) FXJ(16, 2) else if (nlw == 4) FXJ(16, 4) else FXJ(16, 8)
+    } else if (MP == 32) {
+        if (nlw == 1) FXJ(32, 1) else if (nlw == 2) FXJ(32, 2) else FXJ(32, 4)
+    } else {
+        if (nlw == 1) FXJ(64, 1) else FXJ(64, 2)
     }
-    if (rev) { FXJ_ALL(true) } else { FXJ_ALL(false) }
-#undef FXJ_ALL
 #undef FXJ
+#undef FXL
     DEER_LAUNCH_CHECK("k_fixup_shjvp");
     return DEER_OK;
 }

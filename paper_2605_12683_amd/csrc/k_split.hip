@@ -245,7 +245,7 @@ __global__ __launch_bounds__(MP * 4) void k_newton_local_plrnn(
 // B operand: column j of P carries its own power of two 2^E[j].  Every step multiplies by 2^-(s+q),
 // 2^q at least the largest absolute row sum of gamma (W + diag A) diag(p), so no entry can grow
 // out of fp16's range whatever the masks are; every KR steps (fewer where 2^q is large) the
-// column is renormalised to [2^13, 2^14) instead.
+// column is brought to a norm in [2^13, 2^14) instead.
 //
 // Per step at M = 64: 96 matrix instructions (0.76 us on a SIMD) and about 280 vector ones
 // (conversion of 4096 entries, masks; issued one after the other, the matrix cores and the vector
@@ -375,12 +375,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         for (int Jt = 0; Jt < NI; ++Jt) {
             float f = fplain;
             if (renorm) {
-                float m = 0.f;
+                float m2 = 0.f;
 #pragma unroll
                 for (int I = 0; I < NI; ++I)
-                    m = absmax3(acc[I][Jt][2], acc[I][Jt][3], absmax3(acc[I][Jt][0], acc[I][Jt][1], m));
-                m = group_max(m);
-                const int ph = min(13 - exp_of(m), 126);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m2 = fmaf(acc[I][Jt][r], acc[I][Jt][r], m2);
+                const int ph = norm_shift(group_sum(m2));
                 f = pow2i(ph);
                 E[Jt] -= ph + sc;
             } else {

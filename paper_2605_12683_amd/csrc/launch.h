@@ -223,10 +223,13 @@ size_t shfused_product_lds(int M, int L);
 int launch_resjac_shmfma(const ShArgs &a, const float *z, const float *zalt, const int *zsel, float *r,
                          uint32_t *masks, const int *active, hipStream_t st, uint32_t *mark = nullptr,
                          uint32_t pass_no = 0u);
-// rev: the adjoint's reverse recursion (gamma and active must be null; the fix-up writes y to out)
-int launch_chunk_product_shfused(bool rev, const ShArgs &a, const uint32_t *masks, const float *rhs,
-                                 float rhs_sign, const float *gamma, float *P, float *v, const int *active, int C,
-                                 int ncs, hipStream_t st);
+// chunk products P and local solutions v (rhs_sign * rhs on the right-hand side).
+// rev: the adjoint's reverse recursion (gamma and active must be null; the fix-up writes y to out).
+// masks_prev (null: none): the masks of the pass before; with pgam[chunk], the damping of each chunk's
+// stored product (NaN: none), the products that would come out the same are kept
+int launch_chunk_aggregates_sh(bool rev, const ShArgs &a, const uint32_t *masks, const uint32_t *masks_prev,
+                               const float *rhs, float rhs_sign, const float *gamma, float *pgam, float *P, float *v,
+                               const int *active, int C, int ncs, hipStream_t st);
 // fc (forward, adaptive loop only): the fix-up takes the pass-end control itself (no chain_bits)
 int launch_fixup_shjvp(bool rev, const ShArgs &a, const uint32_t *masks, const float *rhs, float rhs_sign,
                        const float *gamma, const float *carry_in, float *z, float *out, const int *zsel,

@@ -70,31 +70,24 @@ __device__ __forceinline__ void seq_arrive(const FusedCtl &fc, int b, int cnt, i
     __hip_atomic_store(blk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Arrival of the 16 chains chain0 .. chain0 + 15 from lanes 0..15 of one wave (emax, zmax: lane
-// c's chain; ok: it runs): lane 0 gathers the maxima and arrives once per sequence.
-__device__ __forceinline__ void block16_arrive(const FusedCtl &fc, uint32_t emax, uint32_t zmax, bool ok, int chain0,
-                                               int ncs, int lane) {
-    uint32_t em[16], zm[16];
-    bool okc[16];
+// Arrival of a block's 16 chains from one wave: lane c < 16 holds its chain's maxima, sequence b and
+// whether it runs.  One arrival per sequence (usually all chains are of one), by lane 0.
+__device__ __forceinline__ void block16_arrive(const FusedCtl &fc, uint32_t emax, uint32_t zmax, bool ok, int b, int ncs,
+                                               int lane) {
+    uint64_t left = __builtin_amdgcn_ballot_w64(ok && lane < 16);
+    while (left) {
+        const int bn = __builtin_amdgcn_readlane(b, (int)__builtin_ctzll(left));
+        const bool in = ok && lane < 16 && b == bn;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+        uint32_t E = in ? emax : 0u, Z = in ? zmax : 0u;
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-        em[n] = (uint32_t)__shfl((int)emax, n, 64);
-        zm[n] = (uint32_t)__shfl((int)zmax, n, 64);
-        okc[n] = __shfl((int)ok, n, 64) != 0;
-    }
-    if (lane != 0) return;
-    for (int n = 0; n < 16; ++n) {
-        if (!okc[n]) continue;
-        const int bn = (chain0 + n) / ncs;
-        if (n > 0 && okc[n - 1] && (chain0 + n - 1) / ncs == bn) continue;   // counted with its first chain
-        uint32_t E = 0u, Z = 0u;
-        int cnt = 0;
-        for (int m2 = n; m2 < 16 && okc[m2] && (chain0 + m2) / ncs == bn; ++m2) {
-            E = E > em[m2] ? E : em[m2];
-            Z = Z > zm[m2] ? Z : zm[m2];
-            ++cnt;
+        for (int off = 8; off > 0; off >>= 1) {
+            const uint32_t e = (uint32_t)__shfl_xor((int)E, off, 64), z = (uint32_t)__shfl_xor((int)Z, off, 64);
+            E = E > e ? E : e;
+            Z = Z > z ? Z : z;
         }
-        seq_arrive(fc, bn, cnt, ncs, E, Z);
+        if (lane == 0) seq_arrive(fc, bn, (int)__builtin_popcountll(m), ncs, E, Z);
+        left &= ~m;
     }
 }
 

@@ -47,23 +47,20 @@ __device__ __forceinline__ void split_pair(float x0, float x1, float m1, uint32_
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
-// max over the four lane groups (lanes c, c + 16, c + 32, c + 48) of a non-negative value
-__device__ __forceinline__ float group_max(float v) {
+// sum over the four lane groups (lanes c, c + 16, c + 32, c + 48)
+__device__ __forceinline__ float group_sum(float v) {
     auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
     auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
-}
-
-// max(|a|, |b|, m) in one instruction
-__device__ __forceinline__ float absmax3(float a, float b, float m) {
-    float r;
-    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(m));
-    return r;
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
 // exponent of a non-negative float (0 for zero and subnormals read as -127)
 __device__ __forceinline__ int exp_of(float v) { return (int)(__float_as_uint(v) >> 23) - 127; }
+// exponent of the power of two that brings a column with the sum of squares m2 to a 2-norm in
+// [2^13, 2^14) (its largest entry then is below 2^14 and no less than 2^-3 of that at 64 rows); a
+// column whose squares vanish takes 2^77
+__device__ __forceinline__ int norm_shift(float m2) { return 13 - (exp_of(m2) >> 1); }
 __device__ __forceinline__ float pow2i(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }   // -126 <= e <= 127
 
 }  // namespace deer

@@ -147,3 +147,69 @@ def test_unaligned_rows(M):
         a = D.deer_adjoint(m, x, res[0]["z"], 0.2, M, g=gg)
         b = D.deer_adjoint(m, off(x), off(res[0]["z"]), 0.2, M, g=None if gg is None else off(gg))
         assert torch.equal(a["lam"], b["lam"]) and all(torch.equal(a["grads"][k], b["grads"][k]) for k in a["grads"])
+
+
+def _sh(M, L, N, B, T, seed, w_norm=0.3):
+    return W.random_shplrnn_case(M, L, N, B, T, 0.2, seed, w_norm=w_norm, a_range=(0.3, 0.6))
+
+
+# shallow model: widths and hidden counts at the edges of the tiles and of the 32-unit blocks (50 and
+# 33 end inside one, 448 is about the largest), chunks shorter and longer than the steps formed together
+@pytest.mark.parametrize("M,L,N,B,T,chunk,T_w", [
+    (4, 50, 3, 2, 70, 9, 0), (16, 33, 5, 3, 64, 8, 20), (16, 448, 16, 1, 40, 16, 0), (17, 31, 3, 2, 33, 5, 0),
+    (32, 256, 32, 2, 61, 20, 0), (20, 64, 8, 5, 50, 17, 49), (33, 128, 10, 2, 45, 10, 0), (64, 16, 64, 1, 90, 30, 11),
+    (64, 128, 3, 2, 2, 1, 0), (5, 1, 2, 2, 30, 7, 0)])
+def test_shallow_iterates_and_adjoint(M, L, N, B, T, chunk, T_w):
+    os.environ["DEER_CHUNK"] = str(chunk)
+    c = _sh(M, L, N, B, T, 6600 + M + L)
+    m = oracle_model(c)
+    rng = np.random.default_rng(M)
+    z0 = rng.standard_normal((B, M)).astype(np.float32)
+    say("split shallow", M, L, N, B, T, chunk, T_w)
+    for k in (1, 3):
+        res = D.deer_solve(m, c.x, 0.2, N, fixed_iters=k, z0=z0, T_w=T_w)
+        ref = O.newton(m, c.x, 0.2, N, fixed_iters=k, z0=z0, T_w=T_w)
+        assert rel_inf(res["z"].cpu().numpy(), ref["z"]) < TOL
+    z32 = O.rollout(m, c.x, 0.2, N, z0=z0, T_w=T_w).astype(np.float32)
+    g = rng.standard_normal(z32.shape).astype(np.float32)
+    out = D.deer_adjoint(m, c.x, z32, 0.2, N, z0=z0, g=g, T_w=T_w)
+    lam = O.adjoint(m, c.x, z32, 0.2, N, z0=z0, g=g, mask_precision="float32", T_w=T_w)
+    assert rel_inf(out["lam"].cpu().numpy(), lam) < TOL
+
+
+@pytest.mark.parametrize("M,L", [(6, 40), (32, 100), (64, 64)])
+@pytest.mark.parametrize("kind", ["large", "tiny", "rows", "zero"])
+def test_shallow_scales(M, L, kind):
+    os.environ["DEER_CHUNK"] = "12"
+    c = _sh(M, L, M, 2, 60, 6700 + M)
+    p = {k: v.copy() for k, v in c.params.items()}
+    if kind == "large":
+        p["W1"] *= 64.0
+    elif kind == "tiny":
+        p["W1"] *= 1e-6
+        p["A"] *= 1e-3
+    elif kind == "rows":
+        p["W1"] *= (2.0 ** -np.linspace(0, 18, M)).astype(np.float32)[:, None]
+        p["W2"] *= (2.0 ** -np.linspace(0, 12, L)).astype(np.float32)[:, None]
+    else:
+        p["W1"] *= 0.0
+        p["W2"] *= 0.0
+        p["A"] *= 0.0
+    m = {"kind": "shplrnn", **p}
+    say("split shallow scales", M, L, kind)
+    res = D.deer_solve(m, c.x, 0.2, M, fixed_iters=1, init="zero")
+    ref = O.newton(m, c.x, 0.2, M, fixed_iters=1, init="zero")
+    assert rel_inf(res["z"].cpu().numpy(), ref["z"]) < TOL
+
+
+@pytest.mark.parametrize("M,L,bound", [(5, 50, 0.0), (32, 64, 0.05), (64, 40, 0.05)])
+def test_shallow_kept_products(M, L, bound):
+    os.environ["DEER_CHUNK"] = "16"
+    c = _sh(M, L, M, 3, 300, 6800 + M)
+    m = oracle_model(c)
+    ref = O.rollout(m, c.x, 0.2, M)
+    say("split shallow kept products", M, L, bound)
+    res = D.deer_solve(m, c.x, 0.2, M, tol=1e-5, max_iter=5000, step_bound=bound)
+    assert res["status"] == 0 and rel_inf(res["z"].cpu().numpy(), ref) < TOL
+    more = D.deer_solve(m, c.x, 0.2, M, fixed_iters=8)
+    assert rel_inf(more["z"].cpu().numpy(), ref) < 1e-5
