@@ -8,7 +8,7 @@
 //                      per chunk of C steps: P_c = J~_e ... J~_s on the matrix cores (fp32
 //                      MFMA) and v_c = the chunk's local solution from a zero carry (VALU);
 //                      M > 16: k_split.hip
-//   k_carry            carries across chunks, one wave per sequence
+//   k_carry16, k_carry_walk16  carries across chunks (M > 16: k_carry.hip)
 //   k_fixup_fwd        Delta_t = J~_t Delta_{t-1} - r_t from the carry, z += Delta, max|Delta|
 //   k_fixup_rev        lam_{t-1} = J~_t^T lam_t + g_{t-1} from the carry, fused parameter-
 //                      gradient partial sums (gradients appendix); M > 16: k_split.hip
@@ -1409,148 +1409,13 @@ __global__ __launch_bounds__(512) void k_newton_pass16(
 }
 
 // ---------------------------------------------------------------------------------------
-// carries across chunks
-//   forward: carry_in[c] = y_end(c-1),  y_end(c) = P_c y_end(c-1) + v_c
-//   reverse: carry_in[c] = lam_{s1(c)}, lam_{s0(c)} = P_c^T lam_{s1(c)} + v_c
-// In processing order k (k = c forward, c = ncs - 1 - k reverse) both read
-//   carry_in[c(k)] = cur_k,  cur_{k+1} = A_k cur_k + v_{c(k)},  A_k = P_c or P_c^T.
-// Long chunk sequences use two levels: groups of G consecutive k are composed into one map
-// (Q_j, u_j) (k_carry_group, all groups in parallel), the group carries are walked serially
-// (k_carry over the groups), and every group re-walks its chunks from its carry (k_carry with
-// a start vector).  Serial depth G + ncs / G + G instead of ncs.
-// ---------------------------------------------------------------------------------------
-template <int MP, bool REV>
-__global__ __launch_bounds__(MP) void k_carry(const float *__restrict__ P, const float *__restrict__ v,
-                                              float *__restrict__ carry_in, const int *__restrict__ active,
-                                              uint32_t *__restrict__ norm_bits, int B, int ncs, int G,
-                                              const float *__restrict__ start) {
-    __shared__ __align__(16) float cs[MP];
-    const int ngroups = (ncs + G - 1) / G;
-    const int b = blockIdx.x / ngroups, j = blockIdx.x % ngroups, i = threadIdx.x;
-    if (norm_bits && j == 0 && i == 0) {   // [0, B): max|Delta|, [B, 2B): max|z| of the next fix-up
-        norm_bits[b] = 0u;
-        norm_bits[B + b] = 0u;
-    }
-    if (active && !active[b]) return;
-    const int k0 = j * G, k1 = min(k0 + G, ncs);
-    float cur = start ? start[((size_t)b * ngroups + j) * MP + i] : 0.f;
-    float pr[MP], pn[MP];
-    auto load = [&](int step, float *dst) {
-        const int cc = REV ? ncs - 1 - step : step;
-        const float *Pc = P + ((size_t)b * ncs + cc) * MP * MP;
-        if (!REV) {
-            const float4 *r4 = reinterpret_cast<const float4 *>(Pc + i * MP);
-#pragma unroll
-            for (int q = 0; q < MP / 4; ++q) {
-                float4 t = r4[q];
-                dst[4 * q] = t.x; dst[4 * q + 1] = t.y; dst[4 * q + 2] = t.z; dst[4 * q + 3] = t.w;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < MP; ++k) dst[k] = Pc[k * MP + i];
-        }
-    };
-    load(k0, pr);
-    for (int step = k0; step < k1; ++step) {
-        const int cc = REV ? ncs - 1 - step : step;
-        const size_t id = (size_t)b * ncs + cc;
-        if (step + 1 < k1) load(step + 1, pn);
-        const float vv = v[id * MP + i];
-        carry_in[id * MP + i] = cur;
-        cs[i] = cur;
-        lds_barrier();
-        float a0 = vv, a1 = 0.f;
-#pragma unroll
-        for (int k = 0; k < MP; k += 2) {
-            a0 = fmaf(pr[k], cs[k], a0);
-            a1 = fmaf(pr[k + 1], cs[k + 1], a1);
-        }
-        lds_barrier();
-        cur = a0 + a1;
-#pragma unroll
-        for (int k = 0; k < MP; ++k) pr[k] = pn[k];
-    }
-}
-
-// group maps in processing order: Q_j = A_{k1-1} ... A_{k0}, u_j = the group's walk from 0
-template <int MP, bool REV>
-__global__ __launch_bounds__(256) void k_carry_group(const float *__restrict__ P, const float *__restrict__ v,
-                                                     float *__restrict__ gq, float *__restrict__ gu,
-                                                     const int *__restrict__ active, int ncs, int G) {
-    constexpr int E = (MP * MP + 255) / 256;
-    __shared__ float Q[MP][MP + 1], Am[MP][MP + 1], u[MP], vv[MP];
-    const int ngroups = (ncs + G - 1) / G;
-    const int b = blockIdx.x / ngroups, j = blockIdx.x % ngroups, tid = threadIdx.x;
-    if (active && !active[b]) return;
-    for (int e = tid; e < MP * MP; e += 256) Q[e / MP][e % MP] = (e / MP == e % MP) ? 1.f : 0.f;
-    if (tid < MP) u[tid] = 0.f;
-    const int k0 = j * G, k1 = min(k0 + G, ncs);
-    // the next step's matrix and vector are loaded while this step is composed
-    float pn[E], vn = 0.f;
-    auto fetch = [&](int step) {
-        const int cc = REV ? ncs - 1 - step : step;
-        const float *Pc = P + ((size_t)b * ncs + cc) * MP * MP;
-#pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const int e = tid + 256 * t;
-            pn[t] = (step < k1 && e < MP * MP) ? Pc[e] : 0.f;
-        }
-        vn = (step < k1 && tid < MP) ? v[((size_t)b * ncs + cc) * MP + tid] : 0.f;
-    };
-    fetch(k0);
-    for (int step = k0; step < k1; ++step) {
-#pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const int e = tid + 256 * t;
-            if (e < MP * MP) {
-                const int r = e / MP, col = e % MP;
-                if (REV) Am[col][r] = pn[t];
-                else Am[r][col] = pn[t];
-            }
-        }
-        if (tid < MP) vv[tid] = vn;
-        fetch(step + 1);
-        lds_barrier();
-        float qn[E];
-#pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const int e = tid + 256 * t;
-            float acc = 0.f;
-            if (e < MP * MP) {
-                const int r = e / MP, col = e % MP;
-#pragma unroll(MP <= 32 ? MP : 8)
-                for (int k = 0; k < MP; ++k) acc = fmaf(Am[r][k], Q[k][col], acc);
-            }
-            qn[t] = acc;
-        }
-        float un = 0.f;
-        if (tid < MP) {
-            un = vv[tid];
-#pragma unroll
-            for (int k = 0; k < MP; ++k) un = fmaf(Am[tid][k], u[k], un);
-        }
-        lds_barrier();
-#pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const int e = tid + 256 * t;
-            if (e < MP * MP) Q[e / MP][e % MP] = qn[t];
-        }
-        if (tid < MP) u[tid] = un;
-        lds_barrier();
-    }
-    float *q = gq + ((size_t)b * ngroups + j) * MP * MP;
-    for (int e = tid; e < MP * MP; e += 256) q[e] = Q[e / MP][e % MP];
-    if (tid < MP) gu[((size_t)b * ngroups + j) * MP + tid] = u[tid];
-}
-
-// ---------------------------------------------------------------------------------------
 // M <= 16 carries on the matrix cores, one wave per walk.  A map A_k (P_c or its transpose)
 // is the A operand of four 16x16x4 MFMAs; the vector being walked is column 0 of the B
 // operand, whose accumulator layout is again the next step's B operand, so a step is four
 // dependent MFMAs and no LDS.  The maps of the next PF steps are in flight while a step runs.
 // ---------------------------------------------------------------------------------------
 
-// walk of the vector: carry_in[c(k)] = cur_k, cur_{k+1} = A_k cur_k + v_{c(k)} (see k_carry)
+// walk of the vector: carry_in[c(k)] = cur_k, cur_{k+1} = A_k cur_k + v_{c(k)} (the recursion at the top of k_carry.hip)
 template <bool REV>
 __global__ __launch_bounds__(64) void k_carry16(const float *__restrict__ P, const float *__restrict__ v,
                                                float *__restrict__ carry_in, const int *__restrict__ active,
@@ -2861,57 +2726,32 @@ size_t carry_ws_floats(int MP, int B, int ncs) {
 
 int launch_carry(int MP, bool rev, const float *P, const float *v, float *carry_in, const int *active,
                  uint32_t *norm_bits, int B, int ncs, float *gws, hipStream_t st) {
-    if (MP == 128) {
-        if (norm_bits) return invalid_arg("width-128 carries take no norms");
-        return launch_carry_big(rev, P, v, carry_in, active, B, ncs, gws ? carry_group_size(MP, ncs) : 0, gws, st);
+    const int G = gws ? carry_group_size(MP, ncs) : 0;
+    if (MP != 16) {
+        if (norm_bits) return invalid_arg("carries of widths over 16 take no norms");
+        if (MP == 128) return launch_carry_big(rev, P, v, carry_in, active, B, ncs, G, gws, st);
+        return launch_carry_mid(MP, rev, P, v, carry_in, active, B, ncs, G, gws, st);
     }
     KTimer kt("k_carry", st);
-    const int G = gws ? carry_group_size(MP, ncs) : 0;
-#define CA(MPV, R, PP, VV, CI, NB, NC, GG, ST, GRID) \
-    hipLaunchKernelGGL((k_carry<MPV, R>), dim3(GRID), dim3(MPV), 0, st, PP, VV, CI, active, NB, B, NC, GG, ST)
-#define CG(MPV, R, GRID) \
-    hipLaunchKernelGGL((k_carry_group<MPV, R>), dim3(GRID), dim3(256), 0, st, P, v, gq, gu, active, ncs, G)
     if (!G) {
-        if (MP == 16) {
-            if (rev)
-                hipLaunchKernelGGL(k_carry16<true>, dim3(B), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, ncs, nullptr);
-            else
-                hipLaunchKernelGGL(k_carry16<false>, dim3(B), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, ncs, nullptr);
-        } else if (!rev) {
-            if (MP == 16) CA(16, false, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-            else if (MP == 32) CA(32, false, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-            else CA(64, false, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-        } else {
-            if (MP == 16) CA(16, true, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-            else if (MP == 32) CA(32, true, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-            else CA(64, true, P, v, carry_in, norm_bits, ncs, ncs, nullptr, B);
-        }
+        if (rev)
+            hipLaunchKernelGGL(k_carry16<true>, dim3(B), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, ncs, nullptr);
+        else
+            hipLaunchKernelGGL(k_carry16<false>, dim3(B), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, ncs, nullptr);
     } else {
         const int ng = (ncs + G - 1) / G;
         float *gq = gws;
         float *gu = gq + (size_t)B * ng * MP * MP;
         float *gc = gu + (size_t)B * ng * MP;
         const int grid = B * ng;
-#define CG3(MPV)                                                             \
-    {                                                                        \
-        if (rev) CG(MPV, true, grid); else CG(MPV, false, grid);             \
-        CA(MPV, false, gq, gu, gc, nullptr, ng, ng, nullptr, B);             \
-        if (rev) CA(MPV, true, P, v, carry_in, norm_bits, ncs, G, gc, grid); \
-        else CA(MPV, false, P, v, carry_in, norm_bits, ncs, G, gc, grid);    \
+        if (rev) hipLaunchKernelGGL(k_carry_group16<true>, dim3(grid), dim3(64), 0, st, P, v, gq, gu, active, ncs, G);
+        else hipLaunchKernelGGL(k_carry_group16<false>, dim3(grid), dim3(64), 0, st, P, v, gq, gu, active, ncs, G);
+        hipLaunchKernelGGL(k_carry16<false>, dim3(B), dim3(64), 0, st, gq, gu, gc, active, nullptr, B, ng, ng, nullptr);
+        if (rev)
+            hipLaunchKernelGGL(k_carry16<true>, dim3(grid), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, G, gc);
+        else
+            hipLaunchKernelGGL(k_carry16<false>, dim3(grid), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, G, gc);
     }
-        if (MP == 16) {
-            if (rev) hipLaunchKernelGGL(k_carry_group16<true>, dim3(grid), dim3(64), 0, st, P, v, gq, gu, active, ncs, G);
-            else hipLaunchKernelGGL(k_carry_group16<false>, dim3(grid), dim3(64), 0, st, P, v, gq, gu, active, ncs, G);
-            hipLaunchKernelGGL(k_carry16<false>, dim3(B), dim3(64), 0, st, gq, gu, gc, active, nullptr, B, ng, ng, nullptr);
-            if (rev)
-                hipLaunchKernelGGL(k_carry16<true>, dim3(grid), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, G, gc);
-            else
-                hipLaunchKernelGGL(k_carry16<false>, dim3(grid), dim3(64), 0, st, P, v, carry_in, active, norm_bits, B, ncs, G, gc);
-        } else if (MP == 32) CG3(32) else CG3(64)
-#undef CG3
-    }
-#undef CG
-#undef CA
     DEER_LAUNCH_CHECK("k_carry");
     return DEER_OK;
 }

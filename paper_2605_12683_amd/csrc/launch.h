@@ -76,6 +76,9 @@ int launch_adjoint_plrnn16(const PlrnnArgs &a, const float *g, float seed_scale,
 int launch_carry(int MP, bool rev, const float *P, const float *v, float *carry_in, const int *active,
                  uint32_t *norm_bits, int B, int ncs, float *gws, hipStream_t st);
 size_t carry_ws_floats(int MP, int B, int ncs);
+// widths 32 and 64 (k_carry.hip): groups of G chunks, gws as sized by carry_ws_floats; G = 0: one level
+int launch_carry_mid(int MP, bool rev, const float *P, const float *v, float *carry_in, const int *active, int B, int ncs,
+                     int G, float *gws, hipStream_t st);
 // whether launch_fixup_fwd_plrnn takes the pass-end control (fc) at this width
 bool plrnn_fixup_control(int M);
 int launch_fixup_fwd_plrnn(const PlrnnArgs &a, const uint32_t *masks, const float *r, const float *carry_in,

@@ -213,3 +213,27 @@ def test_shallow_kept_products(M, L, bound):
     assert res["status"] == 0 and rel_inf(res["z"].cpu().numpy(), ref) < TOL
     more = D.deer_solve(m, c.x, 0.2, M, fixed_iters=8)
     assert rel_inf(more["z"].cpu().numpy(), ref) < 1e-5
+
+
+@pytest.mark.parametrize("M", [17, 32, 33, 64])
+@pytest.mark.parametrize("ncs", [1, 2, 5, 95, 96, 97, 129, 530])
+def test_carry_levels(M, ncs):
+    """Carries in one level (up to 95 chunks) and two (groups of 8, 16, 32; a last group of one chunk),
+    both directions, through the bare dense scan in chunks of two steps."""
+    os.environ["DEER_CHUNK"] = "2"
+    T = 2 * ncs - 1
+    rng = np.random.default_rng(M + ncs)
+    J = (rng.standard_normal((2, T, M, M)) * 0.5 / np.sqrt(M)).astype(np.float32)
+    b = rng.standard_normal((2, T, M)).astype(np.float32)
+    say("split carry", M, ncs)
+    for rev in (False, True):
+        y = D.deer_scan(0, J, b, reverse=rev).cpu().numpy()
+        ref = np.empty(b.shape)
+        v = np.zeros((2, M))
+        for t in (range(T - 1, -1, -1) if rev else range(T)):
+            if rev:
+                v = (np.einsum("bji,bj->bi", J[:, t + 1].astype(np.float64), v) if t + 1 < T else 0.0) + b[:, t]
+            else:
+                v = (np.einsum("bij,bj->bi", J[:, t].astype(np.float64), v) if t > 0 else 0.0) + b[:, t]
+            ref[:, t] = v
+        assert rel_inf(y, ref) < 1e-5
