@@ -3,13 +3,12 @@
 // linear solve of every shallow-PLRNN Newton update (scheduled-sampling appendix, the pair
 // (A_t, b_t) and its composition; eq. GTF_DEER_update; eq. backward_recursion).
 //
-//   k_chunk_product_dense   per chunk: P_c = J_e ... J_s on the matrix cores (fp32 MFMA,
-//                           A operand = J_t streamed from HBM, B operand = the accumulator
-//                           itself, as in the vanilla kernel) and the chunk's local solution
-//                           v_c from a zero carry (VALU)
+//   k_chunk_product_dense   per chunk: P_c = J_e ... J_s and the chunk's local solution v_c from a
+//                           zero carry on the matrix cores (fp32 MFMA, A operand = J_t streamed
+//                           from HBM, B operand = the accumulators themselves)
 //   k_fixup_dense           the chunk re-run from its carry: forward (Newton: z += Delta and
 //                           max|Delta|; bare scan: y written) or reverse (y_{t-1} = J_t^T y_t + b)
-// Carries across chunks use the shared k_carry kernel.
+// Carries across chunks: k_carry.hip (M <= 16: k_plrnn.hip).
 #include "common.h"
 #include "launch.h"
 
@@ -22,273 +21,121 @@ struct DGeo {
     static constexpr int NS = MP / 4;
 };
 
-// J[row][col] of a step, zero outside M x M
-__device__ __forceinline__ float jload(const float *__restrict__ Jp, int M, int row, int col) {
-    return (row < M && col < M) ? Jp[row * M + col] : 0.f;
-}
-
-// FLIP: the scan uses the other orientation of every stored matrix than the direction's default
-// (forward: J_t^T instead of J_t; reverse: J_{t+1} instead of J_{t+1}^T), so one kernel serves all
-// four (direction, transpose) combinations of the bare scan.
-template <int MP, bool REV, bool FLIP>
-__global__ __launch_bounds__(64) void k_chunk_product_dense(const float *__restrict__ J, const float *__restrict__ rhs,
-                                                            float rhs_sign, float *__restrict__ Pout,
-                                                            float *__restrict__ vout, const int *__restrict__ active,
-                                                            int B, int T, int M, int C, int ncs) {
-    using G = DGeo<MP>;
-    constexpr int NCH = G::NCH, NI = G::NI, NS = G::NS;
-    __shared__ __align__(16) float lds[64];
+// ---------------------------------------------------------------------------------------
+// chunk products with the chunk-local solution, all four (direction, transpose) combinations.  The
+// chunk is swept in processing order (forward: k = s0 .., reverse: k = s1 - 1 ..) with the step's
+// matrix A_k = op(J_k) (reverse: op(J_{k+1})), op the transpose when TR:
+//   Q <- A_k Q,   u <- A_k u + rhs_sign * rhs_k.
+// One chain per wave; the B operand is [Q | u] (MP / 16 column tiles plus one whose column 0 is u), so
+// one set of A fragments advances both, and neither LDS nor barriers are needed.  With the
+// k-permutation kappa(4j+q, g) = 16j + 4g + q the accumulators are the next step's B operand, and
+// the four values a lane needs for k-steps 4j..4j+3 are one 16-byte vector of row 16I + c (TR: four
+// rows of column 16I + c).  The matrices of the next PF steps are in flight: a chunk is short and
+// one wave or two run on a SIMD, so a step otherwise waits for its load (M = 32, 4 x 8000 steps:
+// 58 us forward and 51 us reverse; with one step in flight and two chains a wave 70 us, and 155 us
+// with the local solution of the reverse on the vector units).
+// The first matrix of a sequence multiplies a zero state: it is not read.
+// P is stored as the carries take it: Q forward, Q^T reverse.
+// ---------------------------------------------------------------------------------------
+template <int MP, bool REV, bool TR>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MP == 64 ? 1 : 2))) void k_chunk_product_dense(
+    const float *__restrict__ J, const float *__restrict__ rhs, float rhs_sign, float *__restrict__ Pout,
+    float *__restrict__ vout, const int *__restrict__ active, int B, int T, int M, int C, int ncs) {
+    constexpr int NI = MP / 16, PF = MP == 16 ? 8 : MP == 32 ? 4 : 2;
     const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int nchains = B * ncs;
-    const int chain0 = blockIdx.x * NCH;
-    int pb[NCH], plo[NCH], plen[NCH], us0[NCH], us1[NCH];
-    int maxlen = 0;
+    const int id = blockIdx.x, b = id / ncs, s0 = (id % ncs) * C;
+    if (active && !active[b]) return;
+    const int s1 = min(s0 + C, T), len = s1 - s0;
+    const bool vec = !TR && M == MP;   // full 16-byte rows, no padding
+    float an[PF][NI][NI][4], rn[PF][NI][4];
+    auto fetch = [&](int t, float (&a)[NI][NI][4], float (&r)[NI][4]) {
+        const int k = REV ? s1 - 1 - t : s0 + t;
+        const size_t row = (size_t)b * T + k;
+        const float *Jp = J + ((size_t)b * T + (REV ? min(k + 1, T - 1) : k)) * M * M;
 #pragma unroll
-    for (int n = 0; n < NCH; ++n) {
-        const int id = chain0 + n;
-        bool ok = id < nchains;
-        const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
-        ok = ok && (!active || active[b]);
-        const int s0 = cc * C, s1 = min(s0 + C, T);
-        const int lo = REV ? s0 + 1 : s0;
-        const int hi = REV ? min(s1 + 1, T) : s1;
-        pb[n] = b;
-        plo[n] = lo;
-        plen[n] = ok ? max(hi - lo, 0) : 0;
-        us0[n] = s0;
-        us1[n] = ok ? s1 : s0;
-        maxlen = max(maxlen, max(plen[n], us1[n] - us0[n]));
-    }
-    v4f acc[NI][4];
+        for (int I = 0; I < NI; ++I) {
 #pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int col = 16 * Jt + c - n * MP;
+            for (int jj = 0; jj < NI; ++jj) {
+                if (vec) {
+                    const float4 v4 = *reinterpret_cast<const float4 *>(Jp + (16 * I + c) * M + 16 * jj + 4 * g);
+                    a[I][jj][0] = v4.x;
+                    a[I][jj][1] = v4.y;
+                    a[I][jj][2] = v4.z;
+                    a[I][jj][3] = v4.w;
+                } else {
 #pragma unroll
-        for (int I = 0; I < NI; ++I)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == col) ? 1.f : 0.f;
-    }
-    const int un = lane / MP, ui = lane % MP;
-    int ub = 0, ulo = 0, uhi = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n)
-        if (n == un) { ub = pb[n]; ulo = us0[n]; uhi = us1[n]; }
-    float u = 0.f;
-
-    for (int t = 0; t < maxlen; ++t) {
-#pragma unroll
-        for (int Jt = 0; Jt < 4; ++Jt) {
-            const int n = (16 * Jt) / MP;
-            if (t < plen[n]) {
-                const float *Jp = J + ((size_t)pb[n] * T + plo[n] + t) * M * M;
-                float Aop[NI][NS];
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            Aop[I][4 * j + q] = FLIP ? jload(Jp, M, 16 * j + 4 * g + q, 16 * I + c)
-                                                     : jload(Jp, M, 16 * I + c, 16 * j + 4 * g + q);
-                float Bop[NS];
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) Bop[4 * j + q] = acc[j][Jt][q];
-#pragma unroll
-                for (int I = 0; I < NI; ++I) {
-                    v4f a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) a = mfma16x16x4(Aop[I][s], Bop[s], a);
-                    acc[I][Jt] = a;
-                }
-            }
-        }
-        // local solution of the chunk (lane = chain un, row ui)
-        const bool run = ulo + t < uhi;
-        if (!REV) {
-            const int s = ulo + t;
-            lds[lane] = u;
-            lds_barrier();
-            float y = 0.f;
-            if (run && ui < M) {
-                // row ui of J_s, or column ui when flipped
-                const float *Jr = FLIP ? J + ((size_t)ub * T + s) * M * M + ui : J + (((size_t)ub * T + s) * M + ui) * M;
-                const size_t stride = FLIP ? (size_t)M : 1;
-                const float *l = lds + un * MP;
-                for (int k = 0; k < M; ++k) y = fmaf(Jr[k * stride], l[k], y);
-            }
-            lds_barrier();
-            if (run && ui < M) u = fmaf(rhs_sign, rhs[((size_t)ub * T + s) * M + ui], y);
-        } else {
-            const int k = uhi - 1 - t;        // y_k = J_{k+1}^T y_{k+1} + b_k
-            lds[lane] = u;
-            lds_barrier();
-            float y = 0.f;
-            if (run && ui < M && t > 0) {
-                // column ui of J_{k+1}, or row ui when flipped
-                const float *Jc = FLIP ? J + (((size_t)ub * T + k + 1) * M + ui) * M : J + ((size_t)ub * T + k + 1) * M * M + ui;
-                const size_t stride = FLIP ? 1 : (size_t)M;
-                const float *l = lds + un * MP;
-                for (int r = 0; r < M; ++r) y = fmaf(Jc[r * stride], l[r], y);
-            }
-            lds_barrier();
-            if (run && ui < M) u = fmaf(rhs_sign, rhs[((size_t)ub * T + k) * M + ui], y);
-        }
-    }
-#pragma unroll
-    for (int Jt = 0; Jt < 4; ++Jt) {
-        const int n = (16 * Jt) / MP;
-        const int id = chain0 + n;
-        if (id < nchains && (plen[n] > 0 || us1[n] > us0[n])) {
-            const int col = 16 * Jt + c - n * MP;
-            float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + col] = acc[I][Jt][r];
-        }
-    }
-    {
-        const int id = chain0 + un;
-        if (id < nchains) vout[(size_t)id * MP + ui] = u;
-    }
-}
-
-// Forward chunk product with the chunk-local solution on the matrix cores as well: per chain
-// the B operand is [P | u] (P's MP/16 column tiles plus one tile whose column 0 is u and whose
-// other columns stay 0), so one set of A fragments J~_t advances both
-//   P <- J~_t P,   u <- J~_t u + rhs_sign * rhs_t,
-// and neither LDS nor barriers are needed.  The A fragments are read one step ahead; with the
-// k-permutation kappa(4j+q, g) = 16j + 4g + q the four values a lane needs for k-steps 4j..4j+3
-// are one 16-byte vector of row 16I + c.
-template <int MP>
-__global__ __launch_bounds__(64) void k_chunk_product_dense_fwd(const float *__restrict__ J,
-                                                                const float *__restrict__ rhs, float rhs_sign,
-                                                                float *__restrict__ Pout, float *__restrict__ vout,
-                                                                const int *__restrict__ active, int B, int T, int M,
-                                                                int C, int ncs) {
-    using G = DGeo<MP>;
-    constexpr int NCH = G::NCH, NI = G::NI, NS = G::NS, PT = MP / 16;
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int nchains = B * ncs;
-    const int chain0 = blockIdx.x * NCH;
-    int pb[NCH], plo[NCH], plen[NCH];
-    int maxlen = 0;
-#pragma unroll
-    for (int n = 0; n < NCH; ++n) {
-        const int id = chain0 + n;
-        bool ok = id < nchains;
-        const int b = ok ? id / ncs : 0, cc = ok ? id % ncs : 0;
-        ok = ok && (!active || active[b]);
-        const int s0 = cc * C, s1 = min(s0 + C, T);
-        pb[n] = b;
-        plo[n] = s0;
-        plen[n] = ok ? max(s1 - s0, 0) : 0;
-        maxlen = max(maxlen, plen[n]);
-    }
-    const bool vec = (M == MP);   // full 16-byte rows, no padding
-    v4f acc[NCH][PT + 1][NI];
-#pragma unroll
-    for (int n = 0; n < NCH; ++n)
-#pragma unroll
-        for (int tt = 0; tt <= PT; ++tt)
-#pragma unroll
-            for (int I = 0; I < NI; ++I)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    acc[n][tt][I][r] = (tt < PT && 16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
-    float an[NCH][NI][NS];   // A fragments of the next step
-    float rn[NCH][NI][4];    // right-hand side of the next step (lanes of column 0)
-    auto fetch = [&](int t) {
-#pragma unroll
-        for (int n = 0; n < NCH; ++n) {
-            const bool run = t < plen[n];
-            const size_t step = (size_t)pb[n] * T + plo[n] + t;
-            const float *Jp = J + step * M * M;
-#pragma unroll
-            for (int I = 0; I < NI; ++I) {
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j) {
-                    if (vec) {
-                        const float4 v4 = run ? *reinterpret_cast<const float4 *>(Jp + (16 * I + c) * M + 16 * j + 4 * g)
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
-                        an[n][I][4 * j] = v4.x;
-                        an[n][I][4 * j + 1] = v4.y;
-                        an[n][I][4 * j + 2] = v4.z;
-                        an[n][I][4 * j + 3] = v4.w;
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            an[n][I][4 * j + q] = run ? jload(Jp, M, 16 * I + c, 16 * j + 4 * g + q) : 0.f;
+                    for (int q = 0; q < 4; ++q) {   // from a valid address, zeroed outside M x M
+                        const int row2 = 16 * I + c, col = 16 * jj + 4 * g + q;
+                        const bool in = row2 < M && col < M;
+                        const float x = Jp[in ? (TR ? col * M + row2 : row2 * M + col) : 0];
+                        a[I][jj][q] = in ? x : 0.f;
                     }
                 }
+            }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + 4 * g + r;
-                    rn[n][I][r] = (run && c == 0 && row < M) ? rhs[step * M + row] : 0.f;
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int i = 16 * I + 4 * g + q;
+                const float x = rhs[row * M + (i < M ? i : 0)];
+                r[I][q] = c == 0 && i < M ? x : 0.f;
             }
         }
     };
-    fetch(0);
-    for (int t = 0; t < maxlen; ++t) {
-        float ac[NCH][NI][NS], rc[NCH][NI][4];
+    v4f acc[NI + 1][NI];
 #pragma unroll
-        for (int n = 0; n < NCH; ++n)
+    for (int tt = 0; tt <= NI; ++tt)
 #pragma unroll
-            for (int I = 0; I < NI; ++I) {
+        for (int I = 0; I < NI; ++I)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) ac[n][I][s] = an[n][I][s];
+            for (int r = 0; r < 4; ++r) acc[tt][I][r] = (tt < NI && 16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) rc[n][I][r] = rn[n][I][r];
-            }
-        fetch(t + 1);
+    for (int p = 0; p < PF; ++p) fetch(min(p, len - 1), an[p], rn[p]);
+    for (int t0 = 0; t0 < len; t0 += PF) {
 #pragma unroll
-        for (int n = 0; n < NCH; ++n) {
-            if (t < plen[n]) {
+        for (int p = 0; p < PF; ++p) {
+            const int t = t0 + p;
+            if (t >= len) break;
+            const int k = REV ? s1 - 1 - t : s0 + t;
+            if (REV ? k + 1 < T : k > 0) {
 #pragma unroll
-                for (int tt = 0; tt <= PT; ++tt) {
-                    float Bop[NS];
+                for (int tt = 0; tt <= NI; ++tt) {
+                    v4f s[NI];
 #pragma unroll
-                    for (int j = 0; j < NS / 4; ++j)
+                    for (int I = 0; I < NI; ++I) s[I] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) Bop[4 * j + q] = acc[n][tt][j][q];
+                    for (int jj = 0; jj < NI; ++jj)
 #pragma unroll
-                    for (int I = 0; I < NI; ++I) {
-                        v4f a = {0.f, 0.f, 0.f, 0.f};
+                        for (int q = 0; q < 4; ++q)
 #pragma unroll
-                        for (int s = 0; s < NS; ++s) a = mfma16x16x4(ac[n][I][s], Bop[s], a);
-                        acc[n][tt][I] = a;
-                    }
+                            for (int I = 0; I < NI; ++I) s[I] = mfma16x16x4(an[p][I][jj][q], acc[tt][jj][q], s[I]);
+#pragma unroll
+                    for (int I = 0; I < NI; ++I) acc[tt][I] = s[I];
                 }
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[n][PT][I][r] = fmaf(rhs_sign, rc[n][I][r], acc[n][PT][I][r]);
             }
-        }
-    }
-#pragma unroll
-    for (int n = 0; n < NCH; ++n) {
-        const int id = chain0 + n;
-        if (id >= nchains) continue;
-        if (plen[n] > 0) {
-            float *P = Pout + (size_t)id * MP * MP;
-#pragma unroll
-            for (int tt = 0; tt < PT; ++tt)
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = acc[n][tt][I][r];
-        }
-        if (c == 0) {
 #pragma unroll
             for (int I = 0; I < NI; ++I)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) vout[(size_t)id * MP + 16 * I + 4 * g + r] = acc[n][PT][I][r];
+                for (int q = 0; q < 4; ++q) acc[NI][I][q] = fmaf(rhs_sign, rn[p][I][q], acc[NI][I][q]);
+            fetch(min(t + PF, len - 1), an[p], rn[p]);
         }
+    }
+    float *P = Pout + (size_t)id * MP * MP;
+#pragma unroll
+    for (int tt = 0; tt < NI; ++tt)
+#pragma unroll
+        for (int I = 0; I < NI; ++I) {
+            if constexpr (REV) {
+                *reinterpret_cast<float4 *>(P + (16 * tt + c) * MP + 16 * I + 4 * g) =
+                    make_float4(acc[tt][I][0], acc[tt][I][1], acc[tt][I][2], acc[tt][I][3]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = acc[tt][I][r];
+            }
+        }
+    if (c == 0) {
+#pragma unroll
+        for (int I = 0; I < NI; ++I)
+            *reinterpret_cast<float4 *>(vout + (size_t)id * MP + 16 * I + 4 * g) =
+                make_float4(acc[NI][I][0], acc[NI][I][1], acc[NI][I][2], acc[NI][I][3]);
     }
 }
 
@@ -409,25 +256,18 @@ int launch_chunk_product_dense(bool rev, int B, int T, int M, const float *J, co
                                float *P, float *v, const int *active, int C, int ncs, hipStream_t st, bool flip) {
     const int MP = padded_dim(M);
     if (MP == 128) return launch_chunk_product_big(rev, flip, B, T, M, J, rhs, rhs_sign, P, v, active, C, ncs, st);
-    const int nch = B * ncs;
-    const int grid = (nch + (64 / MP) - 1) / (64 / MP);
     KTimer kt("k_chunk_product_dense", st);
-#define CPD(MPV, R, FL)                                                                                          \
-    hipLaunchKernelGGL((k_chunk_product_dense<MPV, R, FL>), dim3(grid), dim3(64), 0, st, J, rhs, rhs_sign, P, v, active, \
-                       B, T, M, C, ncs)
-#define CPF(MPV)                                                                                           \
-    hipLaunchKernelGGL((k_chunk_product_dense_fwd<MPV>), dim3(grid), dim3(64), 0, st, J, rhs, rhs_sign, P, v, \
+#define CPD(MPV, R, TRV)                                                                                             \
+    hipLaunchKernelGGL((k_chunk_product_dense<MPV, R, TRV>), dim3(B * ncs), dim3(64), 0, st, J, rhs, rhs_sign, P, v,   \
                        active, B, T, M, C, ncs)
-    if (!rev && !flip) {
-        if (MP == 16) CPF(16); else if (MP == 32) CPF(32); else CPF(64);
-    } else if (!rev) {
-        if (MP == 16) CPD(16, false, true); else if (MP == 32) CPD(32, false, true); else CPD(64, false, true);
-    } else if (!flip) {
-        if (MP == 16) CPD(16, true, false); else if (MP == 32) CPD(32, true, false); else CPD(64, true, false);
+#define CPW(R, TRV) { if (MP == 16) CPD(16, R, TRV); else if (MP == 32) CPD(32, R, TRV); else CPD(64, R, TRV); }
+    const bool tr = rev != flip;   // the direction's default orientation, or the other
+    if (rev) {
+        if (tr) CPW(true, true) else CPW(true, false)
     } else {
-        if (MP == 16) CPD(16, true, true); else if (MP == 32) CPD(32, true, true); else CPD(64, true, true);
+        if (tr) CPW(false, true) else CPW(false, false)
     }
-#undef CPF
+#undef CPW
 #undef CPD
     DEER_LAUNCH_CHECK("k_chunk_product_dense");
     return DEER_OK;
