@@ -1,6 +1,6 @@
-"""Chunk products on the fp16 matrix cores with split operands (vanilla PLRNN, 16 < M <= 64): the
-Newton iterates against the float64 oracle's at the edges of the tiles, where the power-of-two
-scaling can go wrong, and where a chunk keeps its stored product."""
+"""Products on the fp16 matrix cores with split operands (PLRNN chunk products and carries, read-out):
+results against the float64 oracle's at the edges of the tiles, where the power-of-two scaling can go
+wrong, and where a chunk keeps its stored product."""
 import os
 
 import numpy as np
@@ -237,3 +237,73 @@ def test_carry_levels(M, ncs):
                 v = (np.einsum("bij,bj->bi", J[:, t].astype(np.float64), v) if t > 0 else 0.0) + b[:, t]
             ref[:, t] = v
         assert rel_inf(y, ref) < 1e-5
+
+
+@pytest.mark.parametrize("B,T,M,H,No", [(1, 130, 63, 127, 1), (3, 43, 5, 33, 4), (2, 1100, 64, 128, 3)])
+@pytest.mark.parametrize("kind", ["rows", "tiny", "large", "exact", "nan", "inf", "inf_weight"])
+def test_readout_scales(B, T, M, H, No, kind):
+    """Read-out: rows of very different size, weights far from one, rows without an error, and rows or
+    weights that are not finite (they reach the loss, and no other row's cotangent)."""
+    rng = np.random.default_rng(7000 + M)
+    p = {"Wa": rng.standard_normal((H, M)) / np.sqrt(M), "ca": 0.1 * rng.standard_normal(H),
+         "Wb": rng.standard_normal((No, H)) / np.sqrt(H), "cb": 0.1 * rng.standard_normal(No)}
+    h = rng.standard_normal((B, T, M)) + 1j * rng.standard_normal((B, T, M))
+    x = rng.standard_normal((B, T + 1, No))
+    if kind == "rows":
+        h *= 2.0 ** rng.integers(-20, 21, (B, T, 1))
+    elif kind == "tiny":
+        p["Wa"] *= 2.0 ** -60
+        p["Wb"] *= 2.0 ** -30
+        h *= 2.0 ** 40
+    elif kind == "large":
+        p["Wa"] *= 2.0 ** 50
+        p["Wb"] *= 2.0 ** 20
+        h *= 2.0 ** -60
+    elif kind == "exact":
+        h[:, ::3] = 0.0
+        p["ca"] = -np.abs(p["ca"])           # no unit is on in those rows: y = cb = x there
+        x[:, 1::3] = p["cb"].astype(np.float32)
+    p = {k: v.astype(np.float32) for k, v in p.items()}
+    h, x = h.astype(np.complex64), x.astype(np.float32)
+    hg, pg = h.copy(), dict(p)
+    if kind in ("nan", "inf"):
+        hg[0, 5, 0] = np.nan if kind == "nan" else np.inf
+    if kind == "inf_weight":
+        pg["Wa"] = p["Wa"].copy()
+        pg["Wa"][1, 2] = np.inf
+    say("split readout", B, T, M, H, No, kind)
+    out = D.deer_readout_loss(pg, torch.tensor(hg), x, want_masks=True)
+    mk = out["masks"].cpu().numpy().view(np.uint32).reshape(B, T, -1)
+    on = ((mk[..., :, None] >> np.arange(32, dtype=np.uint32)) & 1).astype(bool).reshape(B, T, -1)[..., :H]
+    gg = out["g"].cpu().numpy()
+    gr = {k: v.cpu().numpy() for k, v in out["grads"].items()}
+    s = O.diag_ssm_readout_preactivation(p, h)
+    if kind == "inf_weight":
+        assert not np.isfinite(float(out["loss"].cpu()[0]))
+        s = s[..., np.arange(H) != 1]
+        assert np.array_equal((s > 0)[np.abs(s) > 1e-5], on[..., np.arange(H) != 1][np.abs(s) > 1e-5])
+        return
+    rows = np.ones((B, T), bool)
+    rows[0, 5] = kind not in ("nan", "inf")
+    # decisions: fp32 sums of M products and the split's 2^-20 are within 1e-5 of sum |Wa| |h| + |ca|
+    band = 1e-5 * (np.abs(h.real.astype(np.float64)) @ np.abs(p["Wa"].astype(np.float64)).T + np.abs(p["ca"]))
+    clear = (np.abs(s) > band) & rows[..., None]
+    assert np.array_equal(on[clear], (s > 0)[clear])
+    loss, g, ref = O.diag_ssm_loss_and_seed(p, h, x, mask=on)
+    # g: the same bound carried through y, dy and dS (a row's own sizes only)
+    y_err = (band * on) @ np.abs(p["Wb"]).T.astype(np.float64) + 1e-5 * (np.abs(np.maximum(s, 0)) @ np.abs(p["Wb"]).T
+                                                                         + np.abs(p["cb"]) + np.abs(x[:, 1:]))
+    tol = 2.0 / (B * No * T) * 2.0 * (y_err @ np.abs(p["Wb"]).astype(np.float64)) @ np.abs(p["Wa"]).astype(np.float64)
+    assert (np.abs(gg - g) <= tol)[rows].all()
+    if kind == "exact":
+        assert not gg[:, ::3].any()
+    if kind == "inf":
+        assert not np.isfinite(float(out["loss"].cpu()[0]))
+        return
+    if kind == "nan":   # no unit is on in the row: y = cb, as for a row of zeros with every unit off
+        assert not on[0, 5].any() and not gg[0, 5].any()
+        assert np.isnan(gr["Wa"][:, 0]).all()
+        gr["Wa"][:, 0] = ref["Wa"][:, 0]
+    assert abs(float(out["loss"].cpu()[0]) - loss) <= 1e-5 * loss
+    for k in ("Wa", "ca", "Wb", "cb"):
+        assert rel_inf(gr[k], ref[k]) < TOL, k
