@@ -483,8 +483,8 @@ static int quasi_L(const deer_model *m) { return m->kind == DEER_SHPLRNN ? m->L 
 
 static int check_shallow_limits(const deer_model *m) {
     const size_t cap = 64 * 1024;
-    if (m->M > 64) {   // width-128 kernels: W1 and W2 in LDS
-        if (big_resjac_lds(m->M, m->L) > cap || big_jacform_lds(m->L) > cap || big_grads_lds(m->M, m->L) > cap) {
+    if (m->M > 64) {   // width-128 kernels: W1 and W2 in LDS; the Jacobians take at most two mask words
+        if (big_resjac_lds(m->M, m->L) > cap || m->L > 64 || big_grads_lds(m->M, m->L) > cap) {
             set_error("shallow PLRNN with M=%d, L=%d exceeds the 64 KiB LDS tiles of the width-128 kernels "
                       "(M > 64 needs L <= 62 and M L <= 7936)", m->M, m->L);
             return DEER_ERR_INVALID_ARG;

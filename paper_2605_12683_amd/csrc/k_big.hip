@@ -3,10 +3,9 @@
 // out for a 128 x 128 chain matrix that one wave cannot hold.
 //
 //   k_chunk_product_big   one 4-wave workgroup per chain: wave w holds columns 32w..32w+31 of the
-//                         chunk product P <- E_t P in matrix-core accumulators (the previous step's
-//                         accumulators are the B operand, the step's Jacobian rows the A operand,
-//                         read as 16-byte vectors); the chunk-local solution u <- E_t u + rhs on
-//                         the vector units through LDS
+//                         chunk product P <- E_t P in matrix-core accumulators (split, the B
+//                         operand of the next step), E_t split into LDS; the chunk-local solution
+//                         u <- E_t u + rhs on the vector units through LDS
 //   k_carry_big           one 256-thread block per walk: carries across the chunks, one level,
 //                         or two with k_carry_group_big (group maps on the matrix cores)
 //   k_fixup_big           one 128-thread block per chain: each chunk re-run from its carry
@@ -19,11 +18,11 @@
 // E_t is J_t, or J_t^T when flipped (the bare scan's other orientation), as in k_dense.hip.
 #include "common.h"
 #include "launch.h"
+#include "split16.h"
 
 namespace deer {
 
 constexpr int BG = 128;   // padded width
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // element (row, col) of E_t (J_t row-major per step, zero outside M x M)
 template <bool FLIP>
@@ -32,166 +31,306 @@ __device__ __forceinline__ float eload(const float *__restrict__ Jp, int M, int 
     return FLIP ? Jp[(size_t)col * M + row] : Jp[(size_t)row * M + col];
 }
 
+// Products of 128 x 128 matrices along a chain, Q <- E_t Q from the identity, on the fp16 matrix
+// cores with split operands (split16.h), one 4-wave workgroup per chain.  Wave w holds columns
+// 32 w .. 32 w + 31 of Q in accumulators, which after the split are the next step's B operand; E_t
+// is split by the workgroup into LDS in the A operand's layout, the next step's loads in flight
+// while the matrix cores work on this one.
+// Scales (powers of two): the wave that stages rows 32 w .. 32 w + 31 of E_t brings their largest
+// entry to [2^9, 2^10), every column of Q is brought to a 2-norm in [2^13, 2^14) before its split;
+// Q = acc[I] * rw[I / 2] * 2^-qe then, rw the row blocks' scales relative to the largest block's.
+// Rows with infinities or NaN are split unscaled (their results are not finite either way).
+// 192 instructions of 16 x 16 x 32 per wave and step take 1.5 us (512 of 16 x 16 x 4 in fp32 7.1 us),
+// after which reading E_t (64 KB a step on every CU) and the splits count as much.
+struct BigProd {
+    v4u es[2][8][4][2][64];   // [buffer][row tile][k block][hi, lo][es_slot(lane)]
+    float ub[2][BG];
+    int sc[2][4];             // [buffer][wave]: scale of the rows it staged
+};
+
+// Staging without a transpose: a load takes 128 bytes of each of 8 rows (16 rows of 64 bytes took 2.3
+// us a step with few blocks, this 1.4 us) and the lane group g of a row's 8-byte pieces is spread
+// over both halves of the banks; with a transpose a load takes 64 bytes of each of 4 source rows.
+__device__ __forceinline__ int es_slot(int lane) { return lane ^ ((lane >> 1) & 8); }
+
+template <bool TRN>
+struct BigChain {
+    BigProd &s;
+    int wv, lane, g, c;
+    float m1;
+    v4f acc[8][2];            // acc[I][Jt][r]: row 16 I + 4 g + r, column 32 wv + 16 Jt + c
+    float rw[4];
+    int qe[2];
+    float4 pre[16];           // the next E: columns col(k) .. + 3 of row(k)
+
+    __device__ __forceinline__ explicit BigChain(BigProd &sm) : s(sm) {
+        wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        lane = threadIdx.x & 63;
+        g = lane >> 4;
+        c = lane & 15;
+        m1 = opaque_m1();
+#pragma unroll
+        for (int I = 0; I < 8; ++I)
+#pragma unroll
+            for (int Jt = 0; Jt < 2; ++Jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 32 * wv + 16 * Jt + c) ? 1.f : 0.f;
+        for (int w = 0; w < 4; ++w) rw[w] = 1.f;
+        qe[0] = qe[1] = 0;
+    }
+    __device__ __forceinline__ int row(int k) const {
+        return TRN ? 16 * (2 * wv + (k >> 3)) + c : 32 * wv + 8 * (k >> 2) + (lane >> 3);
+    }
+    __device__ __forceinline__ int col(int k) const { return TRN ? 16 * (k & 7) + 4 * g : 32 * (k & 3) + 4 * (lane & 7); }
+    // the staged rows, split, into buffer buf
+    __device__ __forceinline__ void stage_store(int buf) {
+        float mx = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            mx = fmaxf(fmaxf(fmaxf(mx, fabsf(pre[k].x)), fmaxf(fabsf(pre[k].y), fabsf(pre[k].z))), fabsf(pre[k].w));
+        mx = __uint_as_float(wave_max_u32(__float_as_uint(mx)));
+        const int e = exp_of(mx);
+        const int sc = __builtin_amdgcn_readfirstlane(e == 128 ? 0 : min(9 - e, 100));
+        const float f = ldexpf(1.f, sc);
+        typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+        if constexpr (TRN) {
+#pragma unroll
+            for (int k = 0; k < 16; k += 2) {
+                v4u hi, lo;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4 v = pre[k + h];
+                    uint32_t a, b;
+                    split_pair(v.x * f, v.y * f, m1, a, b);
+                    hi[2 * h] = a;
+                    lo[2 * h] = b;
+                    split_pair(v.z * f, v.w * f, m1, a, b);
+                    hi[2 * h + 1] = a;
+                    lo[2 * h + 1] = b;
+                }
+                s.es[buf][2 * wv + (k >> 3)][(k & 7) >> 1][0][es_slot(lane)] = hi;
+                s.es[buf][2 * wv + (k >> 3)][(k & 7) >> 1][1][es_slot(lane)] = lo;
+            }
+        } else {
+            const int gg = lane & 3, e2 = (lane >> 2) & 1, cr = lane >> 3;   // lane group, slot half, row mod 8
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float4 v = pre[k];
+                uint32_t a, b, a2, b2;
+                split_pair(v.x * f, v.y * f, m1, a, b);
+                split_pair(v.z * f, v.w * f, m1, a2, b2);
+                const int sl = es_slot(16 * gg + 8 * ((k >> 2) & 1) + cr);
+                reinterpret_cast<v2u *>(&s.es[buf][2 * wv + (k >> 3)][k & 3][0][sl])[e2] = (v2u){a, a2};
+                reinterpret_cast<v2u *>(&s.es[buf][2 * wv + (k >> 3)][k & 3][1][sl])[e2] = (v2u){b, b2};
+            }
+        }
+        if (lane == 0) s.sc[buf][wv] = sc;
+    }
+    // Q <- E Q with the E of buffer buf
+    __device__ __forceinline__ void multiply(int buf) {
+        v4u bh[2][4], bl[2][4];
+        int sh[2];
+#pragma unroll
+        for (int Jt = 0; Jt < 2; ++Jt) {
+            float m2 = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                float q = 0.f;
+#pragma unroll
+                for (int I = 2 * w; I < 2 * w + 2; ++I)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) q = fmaf(acc[I][Jt][r], acc[I][Jt][r], q);
+                m2 = fmaf(q, rw[w] * rw[w], m2);
+            }
+            sh[Jt] = norm_shift(group_sum(m2));
+            const float f = pow2i(sh[Jt]);
+#pragma unroll
+            for (int I = 0; I < 8; ++I) {
+                const float fi = f * rw[I >> 1];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t a, b;
+                    split_pair(acc[I][Jt][2 * h] * fi, acc[I][Jt][2 * h + 1] * fi, m1, a, b);
+                    bh[Jt][I >> 1][2 * (I & 1) + h] = a;
+                    bl[Jt][I >> 1][2 * (I & 1) + h] = b;
+                }
+            }
+        }
+#pragma unroll
+        for (int I0 = 0; I0 < 8; I0 += 4) {
+#pragma unroll
+            for (int I = I0; I < I0 + 4; ++I)
+#pragma unroll
+                for (int Jt = 0; Jt < 2; ++Jt) acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                v4u ah[4], al[4];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    ah[n] = s.es[buf][I0 + n][kk][0][es_slot(lane)];
+                    al[n] = s.es[buf][I0 + n][kk][1][es_slot(lane)];
+                }
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+#pragma unroll
+                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(al[n], bh[Jt][kk], acc[I0 + n][Jt]);
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+#pragma unroll
+                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(ah[n], bl[Jt][kk], acc[I0 + n][Jt]);
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+#pragma unroll
+                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(ah[n], bh[Jt][kk], acc[I0 + n][Jt]);
+            }
+        }
+        int sc[4], ref = 1000;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            sc[w] = __builtin_amdgcn_readfirstlane(s.sc[buf][w]);
+            ref = min(ref, sc[w]);
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) rw[w] = ldexpf(1.f, ref - sc[w]);
+#pragma unroll
+        for (int Jt = 0; Jt < 2; ++Jt) qe[Jt] += sh[Jt] + ref;
+    }
+    // row 32 wv + lane % 32 of E u for the E and the u of buffer buf (both halves of the wave hold it)
+    __device__ __forceinline__ float apply(int buf) {
+        const int I = 2 * wv + ((lane & 31) >> 4), hh = lane >> 5;
+        float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2) {
+            const int kk = 2 * hh + k2;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const v4u hi = s.es[buf][I][kk][0][es_slot(16 * q + c)], lo = s.es[buf][I][kk][1][es_slot(16 * q + c)];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4 y = *reinterpret_cast<const float4 *>(&s.ub[buf][32 * kk + 16 * h + 4 * q]);
+                    const v2h a0 = __builtin_bit_cast(v2h, (uint32_t)hi[2 * h]), a1 = __builtin_bit_cast(v2h, (uint32_t)hi[2 * h + 1]);
+                    const v2h b0 = __builtin_bit_cast(v2h, (uint32_t)lo[2 * h]), b1 = __builtin_bit_cast(v2h, (uint32_t)lo[2 * h + 1]);
+                    p0 = fmaf((float)b0[0], y.x, p0);
+                    p1 = fmaf((float)b0[1], y.y, p1);
+                    p0 = fmaf((float)b1[0], y.z, p0);
+                    p1 = fmaf((float)b1[1], y.w, p1);
+                    p0 = fmaf((float)a0[0], y.x, p0);
+                    p1 = fmaf((float)a0[1], y.y, p1);
+                    p0 = fmaf((float)a1[0], y.z, p0);
+                    p1 = fmaf((float)a1[1], y.w, p1);
+                }
+            }
+        }
+        float part = p0 + p1;
+        part += __shfl_xor(part, 32, 64);
+        return ldexpf(part, -__builtin_amdgcn_readfirstlane(s.sc[buf][wv]));
+    }
+    // (Q^T r)[32 wv + 16 Jt + c] for the r of buffer buf
+    __device__ __forceinline__ float apply_t(int buf, int Jt) {
+        float part = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            float q = 0.f;
+#pragma unroll
+            for (int I = 2 * w; I < 2 * w + 2; ++I) {
+                const float4 rv = *reinterpret_cast<const float4 *>(&s.ub[buf][16 * I + 4 * g]);
+                q = fmaf(acc[I][Jt][0], rv.x, q);
+                q = fmaf(acc[I][Jt][1], rv.y, q);
+                q = fmaf(acc[I][Jt][2], rv.z, q);
+                q = fmaf(acc[I][Jt][3], rv.w, q);
+            }
+            part = fmaf(q, rw[w], part);
+        }
+        return ldexpf(group_sum(part), -qe[Jt]);
+    }
+    __device__ __forceinline__ void store(float *__restrict__ P) {
+#pragma unroll
+        for (int I = 0; I < 8; ++I)
+#pragma unroll
+            for (int Jt = 0; Jt < 2; ++Jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    P[(16 * I + 4 * g + r) * BG + 32 * wv + 16 * Jt + c] = ldexpf(acc[I][Jt][r] * rw[I >> 1], -qe[Jt]);
+    }
+};
+
 // REV: the product covers steps [s0 + 1, min(s1 + 1, T)) (the reverse chunk map is its
 // transpose) and the local solution of u_k = E_{k+1}^T u_{k+1} + rhs_k (zero past the chunk) is
-// taken as the sum u_{s0} = sum_k (E_k ... E_{s0+1})^T rhs_k along the same sweep.
-// The step's E (128 x 128, zero outside M x M) is staged in LDS by the whole workgroup, the next
-// step's loads in flight while the matrix cores work on this one (double buffer), and every wave
-// reads its A operands there; the forward local solution reads the same tile.
-constexpr int JST = BG + 4;   // LDS row stride of the staged E (16-byte rows, conflict-free reads)
-
+// taken as the sum u_{s0} = sum_k (E_k ... E_{s0+1})^T rhs_k along the same sweep: Q_k =
+// E_k ... E_{s0+1} is the accumulated product after the step that takes E_k.
+// M = 128, 8192 steps in 256 chunks: forward 347 us and reverse 310 us with fp32 instructions,
+// 194 us and 169 us now (reading the matrices alone takes 109 us).
 template <bool REV, bool FLIP>
 __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restrict__ J, const float *__restrict__ rhs,
                                                            float rhs_sign, float *__restrict__ Pout,
                                                            float *__restrict__ vout, const int *__restrict__ active,
                                                            int B, int T, int M, int C, int ncs) {
-    __shared__ __align__(16) float js[2][BG][JST];
-    __shared__ __align__(16) float ub[2][BG];
-    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
+    __shared__ __align__(16) BigProd sm;
     const int id = blockIdx.x;   // chain
     const int b = id / ncs, cc = id % ncs;
-    const bool ok = !active || active[b];
+    if (active && !active[b]) return;
+    BigChain<FLIP> q(sm);
+    const int tid = threadIdx.x, g = q.g, c = q.c, wv = q.wv;
     const int s0 = cc * C, s1 = min(s0 + C, T);
     const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
-    const int plen = ok ? max(hi - lo, 0) : 0;
-    const int ulen = ok ? s1 - s0 : 0;
-    // REV: the chunk's local adjoint is u_{s0} = sum_k Q_k^T rhs_k with Q_k = E_k ... E_{s0+1}
-    // (Q_{s0} = I), and Q_k is the accumulated product after the step that takes E_k: the sweep
-    // that forms the product forms u_{s0} too, with the staged right-hand side of that step
-    const int nsteps = REV ? plen : max(plen, ulen);
-    // staging: thread tid takes the 16-byte groups tid + 256 k (k < 16) of the 128 x 128 tile,
-    // row (tid + 256 k) / 32, columns 4 ((tid + 256 k) % 32) .. + 3
-    float4 pre[16];
+    const int len = max(hi - lo, 0);
+    const int ui = 32 * wv + (q.lane & 31);   // the row of u this lane forms (REV: whose rhs it stages)
+    const bool own = q.lane < 32;
     float rpre = 0.f;
     // row-major E with M % 4 == 0: 16-byte loads through a resource bounded at the matrix's end
-    // (rows past M read zero) with one lane offset (columns past M: an offset outside it)
+    // (rows past M read zero; columns past M take an offset outside it)
     const bool fast = !FLIP && (M & 3) == 0;
-    const uint32_t vlane = ((tid & 31) * 4 + 3 < M) ? 4u * ((uint32_t)(tid >> 5) * M + (tid & 31) * 4) : kOffLane;
     auto stage_load = [&](int t) {
-        const float *Jp = J + ((size_t)b * T + lo + t) * M * M;
-        if (REV) rpre = (tid < M && lo + t < s1) ? rhs[((size_t)b * T + lo + t) * M + tid] : 0.f;
+        const size_t row = (size_t)b * T + lo + t;
+        const float *Jp = J + row * M * M;
+        rpre = (ui < M && lo + t < s1) ? rhs[row * M + ui] : 0.f;
         if (fast) {
             const auto rs = bounded_rsrc(Jp, (uint32_t)M * M * 4u);
 #pragma unroll
-            for (int k = 0; k < 16; ++k)
-                pre[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vlane, k * 32 * M, 0));
+            for (int k = 0; k < 16; ++k) {
+                const uint32_t vo = q.col(k) < M ? 4u * (uint32_t)(q.row(k) * M + q.col(k)) : kOffLane;
+                q.pre[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, 0, 0));
+            }
             return;
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const int e4 = tid + 256 * k, row = e4 >> 5, c4 = (e4 & 31) * 4;
-            pre[k] = make_float4(eload<FLIP>(Jp, M, row, c4), eload<FLIP>(Jp, M, row, c4 + 1),
-                                 eload<FLIP>(Jp, M, row, c4 + 2), eload<FLIP>(Jp, M, row, c4 + 3));
+            const int r = q.row(k), col = q.col(k);
+            q.pre[k] = make_float4(eload<FLIP>(Jp, M, r, col), eload<FLIP>(Jp, M, r, col + 1),
+                                   eload<FLIP>(Jp, M, r, col + 2), eload<FLIP>(Jp, M, r, col + 3));
         }
     };
-    auto stage_store = [&](int buf) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int e4 = tid + 256 * k;
-            *reinterpret_cast<float4 *>(&js[buf][e4 >> 5][(e4 & 31) * 4]) = pre[k];
-        }
-        if (REV && tid < BG) ub[buf][tid] = rpre;
-    };
-    // accumulators: acc[I][Jt][r] = P[16 I + 4 g + r][32 wv + 16 Jt + c]
-    v4f acc[8][2];
-#pragma unroll
-    for (int I = 0; I < 8; ++I)
-#pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 32 * wv + 16 * Jt + c) ? 1.f : 0.f;
-    // local solution: thread pair (row i = tid / 2, half hh) sums half of the row
-    const int ui = tid >> 1, hh = tid & 1;
-    if (tid < BG) ub[0][tid] = 0.f;
     float vsum[2] = {0.f, 0.f};   // REV: sum over the steps of (Q_k^T rhs_k)[32 wv + 16 Jt + c]
-    if (plen > 0) {
+    if (!REV && tid < BG) sm.ub[0][tid] = 0.f;
+    if (len > 0) {
         stage_load(0);
-        stage_store(0);
+        q.stage_store(0);
+        if (REV && own) sm.ub[0][ui] = rpre;
     }
     __syncthreads();
     int cur = 0;
-    for (int t = 0; t < nsteps; ++t) {
-        const bool more = t + 1 < plen;
+    for (int t = 0; t < len; ++t, cur ^= 1) {
+        const bool more = t + 1 < len;
+        const float rc = rpre;
         if (more) stage_load(t + 1);   // in flight during this step
-        if (t < plen) {
-            v4f old[8][2];
+        q.multiply(cur);
+        if (REV) {
+            if (lo + t < s1) {
 #pragma unroll
-            for (int I = 0; I < 8; ++I)
-#pragma unroll
-                for (int Jt = 0; Jt < 2; ++Jt) {
-                    old[I][Jt] = acc[I][Jt];
-                    acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-            for (int I = 0; I < 8; ++I) {
-                float4 a[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) a[j] = *reinterpret_cast<const float4 *>(&js[cur][16 * I + c][16 * j + 4 * g]);
-#pragma unroll
-                for (int Jt = 0; Jt < 2; ++Jt) {
-                    v4f s = acc[I][Jt];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        s = mfma16x16x4(a[j].x, old[j][Jt][0], s);
-                        s = mfma16x16x4(a[j].y, old[j][Jt][1], s);
-                        s = mfma16x16x4(a[j].z, old[j][Jt][2], s);
-                        s = mfma16x16x4(a[j].w, old[j][Jt][3], s);
-                    }
-                    acc[I][Jt] = s;
-                }
+                for (int Jt = 0; Jt < 2; ++Jt) vsum[Jt] += q.apply_t(cur, Jt);
             }
-            if (REV && lo + t < s1) {
-                // rows 16 I + 4 g + r of column 32 wv + 16 Jt + c, then the four row groups g
-#pragma unroll
-                for (int Jt = 0; Jt < 2; ++Jt) {
-                    float part = 0.f;
-#pragma unroll
-                    for (int I = 0; I < 8; ++I) {
-                        const float4 rv = *reinterpret_cast<const float4 *>(&ub[cur][16 * I + 4 * g]);
-                        part = fmaf(acc[I][Jt][0], rv.x, part);
-                        part = fmaf(acc[I][Jt][1], rv.y, part);
-                        part = fmaf(acc[I][Jt][2], rv.z, part);
-                        part = fmaf(acc[I][Jt][3], rv.w, part);
-                    }
-                    part += __shfl_xor(part, 16, 64);
-                    part += __shfl_xor(part, 32, 64);
-                    vsum[Jt] += part;
-                }
-            }
+        } else {
+            // u_k = E_k u_{k-1} + sign rhs_k
+            const float y = q.apply(cur);
+            if (own) sm.ub[cur ^ 1][ui] = ui < M ? fmaf(rhs_sign, rc, y) : 0.f;
         }
-        if (!REV && t < ulen) {
-            // u_s = E_s u_{s-1} + sign rhs_s, s = s0 + t (E_s is the staged tile, zero outside M x M
-            // as u is): half hh of row ui, q in [64 hh, 64 hh + 64) four at a time, walked from 32
-            // entries in for hh = 1 so that the two halves of a lane pair fall on other banks
-            const int k = s0 + t;
-            float p0 = 0.f, p1 = 0.f;
-#pragma unroll 4
-            for (int u = 0; u < 64; u += 4) {
-                const int q = 64 * hh + ((u + 32 * hh) & 63);
-                const float4 e = *reinterpret_cast<const float4 *>(&js[cur][ui][q]);
-                const float4 y = *reinterpret_cast<const float4 *>(&ub[cur][q]);
-                p0 = fmaf(e.x, y.x, p0);
-                p1 = fmaf(e.y, y.y, p1);
-                p0 = fmaf(e.z, y.z, p0);
-                p1 = fmaf(e.w, y.w, p1);
-            }
-            float part = p0 + p1;
-            part += __shfl_xor(part, 1, 64);
-            if (hh == 0 && ui < BG)
-                ub[cur ^ 1][ui] = ui < M ? fmaf(rhs_sign, rhs[((size_t)b * T + k) * M + ui], part) : 0.f;
+        if (more) {
+            q.stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
+            if (REV && own) sm.ub[cur ^ 1][ui] = rpre;
         }
-        if (more) stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
         __syncthreads();
-        cur ^= 1;
     }
-    if (!ok) return;
-    float *P = Pout + (size_t)id * BG * BG;
-#pragma unroll
-    for (int I = 0; I < 8; ++I)
-#pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * BG + 32 * wv + 16 * Jt + c] = acc[I][Jt][r];
+    q.store(Pout + (size_t)id * BG * BG);
     if (REV) {
         if (g == 0) {
 #pragma unroll
@@ -202,7 +341,7 @@ __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restri
             }
         }
     } else if (tid < BG) {
-        vout[(size_t)id * BG + tid] = ub[cur][tid];
+        vout[(size_t)id * BG + tid] = sm.ub[cur][tid];
     }
 }
 
@@ -214,182 +353,138 @@ __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restri
 constexpr int FST = BG + 1;   // LDS row stride of a tile read along rows and along columns
 
 // one walk of G consecutive k per 256-thread block (G = ncs: a whole sequence), from zero or from
-// the walk's start vector.  Lane l of wave w forms half hh = l / 32 of row i = 32 w + l % 32 of
-// A_k y; each step's P_c is staged in LDS with coalesced loads, the next one's in flight.
+// the walk's start vector.  Few blocks run, so a step is bound by latency: the maps go straight to
+// registers, two steps ahead, and only y passes through LDS.  A load takes 128 bytes of each of 8
+// rows, lane l columns 32 j + 4 (l % 8) .. + 3 of row 32 w + 8 u + l / 8; REV: columns
+// 32 w + 4 (l % 8) .. + 3 of row l / 8 + 8 j.  The partial sums are added across the lanes.
+// M = 128: 32 blocks walking 8 maps 11 us, one block walking 32 maps 37 us (20 and 73 us with the
+// maps staged in LDS).
 template <bool REV>
 __global__ __launch_bounds__(256) void k_carry_big(const float *__restrict__ P, const float *__restrict__ v,
                                                    float *__restrict__ carry_in, const int *__restrict__ active,
                                                    int ncs, int G, const float *__restrict__ start) {
-    __shared__ float js[2][BG][FST];
-    __shared__ float ys[2][BG];
+    __shared__ __align__(16) float ys[2][BG];
     const int ngroups = (ncs + G - 1) / G;
     const int b = blockIdx.x / ngroups, j = blockIdx.x % ngroups;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, i = 32 * w + (lane & 31);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (active && !active[b]) return;
     const int k0 = j * G, k1 = min(k0 + G, ncs);
     auto chunk = [&](int k) { return (size_t)b * ncs + (REV ? ncs - 1 - k : k); };
-    // staging: thread tid takes the 16-byte groups tid + 256 q (q < 16) of the 128 x 128 map,
-    // row (tid + 256 q) / 32, columns 4 (tid % 32) .. + 3
-    float4 pre[16];
-    float vpre = 0.f;
-    auto stage_load = [&](int k) {
-        const size_t id = chunk(k);
-        const float4 *P4 = reinterpret_cast<const float4 *>(P + id * BG * BG);
+    float4 pre[2][16];
+    float vpre[2];
+    auto load = [&](int k, float4 (&p)[16], float &vv) {
+        const size_t id = chunk(min(k, k1 - 1));
+        const float *Pc = P + id * BG * BG;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) pre[q] = P4[tid + 256 * q];
-        vpre = v[id * BG + i];
+        for (int q = 0; q < 16; ++q)
+            p[q] = *reinterpret_cast<const float4 *>(
+                REV ? Pc + ((lane >> 3) + 8 * q) * BG + 32 * w + 4 * (lane & 7)
+                    : Pc + (32 * w + 8 * (q >> 2) + (lane >> 3)) * BG + 32 * (q & 3) + 4 * (lane & 7));
+        vv = v[id * BG + (tid & (BG - 1))];
     };
-    auto stage_store = [&](int buf) {
+    auto step = [&](int k, float4 (&p)[16], float &vv) {
+        const int cur = (k - k0) & 1;
+        if (tid < BG) carry_in[chunk(k) * BG + tid] = ys[cur][tid];
+        float o[4] = {0.f, 0.f, 0.f, 0.f};
+        if (REV) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int e4 = tid + 256 * q, row = e4 >> 5, c4 = (e4 & 31) * 4;
-            js[buf][row][c4] = pre[q].x;
-            js[buf][row][c4 + 1] = pre[q].y;
-            js[buf][row][c4 + 2] = pre[q].z;
-            js[buf][row][c4 + 3] = pre[q].w;
+            for (int q = 0; q < 16; ++q) {
+                const float y = ys[cur][(lane >> 3) + 8 * q];
+                o[0] = fmaf(p[q].x, y, o[0]);
+                o[1] = fmaf(p[q].y, y, o[1]);
+                o[2] = fmaf(p[q].z, y, o[2]);
+                o[3] = fmaf(p[q].w, y, o[3]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                o[e] += __shfl_xor(o[e], 8, 64);
+                o[e] = group_sum(o[e]);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 y = *reinterpret_cast<const float4 *>(&ys[cur][32 * q + 4 * (lane & 7)]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    o[u] = fmaf(p[4 * u + q].x, y.x, o[u]);
+                    o[u] = fmaf(p[4 * u + q].y, y.y, o[u]);
+                    o[u] = fmaf(p[4 * u + q].z, y.z, o[u]);
+                    o[u] = fmaf(p[4 * u + q].w, y.w, o[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                o[u] += __shfl_xor(o[u], 1, 64);
+                o[u] += __shfl_xor(o[u], 2, 64);
+                o[u] += __shfl_xor(o[u], 4, 64);
+            }
         }
+        // the new state without v in the other buffer (its reads ended at the previous barrier)
+        if (REV) {
+            if (lane < 8) *reinterpret_cast<float4 *>(&ys[cur ^ 1][32 * w + 4 * lane]) = make_float4(o[0], o[1], o[2], o[3]);
+        } else if ((lane & 7) < 4) {
+            const int u = lane & 3;
+            ys[cur ^ 1][32 * w + 8 * u + (lane >> 3)] = u == 0 ? o[0] : u == 1 ? o[1] : u == 2 ? o[2] : o[3];
+        }
+        lds_barrier();
+        if (tid < BG) ys[cur ^ 1][tid] += vv;
+        load(k + 2, p, vv);
+        lds_barrier();
     };
+    load(k0, pre[0], vpre[0]);
+    load(k0 + 1, pre[1], vpre[1]);
     if (tid < BG) ys[0][tid] = start ? start[((size_t)b * ngroups + j) * BG + tid] : 0.f;
-    stage_load(k0);
-    stage_store(0);
-    float vc = vpre;
     __syncthreads();
-    int cur = 0;
-    const int q0 = 64 * hh;
-    for (int k = k0; k < k1; ++k) {
-        const bool more = k + 1 < k1;
-        if (more) stage_load(k + 1);   // in flight during this step
-        if (hh == 0) carry_in[chunk(k) * BG + i] = ys[cur][i];
-        // half hh of the sum over q in [64 hh, 64 hh + 64), walked from 32 hh on: with the row
-        // stride of 129 the 64 lanes of a read fall on distinct banks, along rows and columns
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 4
-        for (int u = 0; u < 64; u += 4) {
-            const int q = q0 + ((u + 32 * hh) & 63);
-            const float e0 = REV ? js[cur][q][i] : js[cur][i][q];
-            const float e1 = REV ? js[cur][q + 1][i] : js[cur][i][q + 1];
-            const float e2 = REV ? js[cur][q + 2][i] : js[cur][i][q + 2];
-            const float e3 = REV ? js[cur][q + 3][i] : js[cur][i][q + 3];
-            a0 = fmaf(e0, ys[cur][q], a0);
-            a1 = fmaf(e1, ys[cur][q + 1], a1);
-            a2 = fmaf(e2, ys[cur][q + 2], a2);
-            a3 = fmaf(e3, ys[cur][q + 3], a3);
-        }
-        float part = (a0 + a1) + (a2 + a3);
-        part += __shfl_xor(part, 32, 64);
-        if (hh == 0) ys[cur ^ 1][i] = part + vc;
-        if (more) {
-            stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
-            vc = vpre;
-        }
-        __syncthreads();
-        cur ^= 1;
+    for (int k = k0; k < k1; k += 2) {
+        step(k, pre[0], vpre[0]);
+        if (k + 1 < k1) step(k + 1, pre[1], vpre[1]);
     }
 }
 
-// group maps in processing order: Q_j = A_{k1-1} ... A_{k0} and u_j = the group's walk from zero.
-// Q accumulates on the matrix cores as the chunk product above does (A_k staged in LDS, transposed
-// there in REV, the next one's loads in flight; Q in the k-permuted accumulator layout that is the
-// next step's B operand); u by thread pairs over the staged rows.
+// group maps in processing order: Q_j = A_{k1-1} ... A_{k0} and u_j = the group's walk from zero,
+// composed as the chunk products are.  M = 128, 32 groups of 8: 42 us (118 us with fp32
+// instructions).
 template <bool REV>
 __global__ __launch_bounds__(256) void k_carry_group_big(const float *__restrict__ P, const float *__restrict__ v,
                                                          float *__restrict__ gq, float *__restrict__ gu,
                                                          const int *__restrict__ active, int ncs, int G) {
-    __shared__ __align__(16) float js[2][BG][JST];
-    __shared__ __align__(16) float ub[2][BG];
+    __shared__ __align__(16) BigProd sm;
     const int ngroups = (ncs + G - 1) / G;
     const int b = blockIdx.x / ngroups, j = blockIdx.x % ngroups;
-    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
     if (active && !active[b]) return;
+    BigChain<REV> q(sm);
+    const int tid = threadIdx.x, ui = 32 * q.wv + (q.lane & 31);
     const int k0 = j * G, k1 = min(k0 + G, ncs);
-    auto chunk = [&](int k) { return (size_t)b * ncs + (REV ? ncs - 1 - k : k); };
-    const int ui = tid >> 1, hh = tid & 1;
-    float4 pre[16];
     float vpre = 0.f;
     auto stage_load = [&](int k) {
-        const size_t id = chunk(k);
-        const float4 *P4 = reinterpret_cast<const float4 *>(P + id * BG * BG);
+        const size_t id = (size_t)b * ncs + (REV ? ncs - 1 - k : k);
+        const float *Pc = P + id * BG * BG;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) pre[q] = P4[tid + 256 * q];
-        if (hh == 0) vpre = v[id * BG + ui];
-    };
-    auto stage_store = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int e4 = tid + 256 * q, row = e4 >> 5, c4 = (e4 & 31) * 4;
-            if (REV) {
-                js[buf][c4][row] = pre[q].x;
-                js[buf][c4 + 1][row] = pre[q].y;
-                js[buf][c4 + 2][row] = pre[q].z;
-                js[buf][c4 + 3][row] = pre[q].w;
-            } else {
-                *reinterpret_cast<float4 *>(&js[buf][row][c4]) = pre[q];
-            }
+        for (int k2 = 0; k2 < 16; ++k2) {
+            const int r = q.row(k2), col = q.col(k2);
+            q.pre[k2] = REV ? make_float4(Pc[col * BG + r], Pc[(col + 1) * BG + r], Pc[(col + 2) * BG + r],
+                                          Pc[(col + 3) * BG + r])
+                            : *reinterpret_cast<const float4 *>(Pc + r * BG + col);
         }
+        vpre = v[id * BG + ui];
     };
-    // accumulators: acc[I][Jt][r] = Q[16 I + 4 g + r][32 wv + 16 Jt + c]
-    v4f acc[8][2];
-#pragma unroll
-    for (int I = 0; I < 8; ++I)
-#pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 32 * wv + 16 * Jt + c) ? 1.f : 0.f;
-    if (tid < BG) ub[0][tid] = 0.f;
+    if (tid < BG) sm.ub[0][tid] = 0.f;
     stage_load(k0);
-    stage_store(0);
-    float vc = vpre;
+    q.stage_store(0);
     __syncthreads();
     int cur = 0;
-    for (int k = k0; k < k1; ++k) {
+    for (int k = k0; k < k1; ++k, cur ^= 1) {
         const bool more = k + 1 < k1;
+        const float vc = vpre;
         if (more) stage_load(k + 1);   // in flight during this step
-        v4f old[8][2];
-#pragma unroll
-        for (int I = 0; I < 8; ++I)
-#pragma unroll
-            for (int Jt = 0; Jt < 2; ++Jt) {
-                old[I][Jt] = acc[I][Jt];
-                acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-        for (int I = 0; I < 8; ++I) {
-            float4 a[8];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) a[jj] = *reinterpret_cast<const float4 *>(&js[cur][16 * I + c][16 * jj + 4 * g]);
-#pragma unroll
-            for (int Jt = 0; Jt < 2; ++Jt) {
-                v4f s = acc[I][Jt];
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                    s = mfma16x16x4(a[jj].x, old[jj][Jt][0], s);
-                    s = mfma16x16x4(a[jj].y, old[jj][Jt][1], s);
-                    s = mfma16x16x4(a[jj].z, old[jj][Jt][2], s);
-                    s = mfma16x16x4(a[jj].w, old[jj][Jt][3], s);
-                }
-                acc[I][Jt] = s;
-            }
-        }
-        // u <- A_k u + v_c: thread pair (row ui, half hh) sums every other entry of the row
-        float part = 0.f;
-        for (int q = hh; q < BG; q += 2) part = fmaf(js[cur][ui][q], ub[cur][q], part);
-        part += __shfl_xor(part, 1, 64);
-        if (hh == 0) ub[cur ^ 1][ui] = part + vc;
-        if (more) {
-            stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
-            vc = vpre;
-        }
+        q.multiply(cur);
+        const float y = q.apply(cur);
+        if (q.lane < 32) sm.ub[cur ^ 1][ui] = y + vc;
+        if (more) q.stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
         __syncthreads();
-        cur ^= 1;
     }
-    float *q = gq + ((size_t)b * ngroups + j) * BG * BG;
-#pragma unroll
-    for (int I = 0; I < 8; ++I)
-#pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) q[(16 * I + 4 * g + r) * BG + 32 * wv + 16 * Jt + c] = acc[I][Jt][r];
-    if (tid < BG) gu[((size_t)b * ngroups + j) * BG + tid] = ub[cur][tid];
+    q.store(gq + ((size_t)b * ngroups + j) * BG * BG);
+    if (tid < BG) gu[((size_t)b * ngroups + j) * BG + tid] = sm.ub[cur][tid];
 }
 
 // MODE 0: Newton fix-up (next iterate = current + Delta, per-chain max |Delta| and max |z|);
@@ -610,35 +705,81 @@ __global__ __launch_bounds__(256) void k_resjac_big(const ShArgs a, const float 
     }
 }
 
-// J~_s = Cd (or diag(A p)) + W1 diag(m_s) V with V = W2 diag(p) (or the given W2 P): one row at a
-// time per block, the blocks walking the rows, wave wv computes the column tiles 2 wv, 2 wv + 1 of all 8 row tiles.  LDS: W1 [BG][LP],
-// V^T [BG][LP], zero padded (LP = L rounded up to 16).
-template <bool ROW4>
-__global__ __launch_bounds__(256) void k_jacform_big(const ShArgs a, const uint32_t *__restrict__ masks,
+// J~_s = Cd (or diag(A p)) + W1 diag(m_s) V with V = W2 diag(p) (or the given W2 P), on the fp16
+// matrix cores with split operands (W1 and V scaled by their largest entries): one row at a time per
+// block, the blocks walking the rows, wave wv computes the column tiles 2 wv, 2 wv + 1 of all 8 row
+// tiles.  KB = blocks of 32 hidden units; lane group g takes units 32 kk + 8 g .. + 7 of a block.  W1's
+// halves are shared through LDS, a wave's columns of V stay in registers, and a step's mask clears
+// half-words of V.  M = 128, L = 50, 8192 rows: 97 us, near the 537 MB written (78 us at
+// the rate of a fill); 187 us with fp32 instructions and stores of 64 bytes of 16 rows.  Two waves a
+// SIMD are needed: 189 us with one (256 VGPRs and more).
+template <bool ROW4, int KB>
+__global__ __launch_bounds__(256, 2) void k_jacform_big(const ShArgs a, const uint32_t *__restrict__ masks,
                                                      float *__restrict__ Jout, const int *__restrict__ active,
-                                                     const float *__restrict__ gamma, int LP) {
-    extern __shared__ __align__(16) float smem[];
+                                                     const float *__restrict__ gamma) {
+    __shared__ __align__(16) v4u w1s[8][KB][2][64];   // [row tile][k block][hi, lo][lane]
+    __shared__ float mxs[4][2];
     const int M = a.M, L = a.L, T = a.T, N = a.N;
-    float *w1s = smem, *vts = smem + BG * LP;
     const int tid = threadIdx.x;
     const float p1 = __fsub_rn(1.0f, a.alpha);
-    for (int e = tid; e < BG * LP; e += 256) {
-        const int i = e / LP, l = e % LP;
-        const bool in = i < M && l < L;
-        w1s[e] = in ? a.W1[(size_t)i * L + l] : 0.f;
-        vts[e] = in ? a.W2[(size_t)l * M + i] * (i < N ? p1 : 1.f) : 0.f;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
+    const float m1 = opaque_m1();
+    v4u vh[2][KB], vl[2][KB];
+    int sc;
+    {
+        float x1 = 0.f, x2 = 0.f;   // largest finite entries
+        for (int e = tid; e < M * L; e += 256) {
+            const float w1 = fabsf(a.W1[e]), w2 = fabsf(a.W2[e]);
+            x1 = fmaxf(x1, w1 < __builtin_inff() ? w1 : 0.f);
+            x2 = fmaxf(x2, w2 < __builtin_inff() ? w2 : 0.f);
+        }
+        x1 = __uint_as_float(wave_max_u32(__float_as_uint(x1)));
+        x2 = __uint_as_float(wave_max_u32(__float_as_uint(x2)));
+        if (lane == 0) {
+            mxs[wv][0] = x1;
+            mxs[wv][1] = x2;
+        }
+        __syncthreads();
+        x1 = fmaxf(fmaxf(mxs[0][0], mxs[1][0]), fmaxf(mxs[2][0], mxs[3][0]));
+        x2 = fmaxf(fmaxf(mxs[0][1], mxs[1][1]), fmaxf(mxs[2][1], mxs[3][1]));
+        const int s1 = min(13 - exp_of(x1), 126), s2 = min(13 - exp_of(x2), 126);   // W2 bounds V (0 <= p <= 1)
+        sc = -(s1 + s2);
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            auto put = [&](auto get, v4u &hi, v4u &lo) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t h2, l2;
+                    split_pair(get(32 * kk + 8 * g + 2 * i), get(32 * kk + 8 * g + 2 * i + 1), m1, h2, l2);
+                    hi[i] = h2;
+                    lo[i] = l2;
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int r = 16 * (2 * wv + u) + c;   // a row of W1, a column of V
+                v4u hi, lo;
+                put([&](int l) { return r < M && l < L ? ldexpf(a.W1[(size_t)r * L + l], s1) : 0.f; }, hi, lo);
+                w1s[2 * wv + u][kk][0][lane] = hi;
+                w1s[2 * wv + u][kk][1][lane] = lo;
+                put([&](int l) { return r < M && l < L ? ldexpf(a.W2[(size_t)l * M + r] * (r < N ? p1 : 1.f), s2) : 0.f; },
+                    vh[u][kk], vl[u][kk]);
+            }
+        }
     }
     __syncthreads();
-    const int wv = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
     const int LW = (L + 31) / 32;
+    const float f1 = ldexpf(1.f, sc / 2), f2 = ldexpf(1.f, sc - sc / 2);   // two factors: the scales may meet 2^252
     const auto cd_rs = bounded_rsrc(a.Cd, a.Cd ? (uint32_t)M * M * 4u : 0u);
-    // diagonal A p of rows 16 I + c (the transposed-tile stores)
-    float dgI[8];
+    // diagonal A p of rows 16 I + 8 u + c % 8 (the transposed-tile stores)
+    float dgI[8][2];
 #pragma unroll
-    for (int I = 0; I < 8; ++I) {
-        const int i = 16 * I + c;
-        dgI[I] = (ROW4 && !a.Cd && i < M) ? a.A[i] * (i < N ? p1 : 1.f) : 0.f;
-    }
+    for (int I = 0; I < 8; ++I)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = 16 * I + 8 * u + (c & 7);
+            dgI[I][u] = (ROW4 && !a.Cd && i < M) ? a.A[i] * (i < N ? p1 : 1.f) : 0.f;
+        }
     const int t_lo = a.t_hi > a.t_lo ? a.t_lo : 0;
     const int len = a.t_hi > a.t_lo ? a.t_hi - a.t_lo : T;
     const long rows = (long)a.B * len;
@@ -666,57 +807,83 @@ __global__ __launch_bounds__(256) void k_jacform_big(const ShArgs a, const uint3
         for (int I = 0; I < 8; ++I)
 #pragma unroll
             for (int Jt = 0; Jt < 2; ++Jt) acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
-        for (int j = 0; j < LP / 16; ++j) {
-            const int sh = 16 * (j & 1) + 4 * g;
-            const uint32_t w = j < 2 ? wc0 : wc1;
-            float4 bv[2];
+        v4u bh[2][KB], bl[2][KB];
 #pragma unroll
-            for (int Jt = 0; Jt < 2; ++Jt) {
-                const float4 t4 = *reinterpret_cast<const float4 *>(vts + (32 * wv + 16 * Jt + c) * LP + 16 * j + 4 * g);
-                bv[Jt] = make_float4(select_bit(w, sh, t4.x), select_bit(w, sh + 1, t4.y), select_bit(w, sh + 2, t4.z),
-                                     select_bit(w, sh + 3, t4.w));
-            }
+        for (int kk = 0; kk < KB; ++kk) {
+            const int by = (int)((kk ? wc1 : wc0) >> (8 * g));
 #pragma unroll
-            for (int I = 0; I < 8; ++I) {
-                const float4 av = *reinterpret_cast<const float4 *>(w1s + (16 * I + c) * LP + 16 * j + 4 * g);
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t e0 = (uint32_t)((by << (31 - 2 * i)) >> 31), e1 = (uint32_t)((by << (30 - 2 * i)) >> 31);
+                const uint32_t m = (e0 & 0xffffu) | (e1 & 0xffff0000u);
 #pragma unroll
                 for (int Jt = 0; Jt < 2; ++Jt) {
-                    v4f t = acc[I][Jt];
-                    if (ROW4) {   // the transposed tile: V^T diag(m) W1^T
-                        t = mfma16x16x4(bv[Jt].x, av.x, t);
-                        t = mfma16x16x4(bv[Jt].y, av.y, t);
-                        t = mfma16x16x4(bv[Jt].z, av.z, t);
-                        t = mfma16x16x4(bv[Jt].w, av.w, t);
-                    } else {
-                        t = mfma16x16x4(av.x, bv[Jt].x, t);
-                        t = mfma16x16x4(av.y, bv[Jt].y, t);
-                        t = mfma16x16x4(av.z, bv[Jt].z, t);
-                        t = mfma16x16x4(av.w, bv[Jt].w, t);
-                    }
-                    acc[I][Jt] = t;
+                    bh[Jt][kk][i] = vh[Jt][kk][i] & m;
+                    bl[Jt][kk][i] = vl[Jt][kk][i] & m;
                 }
             }
         }
+#pragma unroll
+        for (int I0 = 0; I0 < 8; I0 += 4)
+#pragma unroll
+            for (int kk = 0; kk < KB; ++kk) {
+                v4u ah[4], al[4];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    ah[n] = w1s[I0 + n][kk][0][lane];
+                    al[n] = w1s[I0 + n][kk][1][lane];
+                }
+                // ROW4: the transposed tile, V^T diag(m) W1^T
+                auto mul = [&](const v4u (&w)[4], const v4u (&v)[2][KB]) {
+#pragma unroll
+                    for (int n = 0; n < 4; ++n)
+#pragma unroll
+                        for (int Jt = 0; Jt < 2; ++Jt)
+                            acc[I0 + n][Jt] = ROW4 ? mfma_h(v[Jt][kk], w[n], acc[I0 + n][Jt])
+                                                   : mfma_h(w[n], v[Jt][kk], acc[I0 + n][Jt]);
+                };
+                mul(al, bh);
+                mul(ah, bl);
+                mul(ah, bh);
+            }
+#pragma unroll
+        for (int I = 0; I < 8; ++I)
+#pragma unroll
+            for (int Jt = 0; Jt < 2; ++Jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[I][Jt][r] = acc[I][Jt][r] * f1 * f2;
         // stores through a resource bounded at J~_s's end: rows past M fall outside it, columns
         // past M take an offset outside it
         const auto rs = bounded_rsrc(Jout + (size_t)grow * M * M, (uint32_t)M * M * 4u);
         const float gm = gamma ? gamma[bb] : 1.f;
         if (ROW4) {
-            // acc[I][Jt][r] = J~[16 I + c][32 wv + 16 Jt + 4 g + r]: one 16-byte store per tile (with
-            // M % 4 == 0 the four columns are all inside the row or all past it)
+            // acc[I][Jt][r] = J~[16 I + c][32 wv + 16 Jt + 4 g + r].  Lanes c and c ^ 8 exchange a tile, so
+            // that a store takes all 32 columns (128 bytes) of eight rows: store u rows 16 I + 8 u + c % 8,
+            // lane columns 32 wv + 16 (c / 8) + 4 g .. + 3 (with M % 4 == 0 the four are all inside the
+            // row or all past it)
+            const bool up = c >= 8;
+            const int col0 = 32 * wv + (up ? 16 : 0) + 4 * g;
+            const uint32_t vo = col0 < M ? 4u * (uint32_t)((c & 7) * M + col0) : kOffLane;
 #pragma unroll
-            for (int Jt = 0; Jt < 2; ++Jt) {
-                const int col0 = 32 * wv + 16 * Jt + 4 * g;
-                const uint32_t vo = col0 < M ? 4u * (uint32_t)(c * M + col0) : kOffLane;
+            for (int I = 0; I < 8; ++I) {
+                float st[2][4];
 #pragma unroll
-                for (int I = 0; I < 8; ++I) {
-                    const uint32_t vr = vo + 4u * (uint32_t)M * (uint32_t)(16 * I);
-                    const int dr = 16 * I + c - col0;   // the diagonal entry's column in the four
-                    float4 d = make_float4(dr == 0 ? dgI[I] : 0.f, dr == 1 ? dgI[I] : 0.f, dr == 2 ? dgI[I] : 0.f,
-                                           dr == 3 ? dgI[I] : 0.f);
+                for (int r = 0; r < 4; ++r) {
+                    const float give = up ? acc[I][0][r] : acc[I][1][r];
+                    const float got = __int_as_float(
+                        __builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xF, 0xF, true));   // row_ror:8
+                    st[0][r] = up ? got : acc[I][0][r];
+                    st[1][r] = up ? acc[I][1][r] : got;
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int row = 16 * I + 8 * u + (c & 7);
+                    const uint32_t vr = vo + 4u * (uint32_t)M * (uint32_t)(16 * I + 8 * u);
+                    const int dr = row - col0;   // the diagonal entry's column in the four
+                    const float dg = dgI[I][u];
+                    float4 d = make_float4(dr == 0 ? dg : 0.f, dr == 1 ? dg : 0.f, dr == 2 ? dg : 0.f, dr == 3 ? dg : 0.f);
                     if (a.Cd) d = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(cd_rs, (int)vr, 0, 0));
-                    const float4 o = make_float4(gm * (acc[I][Jt][0] + d.x), gm * (acc[I][Jt][1] + d.y),
-                                                 gm * (acc[I][Jt][2] + d.z), gm * (acc[I][Jt][3] + d.w));
+                    const float4 o = make_float4(gm * (st[u][0] + d.x), gm * (st[u][1] + d.y), gm * (st[u][2] + d.z),
+                                                 gm * (st[u][3] + d.w));
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o), rs, (int)vr, 0, 0);
                 }
             }
@@ -911,7 +1078,6 @@ int launch_fixup_big(int mode, bool flip, int B, int T, int M, const float *J, c
 }
 
 size_t big_resjac_lds(int M, int L) { return (size_t)2 * M * L * sizeof(float); }
-size_t big_jacform_lds(int L) { return (size_t)2 * BG * ((L + 15) / 16 * 16) * sizeof(float); }
 size_t big_grads_lds(int M, int L) { return ((size_t)2 * M * L + 2 * BG + 2 * L) * sizeof(float); }
 
 int launch_resjac_big(const ShArgs &a, const float *z, const float *zalt, const int *zsel, float *F, float *r,
@@ -930,18 +1096,14 @@ int launch_resjac_big(const ShArgs &a, const float *z, const float *zalt, const 
 
 int launch_jacform_big(const ShArgs &a, const uint32_t *masks, float *J, const int *active, const float *gamma,
                        hipStream_t st) {
-    // every block walks rows with W1 and V staged once: as many blocks as the LDS holds (two per CU
-    // at L > 48)
+    // every block walks rows with W1 and V split once: two blocks per CU (the registers of a wave)
     const long rows = (long)a.B * (a.t_hi > a.t_lo ? a.t_hi - a.t_lo : a.T);
-    long per_cu = (long)(160 * 1024) / (long)big_jacform_lds(a.L);
-    per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
-    const int grid = (int)(rows < 256 * per_cu ? rows : 256 * per_cu);
-    const int LP = (a.L + 15) / 16 * 16;
+    const int grid = (int)(rows < 256 * 2 ? rows : 256 * 2);
     KTimer kt("k_jacform_shplrnn", st);
-    if ((a.M & 3) == 0)
-        hipLaunchKernelGGL(k_jacform_big<true>, dim3(grid), dim3(256), big_jacform_lds(a.L), st, a, masks, J, active, gamma, LP);
-    else
-        hipLaunchKernelGGL(k_jacform_big<false>, dim3(grid), dim3(256), big_jacform_lds(a.L), st, a, masks, J, active, gamma, LP);
+#define JFB(R, K) hipLaunchKernelGGL((k_jacform_big<R, K>), dim3(grid), dim3(256), 0, st, a, masks, J, active, gamma)
+    if ((a.M & 3) == 0) { if (a.L > 32) JFB(true, 2); else JFB(true, 1); }
+    else { if (a.L > 32) JFB(false, 2); else JFB(false, 1); }
+#undef JFB
     DEER_LAUNCH_CHECK("k_jacform_big");
     return DEER_OK;
 }

@@ -209,7 +209,6 @@ int launch_fixup_big(int mode, bool flip, int B, int T, int M, const float *J, c
                      const float *carry_in, float *z, float *out, const int *zsel, uint32_t *chain_bits,
                      const int *active, int C, int ncs, hipStream_t st);
 size_t big_resjac_lds(int M, int L);
-size_t big_jacform_lds(int L);
 size_t big_grads_lds(int M, int L);
 int launch_resjac_big(const ShArgs &a, const float *z, const float *zalt, const int *zsel, float *F, float *r,
                       uint32_t *masks, const int *active, hipStream_t st);

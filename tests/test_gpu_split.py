@@ -307,3 +307,33 @@ def test_readout_scales(B, T, M, H, No, kind):
     assert abs(float(out["loss"].cpu()[0]) - loss) <= 1e-5 * loss
     for k in ("Wa", "ca", "Wb", "cb"):
         assert rel_inf(gr[k], ref[k]) < TOL, k
+
+
+@pytest.mark.parametrize("M,B,T,chunk", [(65, 1, 31, 3), (100, 2, 64, 4), (127, 1, 200, 2), (128, 1, 130, 2)])
+@pytest.mark.parametrize("rev", [False, True])
+@pytest.mark.parametrize("tr", [False, True])
+@pytest.mark.parametrize("kind", ["plain", "rows", "small", "zero"])
+def test_wide_scan_scales(M, B, T, chunk, rev, tr, kind):
+    """Widths 65..128: all directions and orientations, with one and two carry levels, last chunks and
+    groups of one, and rows of a matrix (or whole matrices) of very different size."""
+    os.environ["DEER_CHUNK"] = str(chunk)
+    rng = np.random.default_rng(7300 + M)
+    J = rng.standard_normal((B, T, M, M)) * 0.6 / np.sqrt(M)
+    if kind == "rows":
+        J *= 2.0 ** -rng.integers(0, 24, (B, T, M, 1))
+    elif kind == "small":
+        J *= 2.0 ** -rng.integers(0, 60, (B, T, 1, 1))
+    elif kind == "zero":
+        J[:, 1::2] = 0.0
+    J = J.astype(np.float32)
+    b = rng.standard_normal((B, T, M)).astype(np.float32)
+    say("split wide scan", M, B, T, chunk, rev, tr, kind)
+    y = D.deer_scan(0, J, b, reverse=rev, transpose=tr).cpu().numpy()
+    ref = np.empty(b.shape)
+    v = np.zeros((B, M))
+    Jd = J.astype(np.float64).transpose(0, 1, 3, 2) if tr else J.astype(np.float64)
+    for t in (range(T - 1, -1, -1) if rev else range(T)):
+        k = t + 1 if rev else t
+        v = (np.matmul(Jd[:, k], v[..., None])[..., 0] if (0 < k < T) else 0.0) + b[:, t]
+        ref[:, t] = v
+    assert rel_inf(y, ref) < 1e-5
