@@ -35,6 +35,7 @@ sys.path.insert(0, HERE)
 
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 PEAK_FP32_MFMA_TFLOPS = 157.3    # MI355X dense fp32 matrix
+PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 3   # fp32 products as three dense fp16 products of split operands
 # fp32 vector: 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz = 78.6 TFLOP/s.  The
 # published 157.3 counts packed fp32 (two FMAs per lane per instruction); the kernels are built
 # without packed instructions, so 78.6 is the ceiling they can reach and the peak used here.
@@ -119,20 +120,27 @@ def kernel_work(c, steps, updates):
             "k_diag_scan_lb_grads": ("hbm", elems * 12 + xin),
             "k_diag_scan_lb": ("hbm", elems * 12 + xin),
             # read-out: three [rows x 64] x [64 x 128] products (s, g, dWa) on the matrix cores
-            "k_readout": ("mfma", steps * B * T * 3 * 2.0 * M * c.params["Wa"].shape[0]),
+            "k_readout": ("mfma_split", steps * B * T * 3 * 2.0 * M * c.params["Wa"].shape[0]),
         }
     out = {}
     if c.kind == "plrnn":
-        # forward Newton updates run the fused kernel (residual + masks + product); the
-        # adjoint runs the shifted product and a mask pass
-        out["k_newton_product_plrnn"] = ("mfma", fwd * 2.0 * M ** 3)
+        if M <= 16:
+            # forward Newton updates: residual, masks and product in one kernel; the adjoint runs
+            # the shifted product
+            out["k_newton_product_plrnn"] = ("mfma", fwd * 2.0 * M ** 3)
+            out["k_chunk_product_plrnn"] = ("mfma", steps * B * (T - 1) * 2.0 * M ** 3)
+        else:
+            # residual and masks written with the local walk; a chunk's product is formed again
+            # only where its masks or its damping changed, a count that stays on the device
+            out["k_newton_local_plrnn"] = ("hbm", fwd * (8 * M + 4 * N + 4 * W))
+            out["k_chunk_product_split"] = ("mfma_split", None)
+            out["k_chunk_product_split_rev"] = ("mfma_split", steps * B * (T - 1) * 2.0 * M ** 3)
         # M <= 16 with whole blocks of chunks: one kernel per pass (the fix-up of an update and
         # the forward pass of the next); its matrix-core work is the forward pass's
         out["k_newton_pass16"] = ("mfma", fwd * 2.0 * M ** 3)
         # M <= 4 with a fixed update count: the whole solve in one launch on the vector units
         # (the same chunk-map composition, 2 M^3 flops per timestep and update)
         out["k_newton_small"] = ("alu", fwd * 2.0 * M ** 3)
-        out["k_chunk_product_plrnn"] = ("mfma", steps * B * (T - 1) * 2.0 * M ** 3)
         out["k_resjac_plrnn"] = ("hbm", adj * (4 * M + 4 * N + 4 * W))
         # quasi-DEER: residual and diagonal (z, x read; r, d written / adjoint: d written),
         # chunk aggregates (d and r, or d and the seed inputs), fix-ups (forward: d, r, z read
@@ -156,12 +164,14 @@ def kernel_work(c, steps, updates):
     else:
         L = c.L
         LW = (L + 31) // 32
-        out["k_jacform_shplrnn"] = ("mfma", (fwd + adj) * 2.0 * M * M * L)
-        out["k_chunk_product_dense"] = ("mfma", prod * 2.0 * M ** 3)
+        wide = "mfma_split" if M > 64 else "mfma"
+        out["k_jacform_shplrnn"] = (wide, (fwd + adj) * 2.0 * M * M * L)
+        out["k_chunk_product_dense"] = (wide, prod * 2.0 * M ** 3)
         # without a stored Jacobian: J~_t formed (2 M^2 L) and composed (2 M^3) in the chunk
-        # products; two matrix-vector products with W1 and W2 (4 M L) per step in the fix-ups
-        out["k_chunk_product_shfused"] = ("mfma", fwd * (2.0 * M * M * L + 2.0 * M ** 3))
-        out["k_chunk_product_shfused_rev"] = ("mfma", steps * B * (T - 1) * (2.0 * M * M * L + 2.0 * M ** 3))
+        # products (forward: only where a chunk's masks or its damping changed, a count that stays
+        # on the device); two matrix-vector products with W1 and W2 (4 M L) per step in the fix-ups
+        out["k_chunk_aggregates_sh"] = ("mfma_split", None)
+        out["k_chunk_aggregates_sh_rev"] = ("mfma_split", steps * B * (T - 1) * (2.0 * M * M * L + 2.0 * M ** 3))
         out["k_fixup_shjvp"] = ("mfma", fwd * 4.0 * M * L)
         # the Newton passes' residual on the matrix cores: u = W2 z~ and W1 relu(u), 4 M L per step
         out["k_resjac_shmfma"] = ("mfma", fwd * 4.0 * M * L)
@@ -176,8 +186,11 @@ def kernel_work(c, steps, updates):
 # scaled by the reading of a plain copy of known size in the same run; kept in
 # profiles/traffic_<workload>.txt together with the hash of the kernel's source file, and
 # reported only while that source is unchanged.
-KERNEL_SOURCE = {"k_chunk_product_shfused": "k_shfused.hip", "k_chunk_product_shfused_rev": "k_shfused.hip",
-                 "k_fixup_shjvp": "k_shfused.hip", "k_resjac_shmfma": "k_shfused.hip", "k_newton_product_plrnn": "k_plrnn.hip", "k_newton_pass16": "k_plrnn.hip", "k_chunk_product_plrnn": "k_plrnn.hip",
+KERNEL_SOURCE = {"k_chunk_aggregates_sh": "k_shfused.hip", "k_chunk_aggregates_sh_rev": "k_shfused.hip",
+                 "k_fixup_shjvp": "k_shfused.hip", "k_resjac_shmfma": "k_shfused.hip",
+                 "k_newton_product_plrnn": "k_plrnn.hip", "k_newton_pass16": "k_plrnn.hip",
+                 "k_chunk_product_plrnn": "k_plrnn.hip", "k_newton_local_plrnn": "k_split.hip",
+                 "k_chunk_product_split": "k_split.hip", "k_chunk_product_split_rev": "k_split.hip",
                  "k_fixup_fwd_plrnn": "k_plrnn.hip", "k_jacform_shplrnn": "k_shallow.hip",
                  "k_chunk_product_dense": "k_dense.hip", "k_readout": "k_readout.hip",
                  "k_diag_scan_lb_grads": "k_diag.hip", "k_diag_seg_write": "k_diag.hip",
@@ -237,7 +250,13 @@ def roofline_for(name, c, total_ms, launches, steps, updates):
         base.update({"bound": "unknown", "achieved": None, "peak": None, "unit": None, "frac": None})
         return base
     bound, w = work[name]
-    if bound == "mfma":
+    if w is None:
+        base.update({"bound": bound, "achieved": None, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": None})
+    elif bound == "mfma_split":
+        ach = w / (total_ms * 1e-3) / 1e12
+        base.update({"bound": bound, "achieved": ach, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
+                     "frac": ach / PEAK_SPLIT_MFMA_TFLOPS, "work_per_launch": w / launches})
+    elif bound == "mfma":
         ach = w / (total_ms * 1e-3) / 1e12
         base.update({"bound": "mfma", "achieved": ach, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": ach / PEAK_FP32_MFMA_TFLOPS, "work_per_launch": w / launches,
