@@ -120,7 +120,7 @@ def kernel_work(c, steps, updates):
             "k_diag_scan_lb_grads": ("hbm", elems * 12 + xin),
             "k_diag_scan_lb": ("hbm", elems * 12 + xin),
             # read-out: three [rows x 64] x [64 x 128] products (s, g, dWa) on the matrix cores
-            "k_readout": ("mfma_split", steps * B * T * 3 * 2.0 * M * c.params["Wa"].shape[0]),
+            "k_readout": ("mfma", steps * B * T * 3 * 2.0 * M * c.params["Wa"].shape[0]),
         }
     out = {}
     if c.kind == "plrnn":

@@ -1,0 +1,108 @@
+"""Latents, hidden units and channels in units of their own.
+
+A diagonal change of variables by powers of two is exact in float32, so a path whose operands, products
+and sums keep float32's precision and range returns the same bits in the new units (times the units),
+whatever the units' spread.  And matrices whose products are exact in float32 (24-bit entries times
+powers of two) come out exact."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2605_12683_amd as D  # noqa: E402
+from gpu_util import oracle_model, rel_inf, say  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-4   # the project's normwise tolerance
+SPREADS = [8, 24, 40]   # bits between the smallest and the largest unit
+
+
+@pytest.fixture(autouse=True)
+def _chunk():
+    os.environ.pop("DEER_CHUNK", None)
+    yield
+    os.environ.pop("DEER_CHUNK", None)
+
+
+def _units(n, bits, rng):
+    """n powers of two over `bits` bits, permuted."""
+    e = np.round(np.linspace(-bits / 2, bits / 2, n)).astype(int)
+    return (2.0 ** rng.permutation(e)).astype(np.float32)
+
+
+def _np(t):
+    return t.cpu().numpy()
+
+
+def _mant(n, rng):
+    """n floats 1 + k 2^-23 with odd k: all 24 bits of the significand in use."""
+    return (1.0 + (2.0 * rng.integers(1 << 18, 1 << 22, n) + 1.0) * 2.0 ** -23).astype(np.float32)
+
+
+# ---- read-out of the diagonal SSM ---------------------------------------------------------------
+
+def test_readout_decisions_to_the_last_bit():
+    """s = h_0 - h_1 with h_0 the float after h_1: exact in float32, one unit in the last place above
+    zero, so the hidden unit is on (and off the other way round)."""
+    B, T, M, H = 2, 200, 64, 128
+    rng = np.random.default_rng(1)
+    p = {"Wa": np.zeros((H, M), np.float32), "ca": np.zeros(H, np.float32),
+         "Wb": rng.standard_normal((3, H)).astype(np.float32), "cb": np.zeros(3, np.float32)}
+    i, j = 2 * rng.integers(0, M // 2, H), 2 * rng.integers(0, M // 2, H) + 1
+    p["Wa"][np.arange(H), i], p["Wa"][np.arange(H), j] = 1.0, -1.0
+    lo = (rng.integers(1 << 23, (1 << 24) - 1, (B, T, 1)) + np.zeros((1, 1, M))).astype(np.float32)
+    up = rng.random((B, T, M)) < 0.5
+    h = np.where(up, np.nextafter(lo, np.float32(np.inf)), lo).astype(np.float32)
+    x = rng.standard_normal((B, T + 1, 3)).astype(np.float32)
+    say("units readout decisions")
+    out = D.deer_readout_loss(p, torch.tensor(h.astype(np.complex64)), x, want_masks=True)
+    mk = _np(out["masks"]).view(np.uint32).reshape(B, T, -1)
+    on = ((mk[..., :, None] >> np.arange(32, dtype=np.uint32)) & 1).astype(bool).reshape(B, T, -1)[..., :H]
+    assert np.array_equal(on, up[..., i] & ~up[..., j])
+
+
+@pytest.mark.parametrize("bits", SPREADS)
+@pytest.mark.parametrize("M,H", [(64, 128), (37, 50)])
+def test_readout_channel_units(M, H, bits):
+    B, T, K = 2, 1100, 3
+    rng = np.random.default_rng(M)
+    p = {"Wa": rng.standard_normal((H, M)) / np.sqrt(M), "ca": 0.1 * rng.standard_normal(H),
+         "Wb": rng.standard_normal((K, H)) / np.sqrt(H), "cb": 0.1 * rng.standard_normal(K)}
+    p = {k: v.astype(np.float32) for k, v in p.items()}
+    h = (rng.standard_normal((B, T, M)) + 1j * rng.standard_normal((B, T, M))).astype(np.complex64)
+    x = rng.standard_normal((B, T + 1, K)).astype(np.float32)
+    d, e = _units(M, bits, rng), _units(H, bits, rng)
+    q = {"Wa": e[:, None] * p["Wa"] / d, "ca": e * p["ca"], "Wb": p["Wb"] / e, "cb": p["cb"]}
+    say("units readout", M, H, bits)
+    a, b = D.deer_readout_loss(p, torch.tensor(h), x), D.deer_readout_loss(q, torch.tensor(h * d), x)
+    assert torch.equal(a["loss"], b["loss"])
+    assert np.array_equal(_np(a["g"]), _np(b["g"]) * d)
+    for k, s in (("Wa", d[None, :] / e[:, None]), ("ca", 1 / e), ("Wb", e), ("cb", 1.0)):
+        assert np.array_equal(_np(a["grads"][k]) * s, _np(b["grads"][k])), k
+
+
+@pytest.mark.parametrize("bits", [12, 18])
+def test_readout_rows_of_opposite_size(bits):
+    """Large states where the error is small and small ones where it is large: every row counts alike
+    in dWa.  Every unit is on with relu = 1, so y and the errors are exact."""
+    B, T, M, H = 1, 640, 64, 128
+    rng = np.random.default_rng(bits)
+    p = {"Wa": np.zeros((H, M), np.float32), "ca": np.ones(H, np.float32),
+         "Wb": (rng.integers(-3, 4, (2, H)) / 64).astype(np.float32), "cb": np.zeros(2, np.float32)}
+    k = rng.integers(0, bits + 1, T)
+    err = rng.integers(1, 4, (T, 2)) * rng.choice([-1.0, 1.0], (T, 2)) * 2.0 ** -k[:, None]
+    x = np.zeros((B, T + 1, 2), np.float32)
+    x[0, 1:] = p["Wb"].sum(1) - err
+    h = (rng.standard_normal((B, T, M)) * 2.0 ** k[:, None]).astype(np.float32)
+    say("units readout rows", bits)
+    out = D.deer_readout_loss(p, torch.tensor(h.astype(np.complex64)), x)
+    ref = O.diag_ssm_loss_and_seed(p, h.astype(np.complex64), x)[2]
+    # fp32 sums of 640 terms of like size
+    assert rel_inf(_np(out["grads"]["Wa"]), ref["Wa"]) < 1e-5
