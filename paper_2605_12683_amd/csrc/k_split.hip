@@ -5,7 +5,7 @@
 //                          solution v_c (from a zero carry), 16 chunks as matrix-core columns;
 //                          says which chunks' masks changed since the pass before
 //   k_chunk_product_split  P_c = J~_e ... J~_s of a chunk from the masks, J~_t = gamma (diag(A) +
-//                          W diag(m_t)) diag(p), on the fp16 matrix cores with split operands
+//                          W diag(m_t)) diag(p), on the bf16 matrix cores with split operands
 //   k_adjoint_walk_plrnn   the adjoint down a chunk: its local solution and the masks, or from the
 //                          carry the adjoint and the parameter gradients
 //
@@ -239,98 +239,75 @@ __global__ __launch_bounds__(MP * 4) void k_newton_local_plrnn(
 // instruction numbered k = 32 kk + 16 (e >> 2) + 4 g + (e & 3) (e the slot within the lane) these
 // accumulators, split, are the next step's B operand: no data moves between lanes.
 //
-// A operand: gamma (W + diag A) diag(p), scaled by 2^s (largest entry in [2^9, 2^10)) and split
-// once, kept in LDS (MP = 64; 16 KB) or registers; per step the columns whose ReLU is off are
-// cleared, the diagonal keeping A (v_bfi between the two).
-// B operand: column j of P carries its own power of two 2^E[j].  Every step multiplies by 2^-(s+q),
-// 2^q at least the largest absolute row sum of gamma (W + diag A) diag(p), so no entry can grow
-// out of fp16's range whatever the masks are; every KR steps (fewer where 2^q is large) the
-// column is brought to a norm in [2^13, 2^14) instead.
+// A operand: gamma (W + diag A) diag(p), formed in float64 and split once, in LDS (MP = 64: 24 KB,
+// shared by the four chunks of a block, all of one sequence and so of one damping); per step the
+// columns whose ReLU is off are cleared, the diagonal keeping A (v_bfi between the two).
 //
-// Per step at M = 64: 96 matrix instructions (0.76 us on a SIMD) and about 280 vector ones
-// (conversion of 4096 entries, masks; issued one after the other, the matrix cores and the vector
-// units of a SIMD do not overlap), where fp32 matrix instructions took 256 (3.55 us).  M = 64,
-// 32 x 131072 steps: 5.6 ms for every chunk against 15.6 ms in fp32 with the residual in the same
-// kernel; with the products that are kept, 33 ms against 140 ms for the passes of a solve of
-// nine updates.
+// Per step at M = 64: 192 matrix instructions (1.52 us on a SIMD) and about 490 vector ones
+// (splitting 4096 entries, masks), where fp32 matrix instructions took 256 (3.55 us).  M = 64,
+// 32 x 131072 steps: 8.4 ms for every chunk (2.05 us a step on a SIMD; 20.3 ms in fp32 with the local
+// solution in the same kernel), and with the products that are kept 50 ms for the nine passes of a
+// solve (125 ms for eight passes in fp32).
 // REV: the adjoint's range, J~_{hi-1} ... J~_{s0+1}, hi = min(s1 + 1, T).
 // ---------------------------------------------------------------------------------------
+template <int MP>
+constexpr int kSplitWaves = MP == 64 ? 4 : 1;   // chunks per block
+
 template <int MP, bool REV, bool WU>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_product_split(
+__global__ __launch_bounds__(kSplitWaves<MP> * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_product_split(
     const float *__restrict__ A, const float *__restrict__ W, float alpha, int N, const uint32_t *__restrict__ masks,
     const int *__restrict__ changed, float *__restrict__ pgam, float *__restrict__ Pout, const int *__restrict__ active,
     const float *__restrict__ gamma, int B, int T, int M, int C, int ncs, int tw) {
-    constexpr int NI = MP / 16, KK = MP / 32, MW = MP / 32;
-    __shared__ __align__(16) v4u wls[NI][KK][2][64];   // [row tile][k block][hi, lo][lane]
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int id = blockIdx.x;
-    const int b = id / ncs, s0 = (id % ncs) * C;
+    constexpr int NI = MP / 16, KK = MP / 32, MW = MP / 32, NW = kSplitWaves<MP>;
+    constexpr int IB = MP == 32 ? 2 : 1;   // row tiles formed together: four independent sums
+    __shared__ __align__(16) v4u wls[NI][KK][3][64];   // [row tile][k block][hi, mid, lo][lane]
+    __shared__ __align__(16) uint2 dls[NI][3][64];     // diag A alone: slots 0..3 of k tile I, for rows whose ReLU is off
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int nb = (ncs + NW - 1) / NW;
+    const int b = blockIdx.x / nb, cc = (int)(blockIdx.x % nb) * NW + wv;
     if (active && !active[b]) return;
+    const int id = b * ncs + cc, s0 = cc * C;
     const float gm = gamma ? gamma[b] : 1.f;
-    // the stored product is that of these masks and this damping
-    if (!REV && changed && !changed[id] && pgam[id] == gm) return;
-    const int s1 = min(s0 + C, T);
-    const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
-    const int len = __builtin_amdgcn_readfirstlane(hi - lo);
-    const float m1 = opaque_m1();
-
-    // scale of the A operand and the row-sum bound
-    float wf[NI][NI][4], ad[NI];
-    float wmax = 0.f, rsum = 0.f;
-#pragma unroll
-    for (int I = 0; I < NI; ++I) {
+    // kept: the stored product is that of these masks and this damping
+    const bool todo = cc < ncs && (REV || !changed || changed[id] || pgam[id] != gm);
+    if constexpr (NW > 1) {
+        if (!__syncthreads_or(todo)) return;
+    } else {
+        if (!todo) return;
+    }
+    for (int I = wv; I < NI; I += NW) {
         const int row = 16 * I + c;
-        ad[I] = row < M ? A[row] * (gm * sp_p(row, N, alpha)) : 0.f;
-        float rs = 0.f;
+        const double ad = row < M ? (double)A[row] * gm * sp_p(row, N, alpha) : 0.0;
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = 16 * j + 4 * g + q;
-                const float w = (row < M && k < M) ? W[row * M + k] * (gm * sp_p(k, N, alpha)) : 0.f;
-                wf[I][j][q] = (k == row) ? w + ad[I] : w;
-                wmax = fmaxf(wmax, fabsf(wf[I][j][q]));
-                rs += fabsf(w);
+            for (int h2 = 0; h2 < 2; ++h2) {
+                double w[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int k = 16 * j + 4 * g + 2 * h2 + e;
+                    w[e] = (row < M && k < M) ? (double)W[row * M + k] * gm * sp_p(k, N, alpha) : 0.0;
+                    w[e] += k == row ? ad : 0.0;
+                }
+                uint32_t part[3];
+                split_pair_f64(w[0], w[1], part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) reinterpret_cast<uint32_t *>(&wls[I][j >> 1][q][lane])[2 * (j & 1) + h2] = part[q];
             }
-        rs += __shfl_xor(rs, 16, 64);
-        rs += __shfl_xor(rs, 32, 64);
-        rsum = fmaxf(rsum, rs + fabsf(ad[I]));
-        wmax = fmaxf(wmax, fabsf(ad[I]));
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        wmax = fmaxf(wmax, __shfl_xor(wmax, off, 64));
-        rsum = fmaxf(rsum, __shfl_xor(rsum, off, 64));
-    }
-    const int sc = __builtin_amdgcn_readfirstlane(min(9 - exp_of(wmax), 100));
-    const int qe = __builtin_amdgcn_readfirstlane(max(exp_of(rsum) + 1, -20));
-    const int kr = qe <= 3 ? 4 : qe <= 6 ? 2 : 1;
-    const float fplain = pow2i(max(-(sc + qe), -126));
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            v4u hv, lv;
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                uint32_t ph, pl;
-                const float *w4 = wf[I][2 * kk + (e2 >> 1)];
-                split_pair(ldexpf(w4[2 * (e2 & 1)], sc), ldexpf(w4[2 * (e2 & 1) + 1], sc), m1, ph, pl);
-                hv[e2] = ph;
-                lv[e2] = pl;
-            }
-            wls[I][kk][0][lane] = hv;
-            wls[I][kk][1][lane] = lv;
-        }
-    // A alone, for the diagonal of a row whose ReLU is off: pair h holds slots q = 2 h, 2 h + 1
-    uint32_t dgh[NI][2], dgl[NI][2];
-#pragma unroll
-    for (int I = 0; I < NI; ++I)
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
-            const float d = ldexpf(ad[I], sc);
-            split_pair(c == 4 * g + 2 * h2 ? d : 0.f, c == 4 * g + 2 * h2 + 1 ? d : 0.f, m1, dgh[I][h2], dgl[I][h2]);
+            uint32_t part[3];
+            split_pair_f64(c == 4 * g + 2 * h2 ? ad : 0.0, c == 4 * g + 2 * h2 + 1 ? ad : 0.0, part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) reinterpret_cast<uint32_t *>(&dls[I][q][lane])[h2] = part[q];
         }
+    }
+    if constexpr (NW > 1) __syncthreads();
+    else wave_lds_sync();
+    if (!todo) return;
+    const int s1 = min(s0 + C, T);
+    const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
+    const int len = __builtin_amdgcn_readfirstlane(hi - lo);
     // columns kept in a latent warm-up step (P_1 drops the observed ones)
     uint32_t om[NI][2];
     if constexpr (WU) {
@@ -342,18 +319,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
                 om[j][h2] = (k < N ? 0u : 0xffffu) | (k + 1 < N ? 0u : 0xffff0000u);
             }
     }
-    wave_lds_sync();
 
     v4f acc[NI][NI];
-    int E[NI];
 #pragma unroll
-    for (int Jt = 0; Jt < NI; ++Jt) {
-        E[Jt] = 0;
+    for (int Jt = 0; Jt < NI; ++Jt)
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 16 * Jt + c) ? 1.f : 0.f;
-    }
     // mask words of 64 steps at a time, one step per lane, the next 64 in flight
     const size_t rowm = (size_t)b * T + lo;
     uint32_t mc[MW], mn[MW];
@@ -369,33 +342,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
             fetch(t + 64);
         }
         // P to the B operand
-        v4u bh[KK][NI], bl[KK][NI];
-        const bool renorm = (t & (kr - 1)) == 0;
+        v4u bq[3][KK][NI];
 #pragma unroll
-        for (int Jt = 0; Jt < NI; ++Jt) {
-            float f = fplain;
-            if (renorm) {
-                float m2 = 0.f;
-#pragma unroll
-                for (int I = 0; I < NI; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) m2 = fmaf(acc[I][Jt][r], acc[I][Jt][r], m2);
-                const int ph = norm_shift(group_sum(m2));
-                f = pow2i(ph);
-                E[Jt] -= ph + sc;
-            } else {
-                E[Jt] += qe;
-            }
+        for (int Jt = 0; Jt < NI; ++Jt)
 #pragma unroll
             for (int I = 0; I < NI; ++I)
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
-                    uint32_t ph, pl;
-                    split_pair(acc[I][Jt][2 * h2] * f, acc[I][Jt][2 * h2 + 1] * f, m1, ph, pl);
-                    bh[I >> 1][Jt][2 * (I & 1) + h2] = ph;
-                    bl[I >> 1][Jt][2 * (I & 1) + h2] = pl;
+                    uint32_t part[3];
+                    split_pair(acc[I][Jt][2 * h2], acc[I][Jt][2 * h2 + 1], part);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) bq[q][I >> 1][Jt][2 * (I & 1) + h2] = part[q];
                 }
-        }
         // all ones in the half of each slot whose ReLU is on
         uint32_t pm[NI][2];
 #pragma unroll
@@ -422,39 +380,49 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
                 }
         }
 #pragma unroll
-        for (int I = 0; I < NI; ++I) {
-            v4u ah[KK], al[KK];
+        for (int I0 = 0; I0 < NI; I0 += IB) {
+            __builtin_amdgcn_sched_barrier(0);   // else the next tile's operands are formed early and spill
+            v4f s[IB][NI];
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const v4u wh = wls[I][kk][0][lane], wl = wls[I][kk][1][lane];
+            for (int n = 0; n < IB; ++n)
 #pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int j = 2 * kk + (e2 >> 1), h2 = e2 & 1;
-                    uint32_t dh = 0u, dl = 0u;
-                    if (j == I) {
-                        dh = WU ? dgh[I][h2] & keep[j][h2] : dgh[I][h2];
-                        dl = WU ? dgl[I][h2] & keep[j][h2] : dgl[I][h2];
+                for (int Jt = 0; Jt < NI; ++Jt) s[n][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
+            v4u aq[IB][KK][3];
+#pragma unroll
+            for (int n = 0; n < IB; ++n)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int I = I0 + n;
+                    const uint2 d2 = dls[I][q][lane];
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) {
+                        const v4u w = wls[I][kk][q][lane];
+#pragma unroll
+                        for (int e2 = 0; e2 < 4; ++e2) {
+                            const int j = 2 * kk + (e2 >> 1), h2 = e2 & 1;
+                            uint32_t d = 0u;
+                            if (j == I) {
+                                d = h2 ? d2.y : d2.x;
+                                if (WU) d &= keep[j][h2];
+                            }
+                            aq[n][kk][q][e2] = (pm[j][h2] & w[e2]) | (~pm[j][h2] & d);
+                        }
                     }
-                    ah[kk][e2] = (pm[j][h2] & wh[e2]) | (~pm[j][h2] & dh);
-                    al[kk][e2] = (pm[j][h2] & wl[e2]) | (~pm[j][h2] & dl);
                 }
-            }
-            v4f s[NI];
 #pragma unroll
-            for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
+            for (int o = 2; o >= 0; --o)   // parts (qa, qb) of one order of magnitude, the smallest first
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
+                for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(al[kk], bh[kk][Jt], s[Jt]);
+                    for (int qa = o; qa >= 0; --qa)
 #pragma unroll
-                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(ah[kk], bl[kk][Jt], s[Jt]);
-            }
+                        for (int n = 0; n < IB; ++n)
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk)
+                            for (int Jt = 0; Jt < NI; ++Jt) s[n][Jt] = mfma_b(aq[n][kk][qa], bq[o - qa][kk][Jt], s[n][Jt]);
 #pragma unroll
-                for (int Jt = 0; Jt < NI; ++Jt) s[Jt] = mfma_h(ah[kk], bh[kk][Jt], s[Jt]);
+            for (int n = 0; n < IB; ++n)
 #pragma unroll
-            for (int Jt = 0; Jt < NI; ++Jt) acc[I][Jt] = s[Jt];
+                for (int Jt = 0; Jt < NI; ++Jt) acc[I0 + n][Jt] = s[n][Jt];
         }
     }
     float *P = Pout + (size_t)id * MP * MP;
@@ -463,7 +431,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * Jt + c] = ldexpf(acc[I][Jt][r], E[Jt]);
+            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * Jt + c] = acc[I][Jt][r];
     if (!REV && pgam && lane == 0) pgam[id] = gm;
 }
 
@@ -785,11 +753,11 @@ int launch_adjoint_walk_plrnn(const PlrnnArgs &a, bool fin, const float *g, floa
 
 int launch_chunk_product_split(const PlrnnArgs &a, bool rev, const uint32_t *masks, const int *changed, float *pgam,
                                float *P, const int *active, const float *gamma, int C, int ncs, hipStream_t st) {
-    const int grid = a.B * ncs;
     KTimer kt(rev ? "k_chunk_product_split_rev" : "k_chunk_product_split", st);
 #define CPS(MPV, RV, WUV)                                                                                              \
-    hipLaunchKernelGGL((k_chunk_product_split<MPV, RV, WUV>), dim3(grid), dim3(64), 0, st, a.A, a.W, a.alpha, a.N, masks, \
-                       changed, pgam, P, active, gamma, a.B, a.T, a.M, C, ncs, a.tw)
+    hipLaunchKernelGGL((k_chunk_product_split<MPV, RV, WUV>),                                                            \
+                       dim3(a.B * ((ncs + kSplitWaves<MPV> - 1) / kSplitWaves<MPV>)), dim3(kSplitWaves<MPV> * 64), 0, st, \
+                       a.A, a.W, a.alpha, a.N, masks, changed, pgam, P, active, gamma, a.B, a.T, a.M, C, ncs, a.tw)
 #define CPSW(MPV, RV) if (a.tw > 0) CPS(MPV, RV, true); else CPS(MPV, RV, false)
     if (padded_dim(a.M) == 32) {
         if (rev) CPSW(32, true); else CPSW(32, false);

@@ -106,3 +106,57 @@ def test_readout_rows_of_opposite_size(bits):
     ref = O.diag_ssm_loss_and_seed(p, h.astype(np.complex64), x)[2]
     # fp32 sums of 640 terms of like size
     assert rel_inf(_np(out["grads"]["Wa"]), ref["Wa"]) < 1e-5
+
+
+# ---- vanilla PLRNN, chunk products of 16 < M <= 64 ------------------------------------------------
+
+@pytest.mark.parametrize("bits", SPREADS)
+@pytest.mark.parametrize("M,N,T_w", [(20, 20, 0), (32, 8, 7), (64, 64, 0), (50, 3, 40)])
+def test_vanilla_units(M, N, T_w, bits):
+    """Newton iterates, lam and gradients."""
+    os.environ["DEER_CHUNK"] = "12"
+    B, T = 2, 150
+    rng = np.random.default_rng(M)
+    c = W.random_plrnn_case(M, N, B, T, 0.2, 900 + M, w_norm=0.4, a_range=(0.3, 0.8))
+    p = c.params
+    z0, g = rng.standard_normal((B, M)).astype(np.float32), rng.standard_normal((B, T, M)).astype(np.float32)
+    d = _units(M, bits, rng)
+    q = {"A": p["A"], "W": d[:, None] * p["W"] / d, "h": d * p["h"]}
+    m, mu = oracle_model(c), {"kind": "plrnn", **q}
+    say("units vanilla", M, N, T_w, bits)
+    ref = O.newton(m, c.x, 0.2, N, fixed_iters=3, z0=z0, T_w=T_w)["z"]
+    r = D.deer_solve(m, c.x, 0.2, N, fixed_iters=3, z0=z0, T_w=T_w)["z"]
+    s = D.deer_solve(mu, c.x * d[:N], 0.2, N, fixed_iters=3, z0=z0 * d, T_w=T_w)["z"]
+    assert rel_inf(_np(r), ref) < TOL
+    assert np.array_equal(_np(r) * d, _np(s))
+    a = D.deer_adjoint(m, c.x, r, 0.2, N, z0=z0, g=g, T_w=T_w)
+    b = D.deer_adjoint(mu, c.x * d[:N], s, 0.2, N, z0=z0 * d, g=g / d, T_w=T_w)
+    assert np.array_equal(_np(a["lam"]), _np(b["lam"]) * d)
+    for k, u in (("A", 1.0), ("W", d[None, :] / d[:, None]), ("h", 1 / d)):
+        assert np.array_equal(_np(a["grads"][k]) * u, _np(b["grads"][k])), k
+
+
+def _one_on(B, T, M, rng):
+    """States that are positive at one step of every latent, else negative; the adjoint of g = 2^e at the
+    last step through J~ = diag(1 + w 1[z > 0]) is 2^e after that step and 2^e (1 + w) up to it."""
+    t_on = rng.integers(0, T - 1, (B, M))
+    z = np.where(np.arange(T)[None, :, None] == t_on[:, None, :], 1.0, -1.0).astype(np.float32)
+    g = np.zeros((B, T, M), np.float32)
+    g[:, -1] = 2.0 ** rng.integers(-3, 4, (B, M))
+
+    def lam(full):
+        return np.where(np.arange(T)[None, :, None] <= t_on[:, None, :], full, np.float32(1.0)) * g[:, -1:]
+    return z, g, lam
+
+
+@pytest.mark.parametrize("M", [20, 64])
+def test_vanilla_products_keep_24_bits(M):
+    os.environ["DEER_CHUNK"] = "16"
+    B, T = 2, 200
+    rng = np.random.default_rng(M)
+    z, g, lam = _one_on(B, T, M, rng)
+    full = _mant(M, rng)
+    m = {"kind": "plrnn", "A": np.ones(M, np.float32), "W": np.diag(full - np.float32(1.0)), "h": np.zeros(M, np.float32)}
+    say("units vanilla 24 bits", M)
+    out = D.deer_adjoint(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1, g=g, z0=np.full((B, M), -1.0, np.float32))
+    assert np.array_equal(_np(out["lam"]), lam(full))
