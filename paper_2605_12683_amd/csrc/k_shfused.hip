@@ -26,19 +26,23 @@ __device__ __forceinline__ float pf_at(int i, int N, float alpha) { return i < N
 
 static int shf_LP(int L) { return (L + 15) / 16 * 16; }
 
-// chunk products: W1 and W2 as hi and lo halves in blocks of 32 units, the mask table, five maxima of
-// each wave; local walk: double-buffered partial sums of the four waves and the maxima
-size_t shfused_product_lds(int M, int L) {
-    const size_t MP = padded_dim(M), prod = 8 * MP * ((L + 31) / 32 * 32) + 256 * sizeof(v4u) + 4 * 5 * sizeof(float);
-    const size_t walk = 2 * 4 * (MP / 16) * 64 * sizeof(v4f) + 4 * 16 * 2 * sizeof(uint32_t);
-    return prod > walk ? prod : walk;
-}
-
-// l tiles per wave of the fix-up (4 waves share the (L + 15) / 16 tiles)
+// l tiles per wave of the walks (4 waves share the (L + 15) / 16 tiles)
 static int shf_nlw(int L) {
     const int nlt = (L + 15) / 16;
     const int per = (nlt + 3) / 4;
     return per <= 1 ? 1 : per <= 2 ? 2 : per <= 4 ? 4 : per <= 8 ? 8 : 0;
+}
+
+// groups of four waves in a block of k_chunk_aggregates_sh: the split weights of the largest sizes
+// (nlw MP = 128: up to 96 KB) leave one block on a CU, which then has two
+static constexpr int shf_groups(int MP, int nlw) { return nlw * MP == 128 ? 2 : 1; }
+
+// chunk products: W1 and W2 in three parts in blocks of 32 units, and the mask table; local walk: per
+// group double-buffered partial sums of the four waves and the maxima
+size_t shfused_product_lds(int M, int L) {
+    const size_t MP = padded_dim(M), prod = 12 * MP * ((L + 31) / 32 * 32) + 256 * sizeof(v4u);
+    const size_t walk = (2 * 4 * (MP / 16) * 64 * sizeof(v4f) + 4 * 16 * 2 * sizeof(uint32_t)) * shf_groups((int)MP, shf_nlw(L));
+    return prod > walk ? prod : walk;
 }
 
 size_t shf_resjac_lds(int M, int L);
@@ -46,50 +50,45 @@ size_t shf_resjac_lds(int M, int L);
 bool shfused_supported(int M, int L) {
     const int MP = padded_dim(M);
     if (MP > 64 || L <= 0) return false;
-    // two blocks per CU
-    if (shfused_product_lds(M, L) > 80 * 1024 || shf_resjac_lds(M, L) > 80 * 1024) return false;
+    if (shf_resjac_lds(M, L) > 80 * 1024) return false;   // two blocks per CU
     const int nlw = shf_nlw(L);
     // fix-up A fragments in registers: NLW * (MP / 4) + (MP / 16) * 4 NLW floats per lane
     return nlw > 0 && nlw * (MP / 4 + MP / 4) <= 64;
 }
 
 // ---------------------------------------------------------------------------------------
-// chunk products on the fp16 matrix cores with split operands (split16.h).  Per step
+// chunk products on the bf16 matrix cores with operands in three exact parts (split16.h).  Per step
 //   J^T tile (I, Jt) = sum_l (W2 diag p)[l, 16 I + .] m_l W1[16 Jt + ., l]
-// from the two weights, split once per block into LDS (hi and lo of eight l per lane and tile) with
-// W1's half cleared where the unit is off; a block of 32 units takes the lane's eight mask bits
+// from the two weights, split once per block into LDS (the parts of eight l per lane and tile) with
+// W1's half-words cleared where the unit is off; a block of 32 units takes the lane's eight mask bits
 // through a 256-entry table of half-word masks.  A lane of the accumulator holds J[16 Jt + c][16 I +
 // 4 g + r], which is slot (I & 1, r) of k block I >> 1 of an A operand with the k slots numbered as in
-// k_chunk_product_split, so with the diagonal added, scaled and split again it composes at once,
-// P <- J~ P.  A wave owns one chunk and forms the Jacobians of NT consecutive steps together (one
-// read of the weights from LDS for all of them).
-//
-// Scales: the weights' largest entries to [2^9, 2^10); J~ by 2^sj from the bound
-// R = gamma (|W1|_inf |W2 diag p|_inf + max |A p|) >= its absolute row sums, R 2^sj in [2^13, 2^14);
-// P's columns as in k_chunk_product_split.
+// k_chunk_product_split, so with the diagonal added and split again it composes at once, P <- J~ P.
+// A wave owns one chunk and forms the Jacobians of NT consecutive steps together (one read of the
+// weights from LDS for all of them).
 //
 // A chunk whose masks are those of the pass before (masks_prev) and whose damping is that of its
 // stored product keeps it; masks_prev null: every product is formed.
 // forward: P_c = J~_{s1-1} ... J~_{s0};  REV (the adjoint): J~_{hi-1} ... J~_{s0+1}, hi = min(s1 + 1, T).
 //
-// M = 32, L = 256: a step is 108 matrix instructions (0.86 us on a SIMD) and about 200 vector ones,
-// where fp32 matrix instructions took 320 (4.4 us); 8 x 65536 steps: 0.71 ms for every chunk of the
-// adjoint against 2.6 ms.
+// M = 32, L = 256: a step is 216 matrix instructions (1.72 us on a SIMD) and about 450 vector ones,
+// where fp32 matrix instructions took 320 (4.4 us); 8 x 65536 steps: 1.2 ms for every chunk of the
+// adjoint against 2.6 ms in fp32.
 // ---------------------------------------------------------------------------------------
-template <int MP, int NT, bool REV, bool WU>
+template <int MP, int NT, int NWV, bool REV, bool WU>
 __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t *__restrict__ masks,
                                                  const uint32_t *__restrict__ masks_prev,
                                                  const float *__restrict__ gamma, float *__restrict__ pgam,
                                                  float *__restrict__ Pout, const int *__restrict__ active, int C,
                                                  int ncs, int LB, int block, v4u *smem4) {
     constexpr int NI = MP / 16, KK = (MP + 31) / 32, NV = (NT * 16 + 63) / 64;
-    v4u *wa = smem4;                       // [LB][NI][hi, lo][64]  (W2 diag p)^T
-    v4u *wb = smem4 + LB * NI * 128;       // [LB][NI][hi, lo][64]  W1
-    v4u *lut = smem4 + 2 * LB * NI * 128;  // [256] half-word masks of eight bits
-    float (*red)[5] = reinterpret_cast<float (*)[5]>(lut + 256);   // [4][5]
+    constexpr int NTB = NT * NI < 4 ? NT : 4 / NI;   // steps whose sums run together: four independent ones
+    v4u *wa = smem4;                       // [LB][NI][part][64]  (W2 diag p)^T
+    v4u *wb = smem4 + LB * NI * 192;       // [LB][NI][part][64]  W1
+    v4u *lut = smem4 + 2 * LB * NI * 192;  // [256] half-word masks of eight bits
     const int M = a.M, L = a.L, T = a.T, N = a.N, LW = (L + 31) / 32;
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const int id = block * 4 + wv;
+    const int id = block * NWV + wv;
     const bool exists = id < a.B * ncs;
     const int b = exists ? id / ncs : 0, s0 = exists ? (id % ncs) * C : 0;
     const int s1 = min(s0 + C, T);
@@ -103,63 +102,19 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
         todo = __builtin_amdgcn_ballot_w64(d != 0u) != 0ull;
     }
     if (!__syncthreads_or(todo)) return;
-    const float m1 = opaque_m1();
-
-    // largest entries and the row-sum bounds of W1 and W2 diag p, max |A p|
-    {
-        constexpr int TR = 256 / MP;   // threads per row of W1
-        float x1 = 0.f, x2 = 0.f, n1 = 0.f, n2 = 0.f, da = 0.f;
-        const int i = tid / TR;
-        for (int l = tid % TR; l < L; l += TR) {
-            const float w = i < M ? fabsf(a.W1[(size_t)i * L + l]) : 0.f;
-            x1 = fmaxf(x1, w);
-            n1 += w;
-        }
-#pragma unroll
-        for (int off = 1; off < TR; off <<= 1) n1 += __shfl_xor(n1, off, 64);
-        for (int l = tid; l < L; l += 256) {
-            float n = 0.f;
-            for (int j = 0; j < M; ++j) {
-                const float w = fabsf(a.W2[(size_t)l * M + j] * pf_at(j, N, a.alpha));
-                x2 = fmaxf(x2, w);
-                n += w;
-            }
-            n2 = fmaxf(n2, n);
-        }
-        if (tid < M) da = fabsf(a.A[tid] * pf_at(tid, N, a.alpha));
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            x1 = fmaxf(x1, __shfl_xor(x1, off, 64));
-            x2 = fmaxf(x2, __shfl_xor(x2, off, 64));
-            n1 = fmaxf(n1, __shfl_xor(n1, off, 64));
-            n2 = fmaxf(n2, __shfl_xor(n2, off, 64));
-            da = fmaxf(da, __shfl_xor(da, off, 64));
-        }
-        if (lane == 0) {
-            red[wv][0] = x1;
-            red[wv][1] = x2;
-            red[wv][2] = n1;
-            red[wv][3] = n2;
-            red[wv][4] = da;
-        }
-    }
     // table: half-word k of entry e is all ones where bit k of e is set
-    {
+    if (tid < 256) {
         v4u t;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             t[k] = ((tid >> (2 * k)) & 1 ? 0xffffu : 0u) | ((tid >> (2 * k + 1)) & 1 ? 0xffff0000u : 0u);
         lut[tid] = t;
     }
-    __syncthreads();
-    float mx[5];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) mx[k] = fmaxf(fmaxf(red[0][k], red[1][k]), fmaxf(red[2][k], red[3][k]));
-    const int sc1 = min(9 - exp_of(mx[0]), 100), sc2 = min(9 - exp_of(mx[1]), 100);
-    for (int e = tid; e < LB * NI * 64; e += 256) {
+    for (int e = tid; e < LB * NI * 64; e += NWV * 64) {
         const int ln = e & 63, I = (e >> 6) % NI, kb = (e >> 6) / NI;
         const int i = 16 * I + (ln & 15), l0 = 32 * kb + 8 * (ln >> 4);
-        v4u ah, al, bh, bl;
+        const double p = pf_at(i, N, a.alpha);
+        v4u pa[3], pb[3];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
             float w2[2], w1[2];
@@ -167,50 +122,42 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
             for (int k = 0; k < 2; ++k) {
                 const int l = l0 + 2 * e2 + k;
                 const bool ok = i < M && l < L;
-                w2[k] = ok ? ldexpf(a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha), sc2) : 0.f;
-                w1[k] = ok ? ldexpf(a.W1[(size_t)i * L + l], sc1) : 0.f;
+                w2[k] = ok ? a.W2[(size_t)l * M + i] : 0.f;
+                w1[k] = ok ? a.W1[(size_t)i * L + l] : 0.f;
             }
-            uint32_t h, lo;
-            split_pair(w2[0], w2[1], m1, h, lo);
-            ah[e2] = h;
-            al[e2] = lo;
-            split_pair(w1[0], w1[1], m1, h, lo);
-            bh[e2] = h;
-            bl[e2] = lo;
+            uint32_t part[3];
+            split_pair_f64(w2[0] * p, w2[1] * p, part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) pa[q][e2] = part[q];
+            split_pair(w1[0], w1[1], part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) pb[q][e2] = part[q];
         }
-        const int o = (kb * NI + I) * 128 + ln;
-        wa[o] = ah;
-        wa[o + 64] = al;
-        wb[o] = bh;
-        wb[o + 64] = bl;
+        const int o = (kb * NI + I) * 192 + ln;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            wa[o + 64 * q] = pa[q];
+            wb[o + 64 * q] = pb[q];
+        }
     }
     __syncthreads();
     if (!todo) return;
 
-    const float R = fabsf(gm) * fmaf(mx[2], mx[3], mx[4]);
-    const int sj = __builtin_amdgcn_readfirstlane(min(13 - exp_of(R), 100));
-    const int qe = __builtin_amdgcn_readfirstlane(max(exp_of(R) + 1, -20));
-    const int kr = qe <= 3 ? 4 : qe <= 6 ? 2 : 1;
-    const float fplain = pow2i(max(-(sj + qe), -126));
-    const float fj = ldexpf(gm, sj - sc1 - sc2);
     float dgr[NI][4];   // the diagonal of row 16 Jt + c, in the lane and slot that hold it
 #pragma unroll
     for (int Jt = 0; Jt < NI; ++Jt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = 16 * Jt + c;
-            dgr[Jt][r] = (c == 4 * g + r && row < M) ? ldexpf(gm * (a.A[row] * pf_at(row, N, a.alpha)), sj) : 0.f;
+            dgr[Jt][r] = (c == 4 * g + r && row < M) ? (float)((double)a.A[row] * gm * pf_at(row, N, a.alpha)) : 0.f;
         }
     v4f acc[NI][NI];
-    int E[NI];
 #pragma unroll
-    for (int tt = 0; tt < NI; ++tt) {
-        E[tt] = 0;
+    for (int tt = 0; tt < NI; ++tt)
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[I][tt][r] = (16 * I + 4 * g + r == 16 * tt + c) ? 1.f : 0.f;
-    }
     const int lo = REV ? s0 + 1 : s0, hi = REV ? min(s1 + 1, T) : s1;
     const int len = __builtin_amdgcn_readfirstlane(hi - lo);
     // mask words of NT steps, one per lane, the next NT steps' in flight
@@ -237,30 +184,41 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
 #pragma unroll
                 for (int Jt = 0; Jt < NI; ++Jt) jt[nt][I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
         for (int kb = 0; kb < LB; ++kb) {
-            v4u oa[NI][2], ob[NI][2];
+            v4u oa[NI][3];
 #pragma unroll
             for (int I = 0; I < NI; ++I)
 #pragma unroll
-                for (int hl = 0; hl < 2; ++hl) {
-                    oa[I][hl] = wa[((kb * NI + I) * 2 + hl) * 64 + lane];
-                    ob[I][hl] = wb[((kb * NI + I) * 2 + hl) * 64 + lane];
-                }
+                for (int q = 0; q < 3; ++q) oa[I][q] = wa[((kb * NI + I) * 3 + q) * 64 + lane];
+            v4u pm[NT];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const int e = nt * LW + kb;   // steps past the chunk have zero masks (and are not composed)
                 uint32_t w;
                 if (NV == 1 || e < 64) w = (uint32_t)__builtin_amdgcn_readlane((int)mc[0], e & 63);
                 else w = (uint32_t)__builtin_amdgcn_readlane((int)mc[NV - 1], e & 63);
-                const v4u pm = lut[(w >> (8 * g)) & 255u];
+                pm[nt] = lut[(w >> (8 * g)) & 255u];
+            }
 #pragma unroll
-                for (int Jt = 0; Jt < NI; ++Jt) {
-                    const v4u bh = ob[Jt][0] & pm, bl = ob[Jt][1] & pm;
+            for (int Jt = 0; Jt < NI; ++Jt) {
+                v4u ob[3];
 #pragma unroll
-                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][1], bh, jt[nt][I][Jt]);
+                for (int q = 0; q < 3; ++q) ob[q] = wb[((kb * NI + Jt) * 3 + q) * 64 + lane];
 #pragma unroll
-                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][0], bl, jt[nt][I][Jt]);
+                for (int n0 = 0; n0 < NT; n0 += NTB) {
+                    v4u bm[NTB][3];
 #pragma unroll
-                    for (int I = 0; I < NI; ++I) jt[nt][I][Jt] = mfma_h(oa[I][0], bh, jt[nt][I][Jt]);
+                    for (int n = 0; n < NTB; ++n)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) bm[n][q] = ob[q] & pm[n0 + n];
+#pragma unroll
+                    for (int o = 2; o >= 0; --o)   // parts of one order of magnitude, the smallest first
+#pragma unroll
+                        for (int qa = o; qa >= 0; --qa)
+#pragma unroll
+                            for (int n = 0; n < NTB; ++n)
+#pragma unroll
+                                for (int I = 0; I < NI; ++I)
+                                    jt[n0 + n][I][Jt] = mfma_b(oa[I][qa], bm[n][o - qa], jt[n0 + n][I][Jt]);
                 }
             }
         }
@@ -269,71 +227,54 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
             if (nt >= nv) break;
             const int t = t0 + nt;
             // P to the B operand
-            v4u bh[KK][NI], bl[KK][NI];
-            const bool renorm = (t & (kr - 1)) == 0;
+            v4u bq[3][KK][NI];
 #pragma unroll
-            for (int tt = 0; tt < NI; ++tt) {
-                float f = fplain;
-                if (renorm) {
-                    float m2 = 0.f;
-#pragma unroll
-                    for (int I = 0; I < NI; ++I)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) m2 = fmaf(acc[I][tt][r], acc[I][tt][r], m2);
-                    const int ph = norm_shift(group_sum(m2));
-                    f = pow2i(ph);
-                    E[tt] -= ph + sj;
-                } else {
-                    E[tt] += qe;
-                }
+            for (int tt = 0; tt < NI; ++tt)
 #pragma unroll
                 for (int I = 0; I < 2 * KK; ++I)
 #pragma unroll
                     for (int h2 = 0; h2 < 2; ++h2) {
-                        uint32_t ph = 0u, pl = 0u;
-                        if (I < NI) split_pair(acc[I < NI ? I : 0][tt][2 * h2] * f, acc[I < NI ? I : 0][tt][2 * h2 + 1] * f, m1, ph, pl);
-                        bh[I >> 1][tt][2 * (I & 1) + h2] = ph;
-                        bl[I >> 1][tt][2 * (I & 1) + h2] = pl;
+                        uint32_t part[3] = {0u, 0u, 0u};
+                        if (I < NI) split_pair(acc[I < NI ? I : 0][tt][2 * h2], acc[I < NI ? I : 0][tt][2 * h2 + 1], part);
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) bq[q][I >> 1][tt][2 * (I & 1) + h2] = part[q];
                     }
-            }
             // a latent warm-up step's P_1 drops the observed latents' columns
             const bool warm = WU && lo + t <= a.tw;
 #pragma unroll
             for (int Jt = 0; Jt < NI; ++Jt) {
-                v4u ah[KK], al[KK];
+                if constexpr (NI == 4) __builtin_amdgcn_sched_barrier(0);   // else operands formed early spill
+                v4u aq[3][KK];
 #pragma unroll
                 for (int I = 0; I < 2 * KK; ++I)
 #pragma unroll
                     for (int h2 = 0; h2 < 2; ++h2) {
-                        uint32_t ph = 0u, pl = 0u;
+                        uint32_t part[3] = {0u, 0u, 0u};
                         if (I < NI) {
                             const int Ic = I < NI ? I : 0, k = 16 * I + 4 * g + 2 * h2;
                             float v0 = jt[nt][Ic][Jt][2 * h2], v1 = jt[nt][Ic][Jt][2 * h2 + 1];
-                            v0 = I == Jt ? fmaf(v0, fj, dgr[Jt][2 * h2]) : v0 * fj;
-                            v1 = I == Jt ? fmaf(v1, fj, dgr[Jt][2 * h2 + 1]) : v1 * fj;
+                            v0 = I == Jt ? fmaf(v0, gm, dgr[Jt][2 * h2]) : v0 * gm;
+                            v1 = I == Jt ? fmaf(v1, gm, dgr[Jt][2 * h2 + 1]) : v1 * gm;
                             if (WU && warm) {
                                 v0 = k < N ? 0.f : v0;
                                 v1 = k + 1 < N ? 0.f : v1;
                             }
-                            split_pair(v0, v1, m1, ph, pl);
+                            split_pair(v0, v1, part);
                         }
-                        ah[I >> 1][2 * (I & 1) + h2] = ph;
-                        al[I >> 1][2 * (I & 1) + h2] = pl;
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) aq[q][I >> 1][2 * (I & 1) + h2] = part[q];
                     }
                 v4f s[NI];
 #pragma unroll
                 for (int tt = 0; tt < NI; ++tt) s[tt] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < KK; ++kk) {
+                for (int o = 2; o >= 0; --o)
 #pragma unroll
-                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(al[kk], bh[kk][tt], s[tt]);
+                    for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(ah[kk], bl[kk][tt], s[tt]);
-                }
+                        for (int qa = o; qa >= 0; --qa)
 #pragma unroll
-                for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-                    for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_h(ah[kk], bh[kk][tt], s[tt]);
+                            for (int tt = 0; tt < NI; ++tt) s[tt] = mfma_b(aq[qa][kk], bq[o - qa][kk][tt], s[tt]);
 #pragma unroll
                 for (int tt = 0; tt < NI; ++tt) acc[Jt][tt] = s[tt];
             }
@@ -345,7 +286,7 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
 #pragma unroll
         for (int I = 0; I < NI; ++I)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = ldexpf(acc[I][tt][r], E[tt]);
+            for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * MP + 16 * tt + c] = acc[I][tt][r];
     if (!REV && pgam && lane == 0) pgam[id] = gm;
 }
 
@@ -363,7 +304,8 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
 // LOCAL: from y = 0 instead of the carry, the chunk's last y (the local solution) written to
 // outbuf[chain][MP] and nothing else.
 // The waves' contributions (wave 0 adds the diagonal and the right-hand side) are summed in
-// LDS in a fixed order, so every wave holds the same next y.
+// LDS in a fixed order, so every wave holds the same next y.  NG groups of four waves may share a
+// block, each with its own 16 chains and LDS and all with the steps of the longest.
 // ---------------------------------------------------------------------------------------
 template <int MP>
 struct ShWalkLds {
@@ -371,18 +313,18 @@ struct ShWalkLds {
     uint32_t mx[4][16][2];
 };
 
-template <int MP, int NLW, bool REV, bool LOCAL>
+template <int MP, int NLW, int NG, bool REV, bool LOCAL>
 __device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__restrict__ masks,
                                            const float *__restrict__ rhs, float rhs_sign,
                                            const float *__restrict__ gamma, const float *__restrict__ carry_in,
                                            float *zbuf, float *outbuf, const int *__restrict__ zsel,
                                            uint32_t *__restrict__ chain_bits, const int *__restrict__ active, int C,
-                                           int ncs, const FusedCtl &fc, int block, ShWalkLds<MP> &sm) {
+                                           int ncs, const FusedCtl &fc, int block, ShWalkLds<MP> *smg) {
     constexpr int NI = MP / 16, NS = MP / 4;
-    auto &red = sm.red;
-    auto &mx = sm.mx;
-    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4,
-              c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NG > 1 ? wave >> 2 : 0, wv = wave & 3,
+              lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    auto &red = smg[grp].red;
+    auto &mx = smg[grp].mx;
     const int M = a.M, L = a.L, T = a.T, N = a.N;
     const int LW = (L + 31) / 32, nlt = (L + 15) / 16;
     // a1: rows l = 16 lt + c, k = i = 16 j + 4 g + q;  a2: rows i = 16 I + c, k = l = 16 lt + 4 g + q
@@ -409,16 +351,21 @@ __device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__re
                     !e ? 0.f : REV ? a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha) : a.W1[(size_t)i * L + l];
             }
     const int nchains = a.B * ncs;
-    const int id = block * 16 + c;
+    const int id = (block * NG + grp) * 16 + c;
     const bool exists = id < nchains;
     const int b = exists ? id / ncs : 0, cc = exists ? id % ncs : 0;
     const bool ok = exists && (!active || active[b]);
     const int s0 = cc * C;
     const int len = ok ? max(min(s0 + C, T) - s0, 0) : 0;
-    // steps of the block: the longest chain of its 16 (the same value in every wave)
+    // steps of the block: the longest of its chains (the same value in every wave)
     int maxlen = len;
+    if constexpr (NG > 1) {   // lane l: chain l % 32 of the block
+        static_assert(NG == 2, "two groups of 16 chains");
+        const int id2 = block * 32 + (lane & 31), b2 = id2 < nchains ? id2 / ncs : 0, s2 = id2 < nchains ? id2 % ncs * C : 0;
+        maxlen = id2 < nchains && (!active || active[b2]) ? max(min(s2 + C, T) - s2, 0) : 0;
+    }
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
+    for (int off = 1; off < 16 * NG; off <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off, 64));
     maxlen = __builtin_amdgcn_readfirstlane(maxlen);
     const float gm = gamma ? gamma[b] : 1.f;
     const float *zin = REV || LOCAL ? nullptr : cur_iter(zbuf, outbuf, zsel, b);
@@ -599,30 +546,31 @@ __global__ __launch_bounds__(256) void k_fixup_shjvp(const ShArgs a, const uint3
                                                      const int *__restrict__ zsel, uint32_t *__restrict__ chain_bits,
                                                      const int *__restrict__ active, int C, int ncs, FusedCtl fc) {
     __shared__ ShWalkLds<MP> sm;
-    shjvp_walk<MP, NLW, REV, false>(a, masks, rhs, rhs_sign, gamma, carry_in, zbuf, outbuf, zsel, chain_bits, active, C,
-                                    ncs, fc, blockIdx.x, sm);
+    shjvp_walk<MP, NLW, 1, REV, false>(a, masks, rhs, rhs_sign, gamma, carry_in, zbuf, outbuf, zsel, chain_bits, active, C,
+                                       ncs, fc, blockIdx.x, &sm);
 }
 
 // ---------------------------------------------------------------------------------------
-// A chunk's aggregates: the first blocks walk the local solutions (16 chunks each), the others form
-// the chunk products (4 chunks each).  The two need nothing of each other, and on a short sequence
-// neither fills the chip: M = 4, L = 50, 32768 steps take 20 us together and 20 + 15 us one after the
-// other.  M = 32, L = 256, 8 x 65536 steps: 0.66 ms a pass on average (with the products that are
-// kept) against 1.96 ms in fp32.
+// A chunk's aggregates: the first blocks walk the local solutions (16 chunks for every four waves), the
+// others form the chunk products (a chunk a wave).  The two need nothing of each other, and on a short sequence
+// neither fills the chip: M = 4, L = 50, 32768 steps take 24 us together (20 + 15 us one after the
+// other).  M = 32, L = 256, 8 x 65536 steps: 1.02 ms a pass on average (with the products that are
+// kept) against 1.94 ms in fp32.
 // ---------------------------------------------------------------------------------------
 template <int MP, int NT, int NLW, bool REV, bool WU>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_aggregates_sh(
+__global__ __launch_bounds__(256 * shf_groups(MP, NLW)) __attribute__((amdgpu_waves_per_eu(2))) void k_chunk_aggregates_sh(
     const ShArgs a, const uint32_t *__restrict__ masks, const uint32_t *__restrict__ masks_prev,
     const float *__restrict__ rhs, float rhs_sign, const float *__restrict__ gamma, float *__restrict__ pgam,
     float *__restrict__ Pout, float *__restrict__ vout, const int *__restrict__ active, int C, int ncs, int LB,
     int nwalk) {
     extern __shared__ __align__(16) v4u smem4[];
+    constexpr int NG = shf_groups(MP, NLW);
     if ((int)blockIdx.x < nwalk)
-        shjvp_walk<MP, NLW, REV, true>(a, masks, rhs, rhs_sign, gamma, nullptr, nullptr, vout, nullptr, nullptr, active, C,
-                                       ncs, FusedCtl{}, blockIdx.x, *reinterpret_cast<ShWalkLds<MP> *>(smem4));
+        shjvp_walk<MP, NLW, NG, REV, true>(a, masks, rhs, rhs_sign, gamma, nullptr, nullptr, vout, nullptr, nullptr, active,
+                                           C, ncs, FusedCtl{}, blockIdx.x, reinterpret_cast<ShWalkLds<MP> *>(smem4));
     else
-        sh_chunk_product<MP, NT, REV, WU>(a, masks, masks_prev, gamma, pgam, Pout, active, C, ncs, LB,
-                                          blockIdx.x - nwalk, smem4);
+        sh_chunk_product<MP, NT, 4 * NG, REV, WU>(a, masks, masks_prev, gamma, pgam, Pout, active, C, ncs, LB,
+                                                  blockIdx.x - nwalk, smem4);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -839,12 +787,12 @@ int launch_chunk_aggregates_sh(bool rev, const ShArgs &a, const uint32_t *masks,
                                const int *active, int C, int ncs, hipStream_t st) {
     const int MP = padded_dim(a.M);
     if (!shfused_supported(a.M, a.L) || (rev && (gamma || active))) return DEER_ERR_INVALID_ARG;
-    const int nwalk = (a.B * ncs + 15) / 16, grid = nwalk + (a.B * ncs + 3) / 4;
-    const int LB = (a.L + 31) / 32, nlw = shf_nlw(a.L);
+    const int LB = (a.L + 31) / 32, nlw = shf_nlw(a.L), ng = shf_groups(MP, nlw);
+    const int nwalk = (a.B * ncs + 16 * ng - 1) / (16 * ng), grid = nwalk + (a.B * ncs + 4 * ng - 1) / (4 * ng);
     const size_t lds = shfused_product_lds(a.M, a.L);
     KTimer kt(rev ? "k_chunk_aggregates_sh_rev" : "k_chunk_aggregates_sh", st);
 #define CPS(MPV, NTV, NL, RV, WUV)                                                                                   \
-    hipLaunchKernelGGL((k_chunk_aggregates_sh<MPV, NTV, NL, RV, WUV>), dim3(grid), dim3(256), lds, st, a, masks,        \
+    hipLaunchKernelGGL((k_chunk_aggregates_sh<MPV, NTV, NL, RV, WUV>), dim3(grid), dim3(256 * ng), lds, st, a, masks,   \
                        masks_prev, rhs, rhs_sign, gamma, pgam, P, v, active, C, ncs, LB, nwalk)
 #define CPW(MPV, NTV, NL, RV) { if (a.tw > 0) CPS(MPV, NTV, NL, RV, true); else CPS(MPV, NTV, NL, RV, false); }
 #define CPR(MPV, NTV, NL) { if (rev) CPW(MPV, NTV, NL, true) else CPW(MPV, NTV, NL, false) }

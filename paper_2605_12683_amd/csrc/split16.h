@@ -53,8 +53,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, float m1, uint32_
 // 2^-109 (below, lo and then mid are subnormal): bf16 has float's exponent, so nothing is scaled and
 // entries of any sizes meet in one product.  A product of two such operands takes six matrix
 // instructions, lo hi + mid mid + hi lo, mid hi + hi mid, hi hi in this order, with fp32 products and
-// sums; the dropped mid lo, lo mid and lo lo are below 2^-24 of the product together, and of either
-// sign.  Against 64 bits the sums are nearer than those of the fp32 instruction, which rounds once per
+// sums; the dropped mid lo, lo mid and lo lo are together below 2^-23 of the largest such product, 2^-25
+// as a rule and of either sign.  Against 64 bits the sums are nearer than those of the fp32 instruction, which rounds once per
 // four terms; the time is 3/7 of its (16 instructions of 16 x 16 x 32 in bf16 take 127 ns on a SIMD, 16
 // of 16 x 16 x 4 in fp32 222 ns).
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -76,7 +76,7 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&part)[
         x1 -= __uint_as_float(p & 0xffff0000u);
     }
 }
-// the same of a value known to more than float's bits, to within 2^-25 of it
+// the same of a value known to more than float's bits, rounded once, to 24 bits
 __device__ __forceinline__ void split_pair_f64(double x0, double x1, uint32_t (&part)[3]) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {

@@ -160,3 +160,50 @@ def test_vanilla_products_keep_24_bits(M):
     say("units vanilla 24 bits", M)
     out = D.deer_adjoint(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1, g=g, z0=np.full((B, M), -1.0, np.float32))
     assert np.array_equal(_np(out["lam"]), lam(full))
+
+
+# ---- shallow PLRNN ------------------------------------------------------------------------------------
+
+@pytest.mark.parametrize("bits", SPREADS)
+@pytest.mark.parametrize("M,L,N,T_w", [(5, 50, 3, 0), (32, 256, 32, 9), (64, 40, 10, 0)])
+def test_shallow_units(M, L, N, T_w, bits):
+    """Newton iterates, lam and gradients, latents and hidden units in units of their own."""
+    os.environ["DEER_CHUNK"] = "12"
+    B, T = 2, 90
+    rng = np.random.default_rng(M)
+    c = W.random_shplrnn_case(M, L, N, B, T, 0.2, 950 + M, w_norm=0.3, a_range=(0.3, 0.6))
+    p = c.params
+    z0, g = rng.standard_normal((B, M)).astype(np.float32), rng.standard_normal((B, T, M)).astype(np.float32)
+    d, e = _units(M, bits, rng), _units(L, bits, rng)
+    q = {"A": p["A"], "W1": d[:, None] * p["W1"] / e, "W2": e[:, None] * p["W2"] / d, "h1": d * p["h1"], "h2": e * p["h2"]}
+    m, mu = oracle_model(c), {"kind": "shplrnn", **q}
+    say("units shallow", M, L, N, T_w, bits)
+    ref = O.newton(m, c.x, 0.2, N, fixed_iters=3, z0=z0, T_w=T_w)["z"]
+    r = D.deer_solve(m, c.x, 0.2, N, fixed_iters=3, z0=z0, T_w=T_w)["z"]
+    s = D.deer_solve(mu, c.x * d[:N], 0.2, N, fixed_iters=3, z0=z0 * d, T_w=T_w)["z"]
+    assert rel_inf(_np(r), ref) < TOL
+    assert np.array_equal(_np(r) * d, _np(s))
+    a = D.deer_adjoint(m, c.x, r, 0.2, N, z0=z0, g=g, T_w=T_w)
+    b = D.deer_adjoint(mu, c.x * d[:N], s, 0.2, N, z0=z0 * d, g=g / d, T_w=T_w)
+    assert np.array_equal(_np(a["lam"]), _np(b["lam"]) * d)
+    for k, u in (("A", 1.0), ("W1", e[None, :] / d[:, None]), ("W2", d[None, :] / e[:, None]), ("h1", 1 / d), ("h2", 1 / e)):
+        assert np.array_equal(_np(a["grads"][k]) * u, _np(b["grads"][k])), k
+
+
+@pytest.mark.parametrize("M,L", [(6, 10), (30, 40), (64, 64)])
+def test_shallow_products_keep_24_bits(M, L):
+    os.environ["DEER_CHUNK"] = "16"
+    B, T = 2, 200
+    rng = np.random.default_rng(M)
+    z, g, lam = _one_on(B, T, M, rng)
+    K = min(M, L)
+    full = np.ones(M, np.float32)
+    full[:K] = _mant(K, rng)
+    W1, W2 = np.zeros((M, L), np.float32), np.zeros((L, M), np.float32)
+    W1[np.arange(K), np.arange(K)] = 1.0
+    W2[np.arange(K), np.arange(K)] = full[:K] - np.float32(1.0)
+    m = {"kind": "shplrnn", "A": np.ones(M, np.float32), "W1": W1, "W2": W2, "h1": np.zeros(M, np.float32),
+         "h2": np.zeros(L, np.float32)}
+    say("units shallow 24 bits", M, L)
+    out = D.deer_adjoint(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1, g=g, z0=np.full((B, M), -1.0, np.float32))
+    assert np.array_equal(_np(out["lam"]), lam(full))
