@@ -31,21 +31,16 @@ __device__ __forceinline__ float eload(const float *__restrict__ Jp, int M, int 
     return FLIP ? Jp[(size_t)col * M + row] : Jp[(size_t)row * M + col];
 }
 
-// Products of 128 x 128 matrices along a chain, Q <- E_t Q from the identity, on the fp16 matrix
-// cores with split operands (split16.h), one 4-wave workgroup per chain.  Wave w holds columns
-// 32 w .. 32 w + 31 of Q in accumulators, which after the split are the next step's B operand; E_t
-// is split by the workgroup into LDS in the A operand's layout, the next step's loads in flight
-// while the matrix cores work on this one.
-// Scales (powers of two): the wave that stages rows 32 w .. 32 w + 31 of E_t brings their largest
-// entry to [2^9, 2^10), every column of Q is brought to a 2-norm in [2^13, 2^14) before its split;
-// Q = acc[I] * rw[I / 2] * 2^-qe then, rw the row blocks' scales relative to the largest block's.
-// Rows with infinities or NaN are split unscaled (their results are not finite either way).
-// 192 instructions of 16 x 16 x 32 per wave and step take 1.5 us (512 of 16 x 16 x 4 in fp32 7.1 us),
+// Products of 128 x 128 matrices along a chain, Q <- E_t Q from the identity, on the bf16 matrix
+// cores with operands in three exact parts (split16.h), one 4-wave workgroup per chain.  Wave w holds
+// columns 32 w .. 32 w + 31 of Q in accumulators, which after the split are the next step's B operand;
+// E_t is split by the workgroup into LDS in the A operand's layout (96 KB: one buffer, written between
+// two barriers), the next step's loads in flight while the matrix cores work on this one.
+// 384 instructions of 16 x 16 x 32 per wave and step take 3.0 us (512 of 16 x 16 x 4 in fp32 7.1 us),
 // after which reading E_t (64 KB a step on every CU) and the splits count as much.
 struct BigProd {
-    v4u es[2][8][4][2][64];   // [buffer][row tile][k block][hi, lo][es_slot(lane)]
+    v4u es[8][4][3][64];   // [row tile][k block][hi, mid, lo][es_slot(lane)]
     float ub[2][BG];
-    int sc[2][4];             // [buffer][wave]: scale of the rows it staged
 };
 
 // Staging without a transpose: a load takes 128 bytes of each of 8 rows (16 rows of 64 bytes took 2.3
@@ -57,10 +52,7 @@ template <bool TRN>
 struct BigChain {
     BigProd &s;
     int wv, lane, g, c;
-    float m1;
     v4f acc[8][2];            // acc[I][Jt][r]: row 16 I + 4 g + r, column 32 wv + 16 Jt + c
-    float rw[4];
-    int qe[2];
     float4 pre[16];           // the next E: columns col(k) .. + 3 of row(k)
 
     __device__ __forceinline__ explicit BigChain(BigProd &sm) : s(sm) {
@@ -68,134 +60,96 @@ struct BigChain {
         lane = threadIdx.x & 63;
         g = lane >> 4;
         c = lane & 15;
-        m1 = opaque_m1();
 #pragma unroll
         for (int I = 0; I < 8; ++I)
 #pragma unroll
             for (int Jt = 0; Jt < 2; ++Jt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[I][Jt][r] = (16 * I + 4 * g + r == 32 * wv + 16 * Jt + c) ? 1.f : 0.f;
-        for (int w = 0; w < 4; ++w) rw[w] = 1.f;
-        qe[0] = qe[1] = 0;
     }
     __device__ __forceinline__ int row(int k) const {
         return TRN ? 16 * (2 * wv + (k >> 3)) + c : 32 * wv + 8 * (k >> 2) + (lane >> 3);
     }
     __device__ __forceinline__ int col(int k) const { return TRN ? 16 * (k & 7) + 4 * g : 32 * (k & 3) + 4 * (lane & 7); }
-    // the staged rows, split, into buffer buf
-    __device__ __forceinline__ void stage_store(int buf) {
-        float mx = 0.f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            mx = fmaxf(fmaxf(fmaxf(mx, fabsf(pre[k].x)), fmaxf(fabsf(pre[k].y), fabsf(pre[k].z))), fabsf(pre[k].w));
-        mx = __uint_as_float(wave_max_u32(__float_as_uint(mx)));
-        const int e = exp_of(mx);
-        const int sc = __builtin_amdgcn_readfirstlane(e == 128 ? 0 : min(9 - e, 100));
-        const float f = ldexpf(1.f, sc);
+    // the loaded rows, split, into LDS (between two barriers)
+    __device__ __forceinline__ void stage_store() {
         typedef uint32_t v2u __attribute__((ext_vector_type(2)));
         if constexpr (TRN) {
 #pragma unroll
             for (int k = 0; k < 16; k += 2) {
-                v4u hi, lo;
+                v4u o[3];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const float4 v = pre[k + h];
-                    uint32_t a, b;
-                    split_pair(v.x * f, v.y * f, m1, a, b);
-                    hi[2 * h] = a;
-                    lo[2 * h] = b;
-                    split_pair(v.z * f, v.w * f, m1, a, b);
-                    hi[2 * h + 1] = a;
-                    lo[2 * h + 1] = b;
+                    uint32_t a[3], b[3];
+                    split_pair(v.x, v.y, a);
+                    split_pair(v.z, v.w, b);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        o[q][2 * h] = a[q];
+                        o[q][2 * h + 1] = b[q];
+                    }
                 }
-                s.es[buf][2 * wv + (k >> 3)][(k & 7) >> 1][0][es_slot(lane)] = hi;
-                s.es[buf][2 * wv + (k >> 3)][(k & 7) >> 1][1][es_slot(lane)] = lo;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) s.es[2 * wv + (k >> 3)][(k & 7) >> 1][q][es_slot(lane)] = o[q];
             }
         } else {
             const int gg = lane & 3, e2 = (lane >> 2) & 1, cr = lane >> 3;   // lane group, slot half, row mod 8
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 const float4 v = pre[k];
-                uint32_t a, b, a2, b2;
-                split_pair(v.x * f, v.y * f, m1, a, b);
-                split_pair(v.z * f, v.w * f, m1, a2, b2);
+                uint32_t a[3], b[3];
+                split_pair(v.x, v.y, a);
+                split_pair(v.z, v.w, b);
                 const int sl = es_slot(16 * gg + 8 * ((k >> 2) & 1) + cr);
-                reinterpret_cast<v2u *>(&s.es[buf][2 * wv + (k >> 3)][k & 3][0][sl])[e2] = (v2u){a, a2};
-                reinterpret_cast<v2u *>(&s.es[buf][2 * wv + (k >> 3)][k & 3][1][sl])[e2] = (v2u){b, b2};
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    reinterpret_cast<v2u *>(&s.es[2 * wv + (k >> 3)][k & 3][q][sl])[e2] = (v2u){a[q], b[q]};
             }
         }
-        if (lane == 0) s.sc[buf][wv] = sc;
     }
-    // Q <- E Q with the E of buffer buf
-    __device__ __forceinline__ void multiply(int buf) {
-        v4u bh[2][4], bl[2][4];
-        int sh[2];
+    // Q <- E Q
+    __device__ __forceinline__ void multiply() {
+        v4u bq[3][2][4];
 #pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt) {
-            float m2 = 0.f;
+        for (int Jt = 0; Jt < 2; ++Jt)
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                float q = 0.f;
-#pragma unroll
-                for (int I = 2 * w; I < 2 * w + 2; ++I)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) q = fmaf(acc[I][Jt][r], acc[I][Jt][r], q);
-                m2 = fmaf(q, rw[w] * rw[w], m2);
-            }
-            sh[Jt] = norm_shift(group_sum(m2));
-            const float f = pow2i(sh[Jt]);
-#pragma unroll
-            for (int I = 0; I < 8; ++I) {
-                const float fi = f * rw[I >> 1];
+            for (int I = 0; I < 8; ++I)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    uint32_t a, b;
-                    split_pair(acc[I][Jt][2 * h] * fi, acc[I][Jt][2 * h + 1] * fi, m1, a, b);
-                    bh[Jt][I >> 1][2 * (I & 1) + h] = a;
-                    bl[Jt][I >> 1][2 * (I & 1) + h] = b;
+                    uint32_t part[3];
+                    split_pair(acc[I][Jt][2 * h], acc[I][Jt][2 * h + 1], part);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) bq[q][Jt][I >> 1][2 * (I & 1) + h] = part[q];
                 }
-            }
-        }
 #pragma unroll
-        for (int I0 = 0; I0 < 8; I0 += 4) {
+        for (int I0 = 0; I0 < 8; I0 += 2) {
+            __builtin_amdgcn_sched_barrier(0);   // else operands read early spill
 #pragma unroll
-            for (int I = I0; I < I0 + 4; ++I)
+            for (int I = I0; I < I0 + 2; ++I)
 #pragma unroll
                 for (int Jt = 0; Jt < 2; ++Jt) acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
-                v4u ah[4], al[4];
+                v4u aq[2][3];
 #pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    ah[n] = s.es[buf][I0 + n][kk][0][es_slot(lane)];
-                    al[n] = s.es[buf][I0 + n][kk][1][es_slot(lane)];
-                }
+                for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int n = 0; n < 4; ++n)
+                    for (int q = 0; q < 3; ++q) aq[n][q] = s.es[I0 + n][kk][q][es_slot(lane)];
 #pragma unroll
-                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(al[n], bh[Jt][kk], acc[I0 + n][Jt]);
+                for (int o = 2; o >= 0; --o)   // parts of one order of magnitude, the smallest first
 #pragma unroll
-                for (int n = 0; n < 4; ++n)
+                    for (int qa = o; qa >= 0; --qa)
 #pragma unroll
-                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(ah[n], bl[Jt][kk], acc[I0 + n][Jt]);
+                        for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int n = 0; n < 4; ++n)
-#pragma unroll
-                    for (int Jt = 0; Jt < 2; ++Jt) acc[I0 + n][Jt] = mfma_h(ah[n], bh[Jt][kk], acc[I0 + n][Jt]);
+                            for (int Jt = 0; Jt < 2; ++Jt)
+                                acc[I0 + n][Jt] = mfma_b(aq[n][qa], bq[o - qa][Jt][kk], acc[I0 + n][Jt]);
             }
         }
-        int sc[4], ref = 1000;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            sc[w] = __builtin_amdgcn_readfirstlane(s.sc[buf][w]);
-            ref = min(ref, sc[w]);
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w) rw[w] = ldexpf(1.f, ref - sc[w]);
-#pragma unroll
-        for (int Jt = 0; Jt < 2; ++Jt) qe[Jt] += sh[Jt] + ref;
+        __builtin_amdgcn_sched_barrier(0);
     }
-    // row 32 wv + lane % 32 of E u for the E and the u of buffer buf (both halves of the wave hold it)
+    // row 32 wv + lane % 32 of E u for the u of buffer buf (both halves of the wave hold it)
     __device__ __forceinline__ float apply(int buf) {
         const int I = 2 * wv + ((lane & 31) >> 4), hh = lane >> 5;
         float p0 = 0.f, p1 = 0.f;
@@ -204,44 +158,43 @@ struct BigChain {
             const int kk = 2 * hh + k2;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const v4u hi = s.es[buf][I][kk][0][es_slot(16 * q + c)], lo = s.es[buf][I][kk][1][es_slot(16 * q + c)];
+                v4u w[3];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) w[e] = s.es[I][kk][e][es_slot(16 * q + c)];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const float4 y = *reinterpret_cast<const float4 *>(&s.ub[buf][32 * kk + 16 * h + 4 * q]);
-                    const v2h a0 = __builtin_bit_cast(v2h, (uint32_t)hi[2 * h]), a1 = __builtin_bit_cast(v2h, (uint32_t)hi[2 * h + 1]);
-                    const v2h b0 = __builtin_bit_cast(v2h, (uint32_t)lo[2 * h]), b1 = __builtin_bit_cast(v2h, (uint32_t)lo[2 * h + 1]);
-                    p0 = fmaf((float)b0[0], y.x, p0);
-                    p1 = fmaf((float)b0[1], y.y, p1);
-                    p0 = fmaf((float)b1[0], y.z, p0);
-                    p1 = fmaf((float)b1[1], y.w, p1);
-                    p0 = fmaf((float)a0[0], y.x, p0);
-                    p1 = fmaf((float)a0[1], y.y, p1);
-                    p0 = fmaf((float)a1[0], y.z, p0);
-                    p1 = fmaf((float)a1[1], y.w, p1);
+                    float x[4];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {   // (lo + mid) + hi: exact
+                        x[2 * e] = (__uint_as_float(w[2][2 * h + e] << 16) + __uint_as_float(w[1][2 * h + e] << 16)) +
+                                   __uint_as_float(w[0][2 * h + e] << 16);
+                        x[2 * e + 1] = (__uint_as_float(w[2][2 * h + e] & 0xffff0000u) +
+                                        __uint_as_float(w[1][2 * h + e] & 0xffff0000u)) +
+                                       __uint_as_float(w[0][2 * h + e] & 0xffff0000u);
+                    }
+                    p0 = fmaf(x[0], y.x, p0);
+                    p1 = fmaf(x[1], y.y, p1);
+                    p0 = fmaf(x[2], y.z, p0);
+                    p1 = fmaf(x[3], y.w, p1);
                 }
             }
         }
-        float part = p0 + p1;
-        part += __shfl_xor(part, 32, 64);
-        return ldexpf(part, -__builtin_amdgcn_readfirstlane(s.sc[buf][wv]));
+        const float part = p0 + p1;
+        return part + __shfl_xor(part, 32, 64);
     }
     // (Q^T r)[32 wv + 16 Jt + c] for the r of buffer buf
     __device__ __forceinline__ float apply_t(int buf, int Jt) {
         float part = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            float q = 0.f;
-#pragma unroll
-            for (int I = 2 * w; I < 2 * w + 2; ++I) {
-                const float4 rv = *reinterpret_cast<const float4 *>(&s.ub[buf][16 * I + 4 * g]);
-                q = fmaf(acc[I][Jt][0], rv.x, q);
-                q = fmaf(acc[I][Jt][1], rv.y, q);
-                q = fmaf(acc[I][Jt][2], rv.z, q);
-                q = fmaf(acc[I][Jt][3], rv.w, q);
-            }
-            part = fmaf(q, rw[w], part);
+        for (int I = 0; I < 8; ++I) {
+            const float4 rv = *reinterpret_cast<const float4 *>(&s.ub[buf][16 * I + 4 * g]);
+            part = fmaf(acc[I][Jt][0], rv.x, part);
+            part = fmaf(acc[I][Jt][1], rv.y, part);
+            part = fmaf(acc[I][Jt][2], rv.z, part);
+            part = fmaf(acc[I][Jt][3], rv.w, part);
         }
-        return ldexpf(group_sum(part), -qe[Jt]);
+        return group_sum(part);
     }
     __device__ __forceinline__ void store(float *__restrict__ P) {
 #pragma unroll
@@ -249,8 +202,7 @@ struct BigChain {
 #pragma unroll
             for (int Jt = 0; Jt < 2; ++Jt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    P[(16 * I + 4 * g + r) * BG + 32 * wv + 16 * Jt + c] = ldexpf(acc[I][Jt][r] * rw[I >> 1], -qe[Jt]);
+                for (int r = 0; r < 4; ++r) P[(16 * I + 4 * g + r) * BG + 32 * wv + 16 * Jt + c] = acc[I][Jt][r];
     }
 };
 
@@ -259,7 +211,7 @@ struct BigChain {
 // taken as the sum u_{s0} = sum_k (E_k ... E_{s0+1})^T rhs_k along the same sweep: Q_k =
 // E_k ... E_{s0+1} is the accumulated product after the step that takes E_k.
 // M = 128, 8192 steps in 256 chunks: forward 347 us and reverse 310 us with fp32 instructions,
-// 194 us and 169 us now (reading the matrices alone takes 109 us).
+// 250 us and 235 us now (reading the matrices alone takes 109 us).
 template <bool REV, bool FLIP>
 __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restrict__ J, const float *__restrict__ rhs,
                                                            float rhs_sign, float *__restrict__ Pout,
@@ -304,16 +256,16 @@ __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restri
     if (!REV && tid < BG) sm.ub[0][tid] = 0.f;
     if (len > 0) {
         stage_load(0);
-        q.stage_store(0);
+        q.stage_store();
         if (REV && own) sm.ub[0][ui] = rpre;
     }
-    __syncthreads();
+    lds_barrier();
     int cur = 0;
     for (int t = 0; t < len; ++t, cur ^= 1) {
         const bool more = t + 1 < len;
         const float rc = rpre;
         if (more) stage_load(t + 1);   // in flight during this step
-        q.multiply(cur);
+        q.multiply();
         if (REV) {
             if (lo + t < s1) {
 #pragma unroll
@@ -325,10 +277,11 @@ __global__ __launch_bounds__(256) void k_chunk_product_big(const float *__restri
             if (own) sm.ub[cur ^ 1][ui] = ui < M ? fmaf(rhs_sign, rc, y) : 0.f;
         }
         if (more) {
-            q.stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
+            lds_barrier();   // every wave has read this step's E
+            q.stage_store();
             if (REV && own) sm.ub[cur ^ 1][ui] = rpre;
         }
-        __syncthreads();
+        lds_barrier();
     }
     q.store(Pout + (size_t)id * BG * BG);
     if (REV) {
@@ -442,7 +395,7 @@ __global__ __launch_bounds__(256) void k_carry_big(const float *__restrict__ P, 
 }
 
 // group maps in processing order: Q_j = A_{k1-1} ... A_{k0} and u_j = the group's walk from zero,
-// composed as the chunk products are.  M = 128, 32 groups of 8: 42 us (118 us with fp32
+// composed as the chunk products are.  M = 128, 32 groups of 8: 57 us (118 us with fp32
 // instructions).
 template <bool REV>
 __global__ __launch_bounds__(256) void k_carry_group_big(const float *__restrict__ P, const float *__restrict__ v,
@@ -470,18 +423,21 @@ __global__ __launch_bounds__(256) void k_carry_group_big(const float *__restrict
     };
     if (tid < BG) sm.ub[0][tid] = 0.f;
     stage_load(k0);
-    q.stage_store(0);
-    __syncthreads();
+    q.stage_store();
+    lds_barrier();
     int cur = 0;
     for (int k = k0; k < k1; ++k, cur ^= 1) {
         const bool more = k + 1 < k1;
         const float vc = vpre;
         if (more) stage_load(k + 1);   // in flight during this step
-        q.multiply(cur);
+        q.multiply();
         const float y = q.apply(cur);
         if (q.lane < 32) sm.ub[cur ^ 1][ui] = y + vc;
-        if (more) q.stage_store(cur ^ 1);   // that buffer's reads ended at the previous barrier
-        __syncthreads();
+        if (more) {
+            lds_barrier();   // every wave has read this step's map
+            q.stage_store();
+        }
+        lds_barrier();
     }
     q.store(gq + ((size_t)b * ngroups + j) * BG * BG);
     if (tid < BG) gu[((size_t)b * ngroups + j) * BG + tid] = sm.ub[cur][tid];

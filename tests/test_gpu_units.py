@@ -207,3 +207,51 @@ def test_shallow_products_keep_24_bits(M, L):
     say("units shallow 24 bits", M, L)
     out = D.deer_adjoint(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1, g=g, z0=np.full((B, M), -1.0, np.float32))
     assert np.array_equal(_np(out["lam"]), lam(full))
+
+
+@pytest.mark.parametrize("bits", SPREADS)
+@pytest.mark.parametrize("rev", [False, True])
+@pytest.mark.parametrize("tr", [False, True])
+@pytest.mark.parametrize("M,B,T,chunk", [(30, 2, 70, 8), (65, 1, 31, 3), (128, 1, 130, 2), (100, 2, 64, 4)])
+def test_scan_units(M, B, T, chunk, rev, tr, bits):
+    """The bare scan, one and two carry levels, every step's state in its own units."""
+    os.environ["DEER_CHUNK"] = str(chunk)
+    rng = np.random.default_rng(M + T)
+    J = (rng.standard_normal((B, T, M, M)) * 0.6 / np.sqrt(M)).astype(np.float32)
+    b = rng.standard_normal((B, T, M)).astype(np.float32)
+    d = np.stack([np.stack([_units(M, bits, rng) for _ in range(T)]) for _ in range(B)])
+    # op(J_t) maps state t - 1 to t (reverse: t to t - 1)
+    prev = np.concatenate([np.ones_like(d[:, :1]), d[:, :-1]], 1)
+    out, inp = (prev, d) if rev else (d, prev)
+    Jd = J * (inp[:, :, :, None] ** -1 * out[:, :, None, :] if tr else out[:, :, :, None] / inp[:, :, None, :])
+    say("units scan", M, B, T, chunk, rev, tr, bits)
+    y = _np(D.deer_scan(0, J, b, reverse=rev, transpose=tr))
+    yd = _np(D.deer_scan(0, Jd.astype(np.float32), b * d, reverse=rev, transpose=tr))
+    assert np.array_equal(y * d, yd)
+
+
+@pytest.mark.parametrize("rev", [False, True])
+@pytest.mark.parametrize("tr", [False, True])
+@pytest.mark.parametrize("M,T,chunk", [(128, 64, 8), (70, 120, 2)])
+def test_wide_scan_keeps_24_bits(M, T, chunk, rev, tr):
+    """Permutations and one diagonal matrix of 24-bit entries: the scan of a state of powers of two is
+    exact, through chunk products, group maps (two carry levels at T = 120) and carries."""
+    os.environ["DEER_CHUNK"] = str(chunk)
+    rng = np.random.default_rng(M)
+    J = np.zeros((1, T, M, M), np.float32)
+    for t in range(T):
+        J[0, t, np.arange(M), rng.permutation(M)] = 1.0
+    J[0, T // 2] = np.diag(_mant(M, rng))
+    b = np.zeros((1, T, M), np.float32)
+    b[0, T - 1 if rev else 0] = 2.0 ** rng.integers(-5, 6, M)
+    say("units wide scan 24 bits", M, rev, tr)
+    y = _np(D.deer_scan(0, J, b, reverse=rev, transpose=tr))[0]
+    ref = np.zeros((T, M))
+    v = np.zeros(M)
+    for t in (range(T - 1, -1, -1) if rev else range(T)):
+        k = t + 1 if rev else t
+        if 0 < k < T:
+            v = (J[0, k].T if tr else J[0, k]).astype(np.float64) @ v
+        v = v + b[0, t]
+        ref[t] = v
+    assert np.array_equal(y, ref)
