@@ -661,71 +661,53 @@ __global__ __launch_bounds__(256) void k_resjac_big(const ShArgs a, const float 
     }
 }
 
-// J~_s = Cd (or diag(A p)) + W1 diag(m_s) V with V = W2 diag(p) (or the given W2 P), on the fp16
-// matrix cores with split operands (W1 and V scaled by their largest entries): one row at a time per
-// block, the blocks walking the rows, wave wv computes the column tiles 2 wv, 2 wv + 1 of all 8 row
-// tiles.  KB = blocks of 32 hidden units; lane group g takes units 32 kk + 8 g .. + 7 of a block.  W1's
-// halves are shared through LDS, a wave's columns of V stay in registers, and a step's mask clears
-// half-words of V.  M = 128, L = 50, 8192 rows: 97 us, near the 537 MB written (78 us at
-// the rate of a fill); 187 us with fp32 instructions and stores of 64 bytes of 16 rows.  Two waves a
-// SIMD are needed: 189 us with one (256 VGPRs and more).
+// J~_s = Cd (or diag(A p)) + W1 diag(m_s) V with V = W2 diag(p) (or the given W2 P), on the bf16
+// matrix cores with operands in three exact parts (split16.h): one row at a time per block, the
+// blocks walking the rows, wave wv computes the column tiles 2 wv, 2 wv + 1 of all 8 row tiles.  KB =
+// blocks of 32 hidden units; lane group g takes units 32 kk + 8 g .. + 7 of a block.  W1's parts are
+// shared through LDS, a wave's columns of V stay in registers, and a step's mask clears half-words of
+// V.  M = 128, L = 50, 8192 rows: 107 us, near the 537 MB written (78 us at the rate of a fill); 187 us
+// with fp32 instructions and stores of 64 bytes of 16 rows.  Two waves a SIMD are needed, hence at
+// most 256 VGPRs: 317 us where the products were ordered over both unit blocks and spilled.
 template <bool ROW4, int KB>
 __global__ __launch_bounds__(256, 2) void k_jacform_big(const ShArgs a, const uint32_t *__restrict__ masks,
                                                      float *__restrict__ Jout, const int *__restrict__ active,
                                                      const float *__restrict__ gamma) {
-    __shared__ __align__(16) v4u w1s[8][KB][2][64];   // [row tile][k block][hi, lo][lane]
-    __shared__ float mxs[4][2];
+    __shared__ __align__(16) v4u w1s[8][KB][3][64];   // [row tile][k block][hi, mid, lo][lane]
     const int M = a.M, L = a.L, T = a.T, N = a.N;
     const int tid = threadIdx.x;
     const float p1 = __fsub_rn(1.0f, a.alpha);
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const float m1 = opaque_m1();
-    v4u vh[2][KB], vl[2][KB];
-    int sc;
-    {
-        float x1 = 0.f, x2 = 0.f;   // largest finite entries
-        for (int e = tid; e < M * L; e += 256) {
-            const float w1 = fabsf(a.W1[e]), w2 = fabsf(a.W2[e]);
-            x1 = fmaxf(x1, w1 < __builtin_inff() ? w1 : 0.f);
-            x2 = fmaxf(x2, w2 < __builtin_inff() ? w2 : 0.f);
-        }
-        x1 = __uint_as_float(wave_max_u32(__float_as_uint(x1)));
-        x2 = __uint_as_float(wave_max_u32(__float_as_uint(x2)));
-        if (lane == 0) {
-            mxs[wv][0] = x1;
-            mxs[wv][1] = x2;
-        }
-        __syncthreads();
-        x1 = fmaxf(fmaxf(mxs[0][0], mxs[1][0]), fmaxf(mxs[2][0], mxs[3][0]));
-        x2 = fmaxf(fmaxf(mxs[0][1], mxs[1][1]), fmaxf(mxs[2][1], mxs[3][1]));
-        const int s1 = min(13 - exp_of(x1), 126), s2 = min(13 - exp_of(x2), 126);   // W2 bounds V (0 <= p <= 1)
-        sc = -(s1 + s2);
+    v4u vq[3][2][KB];
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            auto put = [&](auto get, v4u &hi, v4u &lo) {
+    for (int kk = 0; kk < KB; ++kk)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    uint32_t h2, l2;
-                    split_pair(get(32 * kk + 8 * g + 2 * i), get(32 * kk + 8 * g + 2 * i + 1), m1, h2, l2);
-                    hi[i] = h2;
-                    lo[i] = l2;
+        for (int u = 0; u < 2; ++u) {
+            const int r = 16 * (2 * wv + u) + c;   // a row of W1, a column of V
+            const double p = r < N ? p1 : 1.f;
+            v4u wq[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float w1[2], w2[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int l = 32 * kk + 8 * g + 2 * i + e;
+                    w1[e] = r < M && l < L ? a.W1[(size_t)r * L + l] : 0.f;
+                    w2[e] = r < M && l < L ? a.W2[(size_t)l * M + r] : 0.f;
                 }
-            };
+                uint32_t part[3];
+                split_pair(w1[0], w1[1], part);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int r = 16 * (2 * wv + u) + c;   // a row of W1, a column of V
-                v4u hi, lo;
-                put([&](int l) { return r < M && l < L ? ldexpf(a.W1[(size_t)r * L + l], s1) : 0.f; }, hi, lo);
-                w1s[2 * wv + u][kk][0][lane] = hi;
-                w1s[2 * wv + u][kk][1][lane] = lo;
-                put([&](int l) { return r < M && l < L ? ldexpf(a.W2[(size_t)l * M + r] * (r < N ? p1 : 1.f), s2) : 0.f; },
-                    vh[u][kk], vl[u][kk]);
+                for (int q = 0; q < 3; ++q) wq[q][i] = part[q];
+                split_pair_f64(w2[0] * p, w2[1] * p, part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) vq[q][u][kk][i] = part[q];
             }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) w1s[2 * wv + u][kk][q][lane] = wq[q];
         }
-    }
     __syncthreads();
     const int LW = (L + 31) / 32;
-    const float f1 = ldexpf(1.f, sc / 2), f2 = ldexpf(1.f, sc - sc / 2);   // two factors: the scales may meet 2^252
     const auto cd_rs = bounded_rsrc(a.Cd, a.Cd ? (uint32_t)M * M * 4u : 0u);
     // diagonal A p of rows 16 I + 8 u + c % 8 (the transposed-tile stores)
     float dgI[8][2];
@@ -763,50 +745,41 @@ __global__ __launch_bounds__(256, 2) void k_jacform_big(const ShArgs a, const ui
         for (int I = 0; I < 8; ++I)
 #pragma unroll
             for (int Jt = 0; Jt < 2; ++Jt) acc[I][Jt] = (v4f){0.f, 0.f, 0.f, 0.f};
-        v4u bh[2][KB], bl[2][KB];
 #pragma unroll
         for (int kk = 0; kk < KB; ++kk) {
             const int by = (int)((kk ? wc1 : wc0) >> (8 * g));
+            v4u m;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t e0 = (uint32_t)((by << (31 - 2 * i)) >> 31), e1 = (uint32_t)((by << (30 - 2 * i)) >> 31);
-                const uint32_t m = (e0 & 0xffffu) | (e1 & 0xffff0000u);
+                m[i] = (e0 & 0xffffu) | (e1 & 0xffff0000u);
+            }
+            v4u vm[3][2];
 #pragma unroll
-                for (int Jt = 0; Jt < 2; ++Jt) {
-                    bh[Jt][kk][i] = vh[Jt][kk][i] & m;
-                    bl[Jt][kk][i] = vl[Jt][kk][i] & m;
-                }
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int Jt = 0; Jt < 2; ++Jt) vm[q][Jt] = vq[q][Jt][kk] & m;
+#pragma unroll
+            for (int I0 = 0; I0 < 8; I0 += 2) {
+                v4u wq[2][3];
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) wq[n][q] = w1s[I0 + n][kk][q][lane];
+                // parts of one order of magnitude, the smallest first.  ROW4: the transposed tile,
+                // V^T diag(m) W1^T
+#pragma unroll
+                for (int o = 2; o >= 0; --o)
+#pragma unroll
+                    for (int qa = o; qa >= 0; --qa)
+#pragma unroll
+                        for (int n = 0; n < 2; ++n)
+#pragma unroll
+                            for (int Jt = 0; Jt < 2; ++Jt)
+                                acc[I0 + n][Jt] = ROW4 ? mfma_b(vm[o - qa][Jt], wq[n][qa], acc[I0 + n][Jt])
+                                                       : mfma_b(wq[n][qa], vm[o - qa][Jt], acc[I0 + n][Jt]);
             }
         }
-#pragma unroll
-        for (int I0 = 0; I0 < 8; I0 += 4)
-#pragma unroll
-            for (int kk = 0; kk < KB; ++kk) {
-                v4u ah[4], al[4];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    ah[n] = w1s[I0 + n][kk][0][lane];
-                    al[n] = w1s[I0 + n][kk][1][lane];
-                }
-                // ROW4: the transposed tile, V^T diag(m) W1^T
-                auto mul = [&](const v4u (&w)[4], const v4u (&v)[2][KB]) {
-#pragma unroll
-                    for (int n = 0; n < 4; ++n)
-#pragma unroll
-                        for (int Jt = 0; Jt < 2; ++Jt)
-                            acc[I0 + n][Jt] = ROW4 ? mfma_h(v[Jt][kk], w[n], acc[I0 + n][Jt])
-                                                   : mfma_h(w[n], v[Jt][kk], acc[I0 + n][Jt]);
-                };
-                mul(al, bh);
-                mul(ah, bl);
-                mul(ah, bh);
-            }
-#pragma unroll
-        for (int I = 0; I < 8; ++I)
-#pragma unroll
-            for (int Jt = 0; Jt < 2; ++Jt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[I][Jt][r] = acc[I][Jt][r] * f1 * f2;
         // stores through a resource bounded at J~_s's end: rows past M fall outside it, columns
         // past M take an offset outside it
         const auto rs = bounded_rsrc(Jout + (size_t)grow * M * M, (uint32_t)M * M * 4u);

@@ -165,9 +165,10 @@ def test_vanilla_products_keep_24_bits(M):
 # ---- shallow PLRNN ------------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("bits", SPREADS)
-@pytest.mark.parametrize("M,L,N,T_w", [(5, 50, 3, 0), (32, 256, 32, 9), (64, 40, 10, 0)])
+@pytest.mark.parametrize("M,L,N,T_w", [(5, 50, 3, 0), (32, 256, 32, 9), (64, 40, 10, 0), (100, 50, 3, 0), (67, 30, 20, 9)])
 def test_shallow_units(M, L, N, T_w, bits):
-    """Newton iterates, lam and gradients, latents and hidden units in units of their own."""
+    """Newton iterates, lam and gradients, latents and hidden units in units of their own (M > 64: the
+    path that stores the Jacobians)."""
     os.environ["DEER_CHUNK"] = "12"
     B, T = 2, 90
     rng = np.random.default_rng(M)
@@ -190,7 +191,7 @@ def test_shallow_units(M, L, N, T_w, bits):
         assert np.array_equal(_np(a["grads"][k]) * u, _np(b["grads"][k])), k
 
 
-@pytest.mark.parametrize("M,L", [(6, 10), (30, 40), (64, 64)])
+@pytest.mark.parametrize("M,L", [(6, 10), (30, 40), (64, 64), (70, 64)])
 def test_shallow_products_keep_24_bits(M, L):
     os.environ["DEER_CHUNK"] = "16"
     B, T = 2, 200
@@ -207,6 +208,46 @@ def test_shallow_products_keep_24_bits(M, L):
     say("units shallow 24 bits", M, L)
     out = D.deer_adjoint(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1, g=g, z0=np.full((B, M), -1.0, np.float32))
     assert np.array_equal(_np(out["lam"]), lam(full))
+
+
+# ---- stored Jacobians, 64 < M <= 128 -------------------------------------------------------------------
+
+@pytest.mark.parametrize("bits", SPREADS)
+@pytest.mark.parametrize("M,L", [(65, 33), (100, 50), (128, 62)])
+def test_wide_jacobian_units(M, L, bits):
+    """J~ as the caller gets it."""
+    B, T, N = 2, 40, 20
+    rng = np.random.default_rng(M)
+    c = W.random_shplrnn_case(M, L, N, B, T, 0.2, 970 + M, w_norm=0.3)
+    p = c.params
+    z = rng.standard_normal((B, T, M)).astype(np.float32)
+    d, e = _units(M, bits, rng), _units(L, bits, rng)
+    q = {"A": p["A"], "W1": d[:, None] * p["W1"] / e, "W2": e[:, None] * p["W2"] / d, "h1": d * p["h1"], "h2": e * p["h2"]}
+    say("units wide jacobian", M, L, bits)
+    a = D.plrnn_jacobian(oracle_model(c), c.x, z, 0.2, N, dense_J=True)
+    b = D.plrnn_jacobian({"kind": "shplrnn", **q}, c.x * d[:N], z * d, 0.2, N, dense_J=True)
+    assert torch.equal(a["masks"], b["masks"])
+    assert np.array_equal(_np(a["J"]) * (d[:, None] / d), _np(b["J"]))
+
+
+def test_wide_jacobian_keeps_24_bits():
+    M, L, B, T = 128, 60, 1, 20
+    rng = np.random.default_rng(3)
+    z = rng.standard_normal((B, T, M)).astype(np.float32)
+    W1, W2 = np.zeros((M, L), np.float32), np.zeros((L, M), np.float32)
+    W1[2 * np.arange(L) + 1, np.arange(L)] = _mant(L, rng)
+    W2[np.arange(L), 2 * np.arange(L)] = 2.0 ** rng.integers(-9, 10, L)
+    m = {"kind": "shplrnn", "A": _mant(M, rng), "W1": W1, "W2": W2, "h1": np.zeros(M, np.float32),
+         "h2": np.zeros(L, np.float32)}
+    say("units wide jacobian 24 bits")
+    J = _np(D.plrnn_jacobian(m, np.zeros((B, T + 1, 1), np.float32), z, 0.0, 1,
+                             z0=rng.standard_normal((B, M)).astype(np.float32), dense_J=True)["J"])[:, 1:]
+    on = z[:, :-1, 2 * np.arange(L)] > 0
+    ref = np.zeros_like(J)
+    ref[..., np.arange(M), np.arange(M)] = m["A"]
+    ref[..., 2 * np.arange(L) + 1, 2 * np.arange(L)] = on * (W1[2 * np.arange(L) + 1, np.arange(L)]
+                                                              * W2[np.arange(L), 2 * np.arange(L)])
+    assert np.array_equal(J, ref)
 
 
 @pytest.mark.parametrize("bits", SPREADS)
