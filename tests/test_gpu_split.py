@@ -1,6 +1,6 @@
-"""Products on the fp16 matrix cores with split operands (PLRNN chunk products and carries, read-out):
-results against the float64 oracle's at the edges of the tiles, where the power-of-two scaling can go
-wrong, and where a chunk keeps its stored product."""
+"""Chunk products with split operands, the carries and walks beside them, and the read-out: results against
+the float64 oracle's at the edges of the tiles, for operands of very different size, and where a chunk
+keeps its stored product."""
 import os
 
 import numpy as np
@@ -49,8 +49,8 @@ def test_iterates(M, N, B, T, chunk, T_w):
         assert rel_inf(res["z"].cpu().numpy(), ref["z"]) < TOL
 
 
-# the operands' scales: weights far from one (the row-sum bound and the renormalisation period follow
-# them), a diagonal far below W, rows of very different size
+# weights far from one, a diagonal far below W, rows of very different size (units of the latents:
+# test_gpu_units.py)
 @pytest.mark.parametrize("M", [24, 64])
 @pytest.mark.parametrize("kind", ["large", "huge", "tiny", "rows", "zero"])
 def test_scales(M, kind):
@@ -82,7 +82,8 @@ def test_scales(M, kind):
 def test_kept_products(M, bound):
     """Updates past convergence keep every chunk's product (no mask changes), and with a small step
     bound rejected updates re-form them with another damping at unchanged masks: the fixed point
-    and a second, tighter solve from it agree with the rollout."""
+    and a second, tighter solve from it agree with the rollout (a product kept wrongly would slow the
+    solve, not move its result: the next two tests look at the iterates on the way)."""
     os.environ["DEER_CHUNK"] = "32"
     c = _case(M, M, 3, 500, 6200 + M, w_norm=0.35)
     m = oracle_model(c)
@@ -92,6 +93,91 @@ def test_kept_products(M, bound):
     assert res["status"] == 0 and rel_inf(res["z"].cpu().numpy(), ref) < TOL
     more = D.deer_solve(m, c.x, 0.2, M, fixed_iters=8)
     assert rel_inf(more["z"].cpu().numpy(), ref) < 1e-5
+
+
+def _chunked_newton(m, x, alpha, N, z, C, updates=0, passes=0, bound=0.0, stale=None):
+    """Newton passes of one sequence in float64, the linear solve in chunks of C steps as the library does
+    it: chunk products, carries, each chunk re-run from its carry with the pass's own Jacobians.  `updates`
+    plain updates, or `passes` passes of the safeguarded loop (an update over bound (1 + max |z|) is
+    rejected and tried again with damping 1 - om).  stale: products that should not be kept are, "masks"
+    those of the first pass, "damping" those whose masks stand though the damping changed.  Returns z, the
+    accepted updates and the smallest relative distance of an update from the bound."""
+    T, M = z.shape[1:]
+    z = z.astype(np.float64)
+    p = 1.0 - O.forcing_weights(M, N, alpha)
+    om, accepted, gap, P, old = 0.0, 0, np.inf, {}, None
+    for _ in range(updates or passes):
+        r, _, mask, _ = O.residual_and_masks(m, x, z, alpha, N)
+        J = (1.0 - om) * O.jacobian_dense({k: np.asarray(v, np.float64) if k != "kind" else v for k, v in m.items()}, mask)[0] * p
+        delta, cur = np.empty((T, M)), np.zeros(M)
+        for t0 in range(0, T, C):
+            t1 = min(t0 + C, T)
+            keep = old is not None and (stale == "masks" or stale == "damping"
+                                        and np.array_equal(old[0, t0:t1], mask[0, t0:t1]))
+            if not keep:
+                P[t0] = np.eye(M)
+                for t in range(t0, t1):
+                    P[t0] = J[t] @ P[t0]
+            d, v = cur, np.zeros(M)
+            for t in range(t0, t1):
+                d, v = J[t] @ d - r[0, t], J[t] @ v - r[0, t]
+                delta[t] = d
+            cur = P[t0] @ cur + v
+        old = mask
+        e, lim = np.abs(delta).max(), bound * (1.0 + np.abs(z).max())
+        if updates or om >= 1.0 or e <= lim:
+            z[0] += delta
+            accepted += 1
+            om = 0.0 if om / 4 < 1e-4 else om / 4
+        else:
+            om = 1.0 / 64 if om == 0.0 else min(1.0, om * 4)
+        if passes:
+            gap = min(gap, abs(e / lim - 1.0))
+    return z, accepted, gap
+
+
+def _stale_case(kind, M, L, w_norm):
+    """A wide-awake model and a start far from the solution: masks change in every pass."""
+    if kind == "plrnn":
+        c = W.random_plrnn_case(M, M, 1, 160, 0.2, 10 + M, w_norm=w_norm, a_range=(0.3, 0.75))
+    else:
+        c = W.random_shplrnn_case(M, L, M, 1, 160, 0.2, 10 + M, w_norm=w_norm, a_range=(0.3, 0.6))
+    z = 3.0 * np.random.default_rng(M).standard_normal((1, 160, M)).astype(np.float32)
+    return oracle_model(c), c.x[..., :1], z
+
+
+@pytest.mark.parametrize("kind,M,L,w_norm", [("plrnn", 20, 0, 0.9), ("plrnn", 33, 0, 0.9), ("plrnn", 64, 0, 0.9),
+                                             ("shplrnn", 5, 50, 4.0), ("shplrnn", 32, 64, 1.6), ("shplrnn", 64, 40, 2.2)])
+def test_products_follow_the_masks(kind, M, L, w_norm):
+    """Intermediate updates, where a product kept past a change of its masks would show (the fixed point
+    would not: the residual and the chunks' re-run are exact)."""
+    os.environ["DEER_CHUNK"] = "16"
+    m, x, z = _stale_case(kind, M, L, w_norm)
+    say("split masks", kind, M)
+    for k in (2, 3):
+        ref = _chunked_newton(m, x, 0.05, 1, z, 16, updates=k)[0]
+        bad = _chunked_newton(m, x, 0.05, 1, z, 16, updates=k, stale="masks")[0]
+        assert rel_inf(bad, ref) > 100 * TOL
+        res = D.deer_solve(m, x, 0.05, 1, fixed_iters=k, init="user", z=torch.tensor(z, device="cuda"))
+        assert rel_inf(res["z"].cpu().numpy(), ref) < TOL
+
+
+@pytest.mark.parametrize("kind,M,L,w_norm,bound,passes", [
+    ("plrnn", 20, 0, 1.1, 1.5, 3), ("plrnn", 64, 0, 0.9, 2.0, 3), ("shplrnn", 5, 50, 5.0, 10.0, 3),
+    ("shplrnn", 32, 64, 2.2, 3.0, 4), ("shplrnn", 64, 40, 4.0, 3.0, 3)])
+def test_products_follow_the_damping(kind, M, L, w_norm, bound, passes):
+    """A rejected update is tried again at the same masks with another damping: the iterate after a few
+    passes is that of products formed with it."""
+    os.environ["DEER_CHUNK"] = "16"
+    m, x, z = _stale_case(kind, M, L, w_norm)
+    ref, accepted, gap = _chunked_newton(m, x, 0.05, 1, z, 16, passes=passes, bound=bound)
+    bad = _chunked_newton(m, x, 0.05, 1, z, 16, passes=passes, bound=bound, stale="damping")[0]
+    assert 0 < accepted < passes and gap > 0.05 and rel_inf(bad, ref) > 100 * TOL
+    say("split damping", kind, M)
+    res = D.deer_solve(m, x, 0.05, 1, tol=0.0, max_iter=passes, step_bound=bound, init="user",
+                       z=torch.tensor(z, device="cuda"), check=False)
+    assert res["status"] == 2 and res["iters"][0] == accepted
+    assert rel_inf(res["z"].cpu().numpy(), ref) < TOL
 
 
 def test_nonfinite_weights():
