@@ -35,7 +35,8 @@ sys.path.insert(0, HERE)
 
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 PEAK_FP32_MFMA_TFLOPS = 157.3    # MI355X dense fp32 matrix
-PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 3   # fp32 products as three dense fp16 products of split operands
+PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16 matrix
+PEAK_SPLIT_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6   # fp32 products as six bf16 products of three-part operands
 # fp32 vector: 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz = 78.6 TFLOP/s.  The
 # published 157.3 counts packed fp32 (two FMAs per lane per instruction); the kernels are built
 # without packed instructions, so 78.6 is the ceiling they can reach and the peak used here.
@@ -218,7 +219,7 @@ def measured_traffic(workload, kernel):
 
 def measured_mfma(workload, kernel):
     """Matrix-core activity of the kernel from rocprofv3 counter passes
-    (SQ_INSTS_VALU_MFMA_MOPS_F32, SQ_VALU_MFMA_BUSY_CYCLES, GRBM_GUI_ACTIVE), kept in
+    (SQ_INSTS_VALU_MFMA_MOPS_F32 or _BF16, SQ_VALU_MFMA_BUSY_CYCLES, GRBM_GUI_ACTIVE), kept in
     profiles/mfma_<workload>.txt with the hash of the kernel's source; None once it changed."""
     import hashlib
     path = os.path.join(HERE, "profiles", f"mfma_{workload}.txt")
@@ -236,7 +237,7 @@ def measured_mfma(workload, kernel):
         return None
     tf = float(rec["mfma_counted_tflops"])
     return {"busy_frac": float(rec["mfma_busy_frac"]), "counted_tflops": tf,
-            "counted_frac": tf / PEAK_FP32_MFMA_TFLOPS,
+            "counted_frac": tf / float(rec.get("mfma_peak_tflops", PEAK_FP32_MFMA_TFLOPS)),
             "counted_flops_per_launch": float(rec["mfma_flops_per_dispatch"]),
             "source": f"profiles/mfma_{workload}.txt"}
 
@@ -251,7 +252,8 @@ def roofline_for(name, c, total_ms, launches, steps, updates):
         return base
     bound, w = work[name]
     if w is None:
-        base.update({"bound": bound, "achieved": None, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": None})
+        base.update({"bound": bound, "achieved": None, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": None,
+                     "mfma_counters": measured_mfma(c.name, name)})
     elif bound == "mfma_split":
         ach = w / (total_ms * 1e-3) / 1e12
         base.update({"bound": bound, "achieved": ach, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",

@@ -151,6 +151,9 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// diagonal entry i of P_alpha: the part of latent i that the forcing keeps
+__device__ __forceinline__ float p_of(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
+
 __device__ __forceinline__ float forced_state(const float *__restrict__ x, const float *__restrict__ z0,
                                               const float *__restrict__ z, int b, int s, int i, int T, int M,
                                               int N, float alpha, int tw = 0) {

@@ -17,8 +17,6 @@ namespace deer {
 template <int MP>
 struct DGeo {
     static constexpr int NCH = 64 / MP;
-    static constexpr int NI = MP / 16;
-    static constexpr int NS = MP / 4;
 };
 
 // ---------------------------------------------------------------------------------------
@@ -34,7 +32,7 @@ struct DGeo {
 // one wave or two run on a SIMD, so a step otherwise waits for its load (M = 32, 4 x 8000 steps:
 // 58 us forward and 51 us reverse; with one step in flight and two chains a wave 70 us, and 155 us
 // with the local solution of the reverse on the vector units).
-// The first matrix of a sequence multiplies a zero state: it is not read.
+// The first matrix of a sequence multiplies a zero state: it is loaded but not used.
 // P is stored as the carries take it: Q forward, Q^T reverse.
 // ---------------------------------------------------------------------------------------
 template <int MP, bool REV, bool TR>

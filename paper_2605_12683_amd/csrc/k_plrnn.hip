@@ -31,8 +31,6 @@ struct Geo {
     static constexpr int MW = MP <= 32 ? 1 : 2;   // mask words per step
 };
 
-__device__ __forceinline__ float p_of(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
-
 // Latent warm-up (section "Latent state warm-up", Alg. GTF-DEER): the forced inputs of steps
 // s = 1..tw replace the observed latents by the data (alpha_s = 1, P_1), so those steps'
 // Jacobians have the observed columns zeroed.  Kernels take it as a template flag WU; without it

@@ -22,8 +22,6 @@
 
 namespace deer {
 
-__device__ __forceinline__ float pf_at(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
-
 static int shf_LP(int L) { return (L + 15) / 16 * 16; }
 
 // l tiles per wave of the walks (4 waves share the (L + 15) / 16 tiles)
@@ -113,7 +111,7 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
     for (int e = tid; e < LB * NI * 64; e += NWV * 64) {
         const int ln = e & 63, I = (e >> 6) % NI, kb = (e >> 6) / NI;
         const int i = 16 * I + (ln & 15), l0 = 32 * kb + 8 * (ln >> 4);
-        const double p = pf_at(i, N, a.alpha);
+        const double p = p_of(i, N, a.alpha);
         v4u pa[3], pb[3];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
@@ -149,7 +147,7 @@ __device__ __forceinline__ void sh_chunk_product(const ShArgs &a, const uint32_t
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = 16 * Jt + c;
-            dgr[Jt][r] = (c == 4 * g + r && row < M) ? (float)((double)a.A[row] * gm * pf_at(row, N, a.alpha)) : 0.f;
+            dgr[Jt][r] = (c == 4 * g + r && row < M) ? (float)((double)a.A[row] * gm * p_of(row, N, a.alpha)) : 0.f;
         }
     v4f acc[NI][NI];
 #pragma unroll
@@ -336,7 +334,7 @@ __device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__re
         for (int s = 0; s < NS; ++s) {
             const int i = 16 * (s / 4) + 4 * g + (s % 4);
             const bool e = lt < nlt && l < L && i < M;
-            a1[k][s] = !e ? 0.f : REV ? a.W1[(size_t)i * L + l] : a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha);
+            a1[k][s] = !e ? 0.f : REV ? a.W1[(size_t)i * L + l] : a.W2[(size_t)l * M + i] * p_of(i, N, a.alpha);
         }
     }
 #pragma unroll
@@ -348,7 +346,7 @@ __device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__re
                 const int lt = wv * NLW + k, i = 16 * I + c, l = 16 * lt + 4 * g + q;
                 const bool e = lt < nlt && i < M && l < L;
                 a2[I][4 * k + q] =
-                    !e ? 0.f : REV ? a.W2[(size_t)l * M + i] * pf_at(i, N, a.alpha) : a.W1[(size_t)i * L + l];
+                    !e ? 0.f : REV ? a.W2[(size_t)l * M + i] * p_of(i, N, a.alpha) : a.W1[(size_t)i * L + l];
             }
     const int nchains = a.B * ncs;
     const int id = (block * NG + grp) * 16 + c;
@@ -377,7 +375,7 @@ __device__ __forceinline__ void shjvp_walk(const ShArgs &a, const uint32_t *__re
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = 16 * I + 4 * g + r;
-            dg[I][r] = i < M ? a.A[i] * pf_at(i, N, a.alpha) : 0.f;
+            dg[I][r] = i < M ? a.A[i] * p_of(i, N, a.alpha) : 0.f;
             dl[I][r] = (!LOCAL && ok && i < M) ? carry_in[(size_t)id * MP + i] : 0.f;
         }
     const size_t rowb = (size_t)b * T;

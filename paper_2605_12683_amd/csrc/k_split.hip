@@ -19,8 +19,6 @@
 
 namespace deer {
 
-__device__ __forceinline__ float sp_p(int i, int N, float alpha) { return i < N ? __fsub_rn(1.0f, alpha) : 1.0f; }
-
 // mask word of 32 latents from its eight nibbles, one per byte
 __device__ __forceinline__ uint32_t pack_nibbles(const uint8_t *n8) {
     const uint2 n = *reinterpret_cast<const uint2 *>(n8);
@@ -38,8 +36,11 @@ __device__ __forceinline__ uint32_t pack_nibbles(const uint8_t *n8) {
 // puts relu(z~) and m p u of its latents in LDS (double-buffered, one barrier a step), and two
 // products with the rows of W (A fragments in registers, fp32 matrix cores) follow:
 //   F = A z~ + W relu(z~) + h,  r = z - F;     u <- gamma (A p u + W (m p u)) - r
-// The rows of z and x of PD steps are in flight in a register double buffer.  HBM-bound: z and x
-// read, r and the masks written (M = 64, 32 x 131072 steps: 0.92 ms, 3.5 TB/s).  VEC: M and N multiples of 4 and x, z 16-byte aligned.
+// The rows of z and x of PD steps are in flight in a register double buffer: 8 steps of 16-byte loads,
+// or 4 of scalar loads, whose addresses take more registers.  Bound by the chain of a step, half of it
+// fp32 matrix instructions (32 a wave at M = 64), the rest the exchange through LDS and the barrier
+// (M = 64, 32 x 131072 steps: 0.92 ms; z and x read, r and the masks written at 3.5 TB/s).  VEC: M and
+// N multiples of 4 and x, z 16-byte aligned.
 // The masks of four steps are put together from LDS and stored by one wave, which reads the
 // words they replace ahead and reports any difference in changed[chunk].
 // ---------------------------------------------------------------------------------------
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(MP * 4) void k_newton_local_plrnn(
         const bool lat = i0 + q < M;
         Av[q] = lat ? A[i0 + q] : 0.f;
         hv[q] = lat && h ? h[i0 + q] : 0.f;
-        pv[q] = sp_p(i0 + q, N, alpha);
+        pv[q] = p_of(i0 + q, N, alpha);
         fo[q] = i0 + q < N;
     }
     const float gm = gamma ? gamma[b] : 1.f;
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(kSplitWaves<MP> * 64) __attribute__((amdgpu_waves_p
     }
     for (int I = wv; I < NI; I += NW) {
         const int row = 16 * I + c;
-        const double ad = row < M ? (double)A[row] * gm * sp_p(row, N, alpha) : 0.0;
+        const double ad = row < M ? (double)A[row] * gm * p_of(row, N, alpha) : 0.0;
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(kSplitWaves<MP> * 64) __attribute__((amdgpu_waves_p
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const int k = 16 * j + 4 * g + 2 * h2 + e;
-                    w[e] = (row < M && k < M) ? (double)W[row * M + k] * gm * sp_p(k, N, alpha) : 0.0;
+                    w[e] = (row < M && k < M) ? (double)W[row * M + k] * gm * p_of(k, N, alpha) : 0.0;
                     w[e] += k == row ? ad : 0.0;
                 }
                 uint32_t part[3];
@@ -447,9 +448,11 @@ __global__ __launch_bounds__(kSplitWaves<MP> * 64) __attribute__((amdgpu_waves_p
 //     dimension), two steps at a time in fp32 and those sums in float64, one partial
 //     gpart[block][MP][MP + 2] per block.
 // z~_k = forced(z_{k-1}, x_k) serves the gradient of step k and is the mask of step k - 1's Jacobian
-// term; the same rows give the MSE seed of step k - 1.  HBM-bound: z, x (and g) read, lam written
-// (M = 64, 32 x 131072 steps: 0.82 ms, and 1.15 ms with the gradients; the lane-per-latent kernel with
-// the gradient products on the vector units took 3.8 ms).
+// term; the same rows give the MSE seed of step k - 1.  Bound by the chain of a step as
+// k_newton_local_plrnn is (M = 64, 32 x 131072 steps: 0.83 ms, and 1.14 ms with the gradients; the
+// lane-per-latent kernel with the gradient products on the vector units took 3.8 ms).  Rows in flight:
+// 8 steps where only z and x are read in 16-byte loads, else 4 (three rows a step, or the gradient
+// sums, leave no registers for more).
 // ---------------------------------------------------------------------------------------
 template <int MP, bool VEC, bool WU, bool GIN, bool FINAL>
 __global__ __launch_bounds__(MP * 4) __attribute__((amdgpu_waves_per_eu(2))) void k_adjoint_walk_plrnn(
@@ -484,7 +487,7 @@ __global__ __launch_bounds__(MP * 4) __attribute__((amdgpu_waves_per_eu(2))) voi
     for (int q = 0; q < 4; ++q) {
         la[q] = i0 + q < M;
         Av[q] = la[q] ? A[i0 + q] : 0.f;
-        pv[q] = sp_p(i0 + q, N, alpha);
+        pv[q] = p_of(i0 + q, N, alpha);
         fo[q] = i0 + q < N;
     }
     const size_t rowb = (size_t)b * T, rowx = (size_t)b * (T + 1);

@@ -371,7 +371,7 @@ def test_readout_scales(B, T, M, H, No, kind):
         return
     rows = np.ones((B, T), bool)
     rows[0, 5] = kind not in ("nan", "inf")
-    # decisions: fp32 sums of M products and the split's 2^-20 are within 1e-5 of sum |Wa| |h| + |ca|
+    # decisions: fp32 sums of M products are within 1e-5 of sum |Wa| |h| + |ca|
     band = 1e-5 * (np.abs(h.real.astype(np.float64)) @ np.abs(p["Wa"].astype(np.float64)).T + np.abs(p["ca"]))
     clear = (np.abs(s) > band) & rows[..., None]
     assert np.array_equal(on[clear], (s > 0)[clear])
